@@ -274,8 +274,10 @@ hipError_t launch_map_update(const Ws &ws, const vtgs_map_cfg &cfg, int32_t *ste
                              int max_n, hipStream_t st);
 int64_t rec_scan_blocks(int64_t n_rec);
 
-// visibility: targets of one launch, passed by value
-constexpr int kVisMaxTargets = 16;
+// visibility: targets of one launch, passed by value (40 B each; a launch
+// more costs the frame another pass over its depths and mask, and an
+// overlap selection tests some 5 to 30 candidates)
+constexpr int kVisMaxTargets = 32;
 struct VisCam {
   float fx, fy, cx, cy;
   int32_t width, height;
