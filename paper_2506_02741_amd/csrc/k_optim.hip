@@ -436,15 +436,37 @@ __global__ __launch_bounds__(kNT) void k_gather_accumulate(Ws ws) {
   if (ws.slot_w == 8 && K.geo) store_pose_partial(ws, kf, tw, lds);
 }
 
-// Per keyframe with geometry: the blocks' pose partials summed in order,
-// added into g_pose.
-__global__ __launch_bounds__(kWave) void k_kpose_accumulate(Ws ws) {
+// Sum of keyframe kf's pose twist partials over its gather blocks, block by
+// block in order, valid in threads 0-5 (thread c: component c).  A latency
+// chain, not a bandwidth one: with a dependent add per load from memory,
+// one thread walking all six sums of a 640x480 keyframe's 1,200 partials
+// took 455 us; staged through LDS a block of partials at a time, six lanes
+// adding them up side by side, it takes 16 us.
+__device__ __forceinline__ float reduce_pose_partials(const Ws &ws, int kf, float4 (*lds)[2]) {
+  const float4 *pp = (const float4 *)(ws.kpose_part + (int64_t)kf * ws.gblocks * 8);
+  const int c = threadIdx.x;
+  float s = 0.f;
+  for (int b0 = 0; b0 < ws.gblocks; b0 += kNT) {
+    const int n = min(kNT, ws.gblocks - b0);
+    for (int i = threadIdx.x; i < 2 * n; i += kNT) lds[i / 2][i % 2] = pp[2 * b0 + i];
+    __syncthreads();
+    if (c < 6) {
+#pragma unroll 8
+      for (int b = 0; b < n; b++) s += ((const float *)lds[b])[c];
+    }
+    __syncthreads();
+  }
+  return s;
+}
+
+// Per keyframe with geometry: its pose partials summed, added into g_pose.
+__global__ __launch_bounds__(kNT) void k_kpose_accumulate(Ws ws) {
+  __shared__ float4 lds[kNT][2];
   const int kf = blockIdx.x;
   const DevKF &K = ws.kfs[kf];
-  if (!K.learnable || !K.geo || !K.g_pose || threadIdx.x >= 6) return;
-  float s = 0.f;
-  for (int b = 0; b < ws.gblocks; b++) s += ws.kpose_part[((int64_t)kf * ws.gblocks + b) * 8 + threadIdx.x];
-  K.g_pose[threadIdx.x] += s;
+  if (!K.learnable || !K.geo || !K.g_pose) return;  // uniform over the block
+  const float s = reduce_pose_partials(ws, kf, lds);
+  if (threadIdx.x < 6) K.g_pose[threadIdx.x] += s;
 }
 
 __global__ __launch_bounds__(kNT) void k_map_adam(Ws ws, vtgs_map_cfg cfg, const int32_t *step) {
@@ -498,16 +520,16 @@ __global__ __launch_bounds__(kNT) void k_map_adam(Ws ws, vtgs_map_cfg cfg, const
 // Adam on the left twist of a keyframe pose (lr_trans on rho, lr_rot on
 // phi; step count in pose_adam[12]) from its blocks' partials, then
 // pose <- exp(step^) pose: bundle adjustment inside the mapping step.
-__global__ __launch_bounds__(kWave) void k_kpose_update(Ws ws, vtgs_map_cfg cfg) {
+__global__ __launch_bounds__(kNT) void k_kpose_update(Ws ws, vtgs_map_cfg cfg) {
+  __shared__ float4 lds[kNT][2];
+  __shared__ float g[6];
   const int kf = blockIdx.x;
   const DevKF &K = ws.kfs[kf];
-  if (!K.learnable || !K.geo || !K.pose_adam || threadIdx.x != 0) return;
-  float g[6];
-  for (int c = 0; c < 6; c++) {
-    float s = 0.f;
-    for (int b = 0; b < ws.gblocks; b++) s += ws.kpose_part[((int64_t)kf * ws.gblocks + b) * 8 + c];
-    g[c] = s;
-  }
+  if (!K.learnable || !K.geo || !K.pose_adam) return;  // uniform over the block
+  const float s = reduce_pose_partials(ws, kf, lds);
+  if (threadIdx.x < 6) g[threadIdx.x] = s;
+  __syncthreads();
+  if (threadIdx.x != 0) return;
   bool finite = true;
   for (int c = 0; c < 6; c++) finite &= __builtin_isfinite(g[c]);
   if (!finite) { atomicOr(ws.flags, kFlagNonfinite); return; }
@@ -571,7 +593,7 @@ hipError_t launch_gather(const Ws &ws, int max_n, hipStream_t st) {
   hipLaunchKernelGGL(k_gather_accumulate, dim3((max_n + kNT - 1) / kNT, ws.n_kf), dim3(kNT), 0, st,
                      ws);
   if (ws.slot_w == 8)
-    hipLaunchKernelGGL(k_kpose_accumulate, dim3(ws.n_kf), dim3(kWave), 0, st, ws);
+    hipLaunchKernelGGL(k_kpose_accumulate, dim3(ws.n_kf), dim3(kNT), 0, st, ws);
   return hipGetLastError();
 }
 
@@ -585,7 +607,7 @@ hipError_t launch_map_update(const Ws &ws, const vtgs_map_cfg &cfg, int32_t *ste
     hipLaunchKernelGGL(k_map_adam, dim3((max_n + kNT - 1) / kNT, ws.n_kf), dim3(kNT), 0, st, ws,
                        cfg, (const int32_t *)step);
     if (ws.slot_w == 8)
-      hipLaunchKernelGGL(k_kpose_update, dim3(ws.n_kf), dim3(kWave), 0, st, ws, cfg);
+      hipLaunchKernelGGL(k_kpose_update, dim3(ws.n_kf), dim3(kNT), 0, st, ws, cfg);
   }
   return hipGetLastError();
 }
