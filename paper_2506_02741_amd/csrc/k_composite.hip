@@ -3,15 +3,14 @@
 //
 // One workgroup per (view, tile).  Each wave owns a square block of the
 // tile (8x8 pixels, or 16x16 for 32-pixel tiles with four pixels per lane).
-// The tile's depth-sorted list is walked in batches staged through LDS;
-// while staging, the block marks for every wave which entries may reach
-// the wave's pixels -- extent box touching its block and block inside the
-// entry's cull circle (one 64-bit mask per wave and 64 entries) -- and each
-// wave then visits only the set bits of its masks with scalar bit scans,
-// four entries per step, recording for each lane which entries reach its
-// pixel (q <= q_cut, the exact test).  The lanes then composite their own entries of a
-// group of chunks (up to 256 entries) as one stream each, so a wave takes as
-// many steps as its busiest lane has entries in the whole group.
+// The tile's depth-sorted list is walked in batches staged through LDS.
+// Which entries reach which pixels is a matrix product (Coverage below): the
+// conic's q(x, y) - q_cut is a polynomial in the pixel's tile coordinates,
+// six coefficients per entry against six monomials per pixel, and the signs
+// of the MFMA's results are every lane's bit mask of the entries that may
+// reach its pixel.  The lanes then composite their own entries of a group of
+// chunks (up to 256 entries) as one stream each, with the exact test, so a
+// wave takes as many steps as its busiest lane has entries in the group.
 //
 // Forward, per pixel, front to back [splat of Sec. 3.3]:
 //   q = d^T Q d with d = pixel - mu; skip q > q_cut
@@ -86,57 +85,117 @@ __device__ __forceinline__ void lane_pixel(int k, int &x, int &y) {
   y = qy + l / 8 + 8 * (k / 2);
 }
 
-// Origin of wave ww's pixel block relative to the tile origin.
+// ---------------------------------------------------------------------------
+// Coverage: which entries of a chunk reach which pixels of a wave's block
+// ---------------------------------------------------------------------------
+// With X, Y the pixel's integer offsets from the tile's middle (|X|, |Y| <=
+// H = TILE / 2) and m the mean's,
+//   q - q_cut = A X^2 + B X Y + C Y^2 + D X + E Y + F,
+//   A = qa, B = 2 qb, C = qc, D = -(2 A mx + B my), E = -(B mx + 2 C my),
+//   F = A mx^2 + B mx my + C my^2 - q_cut,
+// a dot product of 16 bf16 terms: the monomials are exact in bf16 (products
+// of integers up to 16 are at most 256), A, B, C enter as two bf16 pieces
+// and D, E, F as three, the products are exact and their sum is FP32.  It
+// errs by at most
+//   |A X^2| .. : 2^-16 H^2 (|A| + |B| + |C|)        (two pieces)
+//   the rest, and the FP32 q of the exact test: a few dozen roundings of
+//   terms below (|A| + |B| + |C|) (|m| + H)^2 each, taken as 2^-18 of that
+// and F is lowered by that much, so the sign is set for every pixel the exact
+// test (FP32, q <= q_cut) accepts, and for few others (about 0.03 per entry
+// and block): the compositing step repeats the exact test and takes their
+// bits back out.  A conic too large for the bound to be finite is tried at
+// every pixel.  One v_alignbit per two (entry, 32 pixels) results moves the
+// signs into the lanes' masks, so 64 entries against 64 pixels cost 4 MFMAs
+// and ~75 VALU instructions; testing q per (entry, pixel) on the VALU took
+// 12.75 for each entry whose cull circle met the block, ~380 per chunk.
+typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+typedef float f32x16 __attribute__((ext_vector_type(16)));
+
+// One entry's 16 bf16 coefficients, terms 0-7 in lo and 8-15 in hi (the
+// halves the lower and upper 32 lanes of an MFMA operand hold).  absent: an
+// entry past the list's end, or of an id out of range, reaches no pixel.
 template <int TILE>
-__device__ __forceinline__ void block_of(int ww, int &x0, int &y0) {
-  if (TILE == 8) { x0 = 0; y0 = 0; return; }
-  x0 = (ww % 2) * Shape<TILE>::WB;
-  y0 = (ww / 2) * Shape<TILE>::WB;
+__device__ __forceinline__ void coverage_row(bool absent, float mx, float my, float A, float B,
+                                             float C, float qcut, float cx, float cy, bf16x8 &lo,
+                                             bf16x8 &hi) {
+  constexpr float H = (float)(TILE / 2);
+  mx -= cx;
+  my -= cy;
+  float D = -fmaf(2.0f * A, mx, B * my), E = -fmaf(2.0f * C, my, B * mx);
+  const float S = fabsf(A) + fabsf(B) + fabsf(C);
+  const float M = fmaxf(fabsf(mx), fabsf(my)) + H;
+  const float slack = fmaf(S, fmaf(M * M, 0x1p-18f, H * H * 0x1p-16f), 1e-5f * qcut);
+  float F = fmaf(-0.5f, fmaf(D, mx, E * my), -(qcut + slack));
+  const bool bounded = slack < 1e30f;  // (false for NaN)
+  const bool flat = absent || !bounded;
+  A = flat ? 0.f : A; B = flat ? 0.f : B; C = flat ? 0.f : C;
+  D = flat ? 0.f : D; E = flat ? 0.f : E;
+  F = absent ? 1.0f : (bounded ? F : -1.0f);
+  auto piece = [](float &x) {  // the leading bf16 of x, which keeps the rest
+    const __bf16 b = (__bf16)x;
+    x -= (float)b;
+    return b;
+  };
+  lo[0] = piece(A); lo[1] = (__bf16)A;
+  lo[2] = piece(B); lo[3] = (__bf16)B;
+  lo[4] = piece(C); lo[5] = (__bf16)C;
+  lo[6] = piece(F); lo[7] = piece(F);
+  hi[0] = piece(D); hi[1] = piece(D); hi[2] = (__bf16)D;
+  hi[3] = piece(E); hi[4] = piece(E); hi[5] = (__bf16)E;
+  hi[6] = (__bf16)F; hi[7] = (__bf16)0.f;
 }
 
-// Squared radius of a circle around mu that holds every offset d with
-// d^T Q d <= q_cut: |d|^2 <= q_cut / lambda_min(Q) = q_cut lambda_max / det,
-// widened by 2 % so that the FP32 value of q can never pass the cut outside
-// it.  A conic that is not positive definite gets no circle (box test only).
-__device__ __forceinline__ float cull_r2(float qa, float qb, float qc, float qcut) {
-  // (hardware square root and reciprocal, ~1 ulp: far inside the 2 %)
-  const float h = 0.5f * (qa - qc);
-  const float lmax = 0.5f * (qa + qc) + __builtin_amdgcn_sqrtf(fmaf(h, h, qb * qb));
-  const float det = fmaf(qa, qc, -qb * qb);
-  return det > 0.f ? 1.0201f * qcut * lmax * __builtin_amdgcn_rcpf(det) : 3.0e38f;
+// The monomials of pixel (l % 32) + 32 n of a lane's k-th 8x8 sub-block, in
+// the order of coverage_row's terms (lanes 0-31 terms 0-7, 32-63 terms 8-15).
+template <int TILE>
+__device__ __forceinline__ bf16x8 coverage_pixel(int k, int n) {
+  const int w = threadIdx.x / kWave, l = lane_id(), p = (l & 31) + 32 * n;
+  const int qx = TILE == 8 ? 0 : (w % 2) * Shape<TILE>::WB, qy = TILE == 8 ? 0 : (w / 2) * Shape<TILE>::WB;
+  const float X = (float)(qx + p % 8 + 8 * (k % 2) - TILE / 2);
+  const float Y = (float)(qy + p / 8 + 8 * (k / 2) - TILE / 2);
+  const bool lower = l < 32;
+  const float a = lower ? X * X : X, c = lower ? Y * Y : Y, b = lower ? X * Y : X;
+  const float d = lower ? X * Y : Y;
+  bf16x8 r;
+  r[0] = r[1] = (__bf16)a;
+  r[2] = (__bf16)b; r[3] = (__bf16)d;
+  r[4] = r[5] = (__bf16)c;
+  r[6] = (__bf16)1.0f; r[7] = (__bf16)(lower ? 1.0f : 0.f);
+  return r;
 }
 
-// Wave masks of a staged batch: bit (i % 64) of masks[ww][i / 64] is set
-// when entry i is present and reaches wave ww's pixel block: its extent box
-// mu +- R touches the block and the block lies within the cull circle.
-// Called by every lane (the ballot is wave-wide); the lanes of a wave stage
-// 64 consecutive entries, so i / 64 is uniform.
-template <int TILE, int NCH>
-__device__ __forceinline__ void stage_masks(unsigned long long (*masks)[NCH], int i, bool have,
-                                            const float4 &e0, float qc, float R, float qcut,
-                                            float ox, float oy) {
-  constexpr int NW = Shape<TILE>::NT / kWave, WB = Shape<TILE>::WB;
-  const float r2 = cull_r2(e0.z, e0.w, qc, qcut);
+// Lane masks of 32 staged entries whose rows are `a` (coverage_entry gives
+// the entry a lane loads): bit e is set where entry e may reach the lane's
+// pixel of the sub-block with monomials pix.
+__device__ __forceinline__ uint32_t coverage32(const bf16x8 &a, const bf16x8 (&pix)[2]) {
+  const f32x16 zero = {};
+  const f32x16 c0 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, pix[0], zero, 0, 0, 0);
+  const f32x16 c1 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, pix[1], zero, 0, 0, 0);
+  // result i of a lane is row 8 (i / 4) + 4 (l / 32) + i % 4, column l % 32:
+  // the upper lanes hold the other rows of the same 32 pixels
+  uint32_t b0 = 0u, b1 = 0u;
 #pragma unroll
-  for (int ww = 0; ww < NW; ww++) {
-    int x0, y0;
-    block_of<TILE>(ww, x0, y0);
-    const float bx0 = ox + (float)x0, by0 = oy + (float)y0;
-    const float bx1 = bx0 + (float)(WB - 1), by1 = by0 + (float)(WB - 1);
-    const bool miss = (e0.x + R < bx0) | (e0.x - R > bx1) | (e0.y + R < by0) | (e0.y - R > by1);
-    // distance from mu to the nearest pixel centre of the block
-    const float gx = fmaxf(fmaxf(bx0 - e0.x, e0.x - bx1), 0.f);
-    const float gy = fmaxf(fmaxf(by0 - e0.y, e0.y - by1), 0.f);
-    const bool far = fmaf(gx, gx, gy * gy) > r2;
-    const unsigned long long m = ballot64(have && !miss && !far);
-    if (lane_id() == 0) masks[ww][i / kWave] = m;
+  for (int i = 15; i >= 0; i--) {
+    b0 = __builtin_amdgcn_alignbit(b0, __float_as_uint(c0[i]), 31);
+    b1 = __builtin_amdgcn_alignbit(b1, __float_as_uint(c1[i]), 31);
   }
+  // b0's upper half (pixels 0-31) changes places with b1's lower half
+  // (pixels 32-63): every lane then holds both masks of its own pixel
+  const auto r = __builtin_amdgcn_permlane32_swap(b0, b1, false, false);
+  return r[0] | (r[1] << 16);
 }
 
-__device__ __forceinline__ unsigned long long uniform_u64(unsigned long long v) {
-  const uint32_t lo = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)v);
-  const uint32_t hi = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(v >> 32));
-  return ((unsigned long long)hi << 32) | lo;
+// Entry of 32 whose row lane l loads: the rows a lane's results come from
+// (above) are entries 0-15 in order for the lower lanes, 16-31 for the upper.
+__device__ __forceinline__ int coverage_entry() {
+  const int r = lane_id() & 31;
+  return 16 * ((r >> 2) & 1) + 4 * (r >> 3) + (r & 3);
+}
+
+// Lanes as a scalar mask, and back.
+__device__ __forceinline__ unsigned long long lanes(bool p) { return __builtin_amdgcn_ballot_w64(p); }
+__device__ __forceinline__ bool in_lanes(unsigned long long m) {
+  return __builtin_amdgcn_inverse_ballot_w64(m);
 }
 
 // First u64 of the lane bits of chunk c of the batch at list offset `boff`
@@ -162,12 +221,15 @@ __device__ __forceinline__ float quad2(const float4 &e0, float qc, float px, flo
 // Chunks of 64 entries whose lane bits one phase-2 pass walks as a single
 // stream per lane (a lane then steps once per entry that reaches its pixel,
 // not once per entry of the busiest lane of every chunk).  Four pixels per
-// lane keep one chunk per pass to bound the LDS word lists.
+// lane keep one chunk per pass to bound the LDS words.
 template <int TILE, int BATCH>
 struct Group {
   static constexpr int NCB = BATCH / kWave;  // chunks of a full batch
   static constexpr int G = Shape<TILE>::PPT > 1 ? 1 : (NCB < 4 ? NCB : 4);
-  static constexpr int NS = 2 * G + 2;       // LDS word slots per pixel
+  static constexpr int NS = 2 * G + 2;       // LDS word slots per pixel (backward)
+  // the forward's passes may be longer: it keeps no per-entry state
+  static constexpr int GF = Shape<TILE>::PPT > 1 ? 1 : (NCB < 8 ? NCB : 8);
+  static constexpr int NH = 2 * GF;          // 32-entry words of a forward pass
 };
 
 // Word list of one pixel-lane: the nonzero 32-entry halves of its bits in
@@ -198,17 +260,23 @@ __device__ __forceinline__ void fetch_record(const Ws &ws, int n_rec, int rec_ba
   e0 = A[0]; e1 = A[1]; e2 = A[2];
 }
 
+// Waves per SIMD the register budget leaves room for (tile 16 with 256-entry
+// batches: the five blocks per CU its LDS allows); two or more also keep the
+// MFMA results in VGPRs, which the sign extraction reads directly.
 template <int TILE, int BATCH>
-__global__ __launch_bounds__(Shape<TILE>::NT) void k_fwd(Ws ws, float *out_rgb, float *out_depth,
-                                                         float *out_sil) {
+__global__ __attribute__((amdgpu_waves_per_eu(TILE == 16 && BATCH <= 256 ? 5 : 2))) __launch_bounds__(
+    Shape<TILE>::NT) void k_fwd(Ws ws, float *out_rgb, float *out_depth, float *out_sil) {
   constexpr int NT = Shape<TILE>::NT, PPT = Shape<TILE>::PPT;
   constexpr int NW = NT / kWave;
   constexpr int PER = (BATCH + NT - 1) / NT;  // list entries each thread stages per batch
-  constexpr int NCH = PER * NT / kWave;       // 64-entry chunks of a staged batch
-  constexpr int G = Group<TILE, BATCH>::G, NS = Group<TILE, BATCH>::NS, NR = NW * PPT;
-  __shared__ float4 e0s[BATCH], e1s[BATCH], e2s[BATCH];
-  __shared__ unsigned long long masks[NW][NCH];
-  __shared__ uint32_t words[NS][NR][kWave];
+  constexpr int SB = PER * NT;                // entries a batch's staging covers
+  constexpr int G = Group<TILE, BATCH>::GF, NH = Group<TILE, BATCH>::NH, NR = NW * PPT;
+  // staged entry: e0 (mx, my, qa, 2 qb), e1 (qc, o; at e0's stride, so that
+  // one address serves all three), e2 (c, z); 32 entries more, never
+  // written, that a finished lane's last reads fall into
+  __shared__ float4 e0s[BATCH + 32], e1s[BATCH + 32], e2s[BATCH + 32];
+  __shared__ bf16x8 cov[2][SB];               // coverage rows, terms 0-7 and 8-15
+  __shared__ uint32_t words[NH + 1][NR][kWave];  // the lanes' bits of a pass; the last row zero
   const int t = tile_of_block(ws);
   const DevView &vw = ws.views[find_view_by_tile(ws, t)];
   const int lt = t - vw.tile_base;
@@ -219,7 +287,8 @@ __global__ __launch_bounds__(Shape<TILE>::NT) void k_fwd(Ws ws, float *out_rgb, 
 
   float px[PPT], py[PPT], T[PPT], C0[PPT], C1[PPT], C2[PPT], D[PPT];
   uint32_t last[PPT];
-  bool done[PPT], valid[PPT];
+  bool valid[PPT];
+  unsigned long long done[PPT];  // lanes whose pixel takes no more entries
 #pragma unroll
   for (int k = 0; k < PPT; k++) {
     int x, y;
@@ -227,16 +296,25 @@ __global__ __launch_bounds__(Shape<TILE>::NT) void k_fwd(Ws ws, float *out_rgb, 
     px[k] = (float)(ox + x);
     py[k] = (float)(oy + y);
     valid[k] = (ox + x) < vw.width && (oy + y) < vw.height;
-    done[k] = !valid[k];
+    done[k] = lanes(!valid[k]);
     T[k] = 1.f; C0[k] = C1[k] = C2[k] = D[k] = 0.f; last[k] = 0;
   }
   const float amin = ws.amin, amax = ws.amax, tmin = ws.tmin, qcut = ws.qcut;
+  const float cx = (float)(ox + TILE / 2), cy = (float)(oy + TILE / 2);
+  bf16x8 pix[PPT][2];
+#pragma unroll
+  for (int k = 0; k < PPT; k++) {
+    pix[k][0] = coverage_pixel<TILE>(k, 0);
+    pix[k][1] = coverage_pixel<TILE>(k, 1);
+    words[NH][w * PPT + k][lane_id()] = 0u;
+  }
+  const bf16x8 *cov_row = &cov[lane_id() >> 5][coverage_entry()];
 
   auto wave_done = [&]() {
-    bool all = true;
+    unsigned long long all = ~0ull;
 #pragma unroll
     for (int k = 0; k < PPT; k++) all &= done[k];
-    return ballot64(!all) == 0ull;
+    return all == ~0ull;
   };
 
   // the next batch's records are gathered into registers while the current
@@ -257,10 +335,7 @@ __global__ __launch_bounds__(Shape<TILE>::NT) void k_fwd(Ws ws, float *out_rgb, 
   }
 
   for (int b = start; b < end; b += BATCH) {
-    bool mine = true;
-#pragma unroll
-    for (int k = 0; k < PPT; k++) mine &= done[k];
-    if (__syncthreads_count(mine) == NT) break;
+    if (__syncthreads_and(wave_done())) break;
     const int nb = min(BATCH, end - b);
 #pragma unroll
     for (int k = 0; k < PER; k++) {
@@ -269,10 +344,11 @@ __global__ __launch_bounds__(Shape<TILE>::NT) void k_fwd(Ws ws, float *out_rgb, 
       // the off-diagonal conic term is staged doubled (exact in FP32)
       if (have) {
         e0s[i] = make_float4(p0[k].x, p0[k].y, p0[k].z, 2.0f * p0[k].w);
-        e1s[i] = p1[k]; e2s[i] = p2[k];
+        *(float2 *)&e1s[i] = make_float2(p1[k].x, p1[k].y);
+        e2s[i] = make_float4(p2[k].x, p2[k].y, p2[k].z, p1[k].z);
       }
-      stage_masks<TILE, NCH>(masks, i, have && pok[k], p0[k], p1[k].x, p1[k].w, qcut, (float)ox,
-                             (float)oy);
+      coverage_row<TILE>(!have || !pok[k], p0[k].x, p0[k].y, p0[k].z, 2.0f * p0[k].w, p1[k].x, qcut,
+                         cx, cy, cov[0][i], cov[1][i]);
     }
     __syncthreads();
     // (past the last batch the clamped loads repeat the list's last entry)
@@ -285,108 +361,113 @@ __global__ __launch_bounds__(Shape<TILE>::NT) void k_fwd(Ws ws, float *out_rgb, 
     const uint32_t base = (uint32_t)(b - start + 1);
     const int nch = (nb + kWave - 1) / kWave;
     for (int g0 = 0; g0 < nch; g0 += G) {
-      uint32_t ns[PPT], seq[PPT];
+      // 1. which of the pass's entries may reach each of this lane's pixels:
+      // a word per 32 entries, kept in LDS for the pass and in memory for the
+      // backward, which replays the same chunks
+      uint32_t nz[PPT];  // bit h: word h is not zero
 #pragma unroll
-      for (int k = 0; k < PPT; k++) ns[k] = seq[k] = 0u;
+      for (int k = 0; k < PPT; k++) nz[k] = 0u;
       const int cend = min(g0 + G, nch);
       for (int c = g0; c < cend; c++) {
-        const unsigned long long m = uniform_u64(masks[w][c]);
-        if (m == 0ull) continue;
-        // 1. which of the chunk's entries reach each of this lane's pixels
-        // bits 0-31 and 32-63 of the chunk in two words; entry j is uniform,
-        // so the half it lands in is a scalar choice
-        uint32_t own_lo[PPT], own_hi[PPT];
-#pragma unroll
-        for (int k = 0; k < PPT; k++) own_lo[k] = own_hi[k] = 0u;
-        for (int h = 0; h < 2; h++) {
-          uint32_t mh = (uint32_t)(m >> (32 * h));
-          while (mh) {  // four entries per step, all loads issued first
-            // past the last set bit: entry 31 of the half, whose bit the
-            // chunk mask clears below unless it is a visited entry anyway
-            int j[4];
-#pragma unroll
-            for (int u = 0; u < 4; u++) {
-              j[u] = __builtin_ctz(mh | 0x80000000u);
-              mh &= mh - 1u;
-            }
-            float4 a[4];
-            float aq[4];
-#pragma unroll
-            for (int u = 0; u < 4; u++) {
-              const int ia = c * kWave + 32 * h + j[u];
-              a[u] = e0s[ia];
-              aq[u] = e1s[ia].x;
-            }
-#pragma unroll
-            for (int k = 0; k < PPT; k++) {
-              uint32_t bits = 0u;
-#pragma unroll
-              for (int u = 0; u < 4; u++)
-                bits |= (uint32_t)(quad2(a[u], aq[u], px[k], py[k]) <= qcut) << j[u];
-              bits = done[k] ? 0u : bits;
-              if (h == 0) own_lo[k] |= bits; else own_hi[k] |= bits;
-            }
-          }
-        }
+        const bf16x8 r0 = cov_row[c * kWave], r1 = cov_row[c * kWave + 32];
+        unsigned long long *dst = ws.lane_bits + chunk_word(start, b - start, c, t, w, NW, PPT);
+        const int h = 2 * (c - g0);
 #pragma unroll
         for (int k = 0; k < PPT; k++) {
-          own_lo[k] &= (uint32_t)m;
-          own_hi[k] &= (uint32_t)(m >> 32);
-        }
-        {
-          // kept for the backward, which replays the same chunks
-          unsigned long long *dst = ws.lane_bits + chunk_word(start, b - start, c, t, w, NW, PPT);
-#pragma unroll
-          for (int k = 0; k < PPT; k++)
-            dst[k * kWave + lane_id()] = ((unsigned long long)own_hi[k] << 32) | own_lo[k];
-        }
-#pragma unroll
-        for (int k = 0; k < PPT; k++) {
-          const uint32_t hh = 2u * (uint32_t)(c - g0);
-          push_word<NS, NR>(words, w * PPT + k, own_lo[k], hh, ns[k], seq[k]);
-          push_word<NS, NR>(words, w * PPT + k, own_hi[k], hh + 1u, ns[k], seq[k]);
+          uint32_t lo = coverage32(r0, pix[k]), hi = coverage32(r1, pix[k]);
+          lo = in_lanes(done[k]) ? 0u : lo;
+          hi = in_lanes(done[k]) ? 0u : hi;
+          words[h][w * PPT + k][lane_id()] = lo;
+          words[h + 1][w * PPT + k][lane_id()] = hi;
+          nz[k] |= (lo ? 1u << h : 0u) | (hi ? 2u << h : 0u);
+          dst[k * kWave + lane_id()] = ((unsigned long long)hi << 32) | lo;
         }
       }
-      // 2. each lane composites its own entries of the group in list order,
+      // 2. each lane composites its own entries of the pass in list order,
       // one step per entry; the wave runs until its last lane is through
 #pragma unroll
       for (int k = 0; k < PPT; k++) {
         const int row = w * PPT + k;
-        words[ns[k]][row][lane_id()] = 0u;
-        uint32_t cur = words[0][row][lane_id()], nxt = words[1][row][lane_id()];
-        uint32_t sq = seq[k], sp = 0u;
         const int gb = g0 * kWave;
-        // the next entry's LDS reads are issued before this one is composited
-        int i = gb + (int)((sq & 15u) << 5) + low_bit(cur);
-        float4 n0 = e0s[i], n1 = e1s[i], n2 = e2s[i];
-        while (cur != 0u) {
-          const float4 e0 = n0, e1 = n1, e2 = n2;
-          const uint32_t pos = base + (uint32_t)i;
+        // the lane's current word (index h) and next one (index hn, the zero
+        // row after its last)
+        auto first = [](uint32_t v) { return __builtin_ctz(v | (1u << NH)); };
+        uint32_t left = nz[k];
+        int h = first(left);
+        left &= left - 1u;
+        int hn = first(left);
+        uint32_t cur = words[h][row][lane_id()], nxt = words[hn][row][lane_id()];
+        int li = -1;  // the pass's last contributor
+        struct Entry {
+          float4 e0, e2;
+          float2 e1;
+          int i;
+        };
+        // the LDS reads of the lane's entry at the front of `cur`
+        auto fetch = [&](Entry &E) {
+          E.i = gb + (h << 5) + low_bit(cur);
+          E.e0 = e0s[E.i];
+          E.e1 = *(const float2 *)&e1s[E.i];
+          E.e2 = e2s[E.i];
+        };
+        // one step of the lanes that have an entry: issue the next entry's
+        // reads into N, composite E; true where the pixel stops
+        auto step = [&](const Entry &E, Entry &N) {
           cur &= cur - 1u;
           const bool z = cur == 0u;
           cur = z ? nxt : cur;
-          sq = z ? sq >> 4 : sq;
-          sp += z ? 1u : 0u;
-          nxt = words[sp + 1u][row][lane_id()];
-          i = gb + (int)((sq & 15u) << 5) + low_bit(cur);
-          n0 = e0s[i]; n1 = e1s[i]; n2 = e2s[i];
-          const float q = quad2(e0, e1.x, px[k], py[k]);
+          h = z ? hn : h;
+          left = z ? left & (left - 1u) : left;
+          hn = first(left);
+          nxt = words[hn][row][lane_id()];
+          fetch(N);
+          const float q = quad2(E.e0, E.e1.x, px[k], py[k]);
           const float gau = __builtin_amdgcn_exp2f(q * kNegHalfLog2e);
-          const float a = fminf(amax, e1.y * gau);
-          const bool ok = a >= amin;
+          const float a = fminf(amax, E.e1.y * gau);
+          const bool ok = q <= qcut && a >= amin;
           const float Tn = T[k] * (1.0f - a);
-          const bool stop = ok && (Tn < tmin);
+          const bool stop = ok && Tn < tmin;
           const bool take = ok && !stop;
-          done[k] = done[k] || stop;
-          cur = stop ? 0u : cur;
           const float wgt = take ? a * T[k] : 0.f;
-          C0[k] = fmaf(e2.x, wgt, C0[k]);
-          C1[k] = fmaf(e2.y, wgt, C1[k]);
-          C2[k] = fmaf(e2.z, wgt, C2[k]);
-          D[k] = fmaf(e1.z, wgt, D[k]);
+          C0[k] = fmaf(E.e2.x, wgt, C0[k]);
+          C1[k] = fmaf(E.e2.y, wgt, C1[k]);
+          C2[k] = fmaf(E.e2.z, wgt, C2[k]);
+          D[k] = fmaf(E.e2.w, wgt, D[k]);
           T[k] = take ? Tn : T[k];
-          last[k] = take ? pos : last[k];
+          li = take ? E.i : li;
+          const bool extra = !(q <= qcut);
+          if (__builtin_expect(lanes(extra) != 0ull, 0)) {
+            // (rare) the bit the backward reads goes: its streams hold the
+            // entries of the exact test only.  The lane's own store of the
+            // word is complete before its atomic.
+            asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+            if (extra) {
+              uint32_t *wd = (uint32_t *)(ws.lane_bits + chunk_word(start, b - start, E.i >> 6, t, w, NW, PPT) +
+                                          k * kWave + lane_id()) + ((E.i >> 5) & 1);
+              atomicAnd(wd, ~(1u << (E.i & 31)));
+            }
+          }
+          return stop;
+        };
+        Entry A, B;
+        fetch(A);
+        // the lanes with an entry left (a scalar mask: the loop itself is
+        // uniform, and the steps alternate between two register sets, so
+        // that no entry is moved from one to the other)
+        auto more = [&]() { return lanes(cur != 0u) & ~done[k]; };
+        while (true) {
+          unsigned long long live = more();
+          if (live == 0ull) break;
+          bool stop = false;
+          if (in_lanes(live)) stop = step(A, B);
+          done[k] |= lanes(stop);
+          live = more();
+          if (live == 0ull) break;
+          stop = false;
+          if (in_lanes(live)) stop = step(B, A);
+          done[k] |= lanes(stop);
         }
+        last[k] = li >= 0 ? base + (uint32_t)li : last[k];
       }
       if (wave_done()) break;
     }
@@ -458,7 +539,6 @@ __global__ __launch_bounds__(Shape<TILE>::NT, (MODE & 2) ? ((MODE & 4) ? 2 : 3) 
   constexpr int NT = Shape<TILE>::NT, PPT = Shape<TILE>::PPT;
   constexpr int NW = NT / kWave;
   constexpr int PER = (BATCH + NT - 1) / NT;
-  constexpr int NCH = PER * NT / kWave;
   constexpr bool kTwist = (MODE & 1) != 0, kSlots = (MODE & 2) != 0;
   constexpr bool kGeo = kSlots && (MODE & 4) != 0;  // slots also carry dL/dp
   constexpr int NA = kGeo ? 8 : 5;                   // floats per slot
@@ -476,7 +556,6 @@ __global__ __launch_bounds__(Shape<TILE>::NT, (MODE & 2) ? ((MODE & 4) ? 2 : 3) 
   __shared__ uint8_t tag_s[kSlots ? NW : 1][AB + kWave];  // + a tag per lane
   __shared__ int maxlast_s;
   __shared__ float red_s[NW][7];
-  __shared__ unsigned long long masks[NW][NCH];
   __shared__ uint32_t words[NS][NR][kWave];
 
   const int t = tile_of_block(ws);
@@ -548,7 +627,7 @@ __global__ __launch_bounds__(Shape<TILE>::NT, (MODE & 2) ? ((MODE & 4) ? 2 : 3) 
   const int wstop = start + __builtin_amdgcn_readfirstlane(wave_max_i((int)mylast));
 
   float tw[6] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-  const float amin = ws.amin, amax = ws.amax, qcut = ws.qcut;
+  const float amin = ws.amin, amax = ws.amax;
   const float vfx = vw.fx, vfy = vw.fy;
 
   // batches walk the list from the block's last contributor towards the front
@@ -581,8 +660,6 @@ __global__ __launch_bounds__(Shape<TILE>::NT, (MODE & 2) ? ((MODE & 4) ? 2 : 3) 
 #pragma unroll
     for (int k = 0; k < PER; k++) {
       const int i = threadIdx.x + k * NT;
-      stage_masks<TILE, NCH>(masks, i, i < nb && st[k].ok, st[k].e0, st[k].e1.x, st[k].e1.w, qcut,
-                             (float)ox, (float)oy);
       if (i >= nb) continue;
       const BwdEntry &E = st[k];
       // the doubled off-diagonal conic term (exact) for q, the plain one
@@ -636,17 +713,13 @@ __global__ __launch_bounds__(Shape<TILE>::NT, (MODE & 2) ? ((MODE & 4) ? 2 : 3) 
       for (int cc = G - 1; cc >= 0; cc--) {
         const int c = g0 + cc;
         if (c > ctop) continue;
-        unsigned long long m = uniform_u64(masks[w][c]);
-        const int top = lim - c * kWave;  // entries [c*64, c*64 + top) are below the limit
-        if (top < kWave) m &= (1ull << top) - 1ull;
-        if (m == 0ull) continue;
         const int base = lo - start + c * kWave;
 #pragma unroll
         for (int k = 0; k < PPT; k++) {
           const int lim_k = (int)last[k] - base;
           const unsigned long long below =
               lim_k >= kWave ? ~0ull : (lim_k <= 0 ? 0ull : (1ull << lim_k) - 1ull);
-          const unsigned long long own = lb[cc][k] & below & m;
+          const unsigned long long own = lb[cc][k] & below;
           const uint32_t hh = 2u * (uint32_t)(c - g0);
           push_word<NS, NR>(words, w * PPT + k, __builtin_bitreverse32((uint32_t)(own >> 32)),
                             hh + 1u, ns[k], seq[k]);
@@ -860,6 +933,15 @@ __global__ __launch_bounds__(Shape<TILE>::NT, (MODE & 2) ? ((MODE & 4) ? 2 : 3) 
   }
 }
 
+// Grids of at most this many 16-pixel tiles (two blocks per CU) take the
+// forward in 512-entry batches and passes when the plan's batch is the default
+// 256: with a block or two per CU the LDS is free, and a pass twice as long
+// takes fewer steps (a lane waits less for its wave's busiest) and half the
+// barriers. Measured: 12 tiles 30 -> 22 us, 80 tiles 35 -> 23, 300 tiles
+// (lists of ~600) 42 -> 27. Above, its two blocks per CU cost more than it
+// saves: 1,200 tiles 43.7 -> 50.4 us, 6,000 tiles 848 -> 1238.
+constexpr int kFwdSmallGrid = 512;
+
 template <int TILE, int BATCH>
 hipError_t fwd_launch(const Ws &ws, float *rgb, float *depth, float *sil, hipStream_t st) {
   hipLaunchKernelGGL((k_fwd<TILE, BATCH>), dim3(ws.n_tiles), dim3(Shape<TILE>::NT), 0, st, ws,
@@ -884,6 +966,8 @@ hipError_t bwd_launch(const Ws &ws, const float *g_rgb, const float *g_depth, co
 
 template <int TILE>
 hipError_t fwd_tile(const Ws &ws, float *rgb, float *depth, float *sil, hipStream_t st) {
+  if (TILE == 16 && ws.batch == 256 && ws.n_tiles <= kFwdSmallGrid)
+    return fwd_launch<TILE, 512>(ws, rgb, depth, sil, st);
   switch (ws.batch) {
     case 128: return fwd_launch<TILE, 128>(ws, rgb, depth, sil, st);
     case 256: return fwd_launch<TILE, 256>(ws, rgb, depth, sil, st);
