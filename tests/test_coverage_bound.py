@@ -57,7 +57,7 @@ def test_no_accepted_pixel_is_missed(tile, kind):
     slack = S * (M * M * F(2 ** -18) + h * h * F(2 ** -16)) + F(1e-5) * Q_CUT
     Fc = F(-0.5) * (D * ux + E * uy) - (Q_CUT + slack)
     rows = [pieces(A, 2), pieces(B, 2), pieces(C, 2), pieces(D, 3), pieces(E, 3), pieces(Fc, 3)]
-    missed = extra = accepted = 0
+    missed = accepted = 0
     for X in range(-tile // 2, tile // 2):
         for Y in range(-tile // 2, tile // 2):
             p = np.zeros(n, F)
@@ -70,7 +70,7 @@ def test_no_accepted_pixel_is_missed(tile, kind):
             q = fma(qc * dy, dy, fma(B * dx, dy, (qa * dx) * dx))
             acc, bit = q <= Q_CUT, np.signbit(p)
             missed += int((acc & ~bit).sum())
-            extra += int((bit & ~acc).sum())
+            assert np.all(q[bit] <= Q_CUT + F(2) * slack[bit])
             accepted += int(acc.sum())
     assert missed == 0
-    assert accepted > 0 and extra <= 0.005 * accepted, (extra, accepted)
+    assert accepted > 0
