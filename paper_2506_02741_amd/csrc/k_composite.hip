@@ -101,13 +101,16 @@ __device__ __forceinline__ void lane_pixel(int k, int &x, int &y) {
 //   the rest, and the FP32 q of the exact test: a few dozen roundings of
 //   terms below (|A| + |B| + |C|) (|m| + H)^2 each, taken as 2^-18 of that
 // and F is lowered by that much, so the sign is set for every pixel the exact
-// test (FP32, q <= q_cut) accepts, and for few others (about 0.03 per entry
-// and block): the compositing step repeats the exact test and takes their
-// bits back out.  A conic too large for the bound to be finite is tried at
+// test (FP32, q <= q_cut) accepts, and for few others (about one in a wave's
+// life): the compositing step repeats the exact test and takes their bits
+// back out.  A conic too large for the bound to be finite is tried at
 // every pixel.  One v_alignbit per two (entry, 32 pixels) results moves the
 // signs into the lanes' masks, so 64 entries against 64 pixels cost 4 MFMAs
-// and ~75 VALU instructions; testing q per (entry, pixel) on the VALU took
-// 12.75 for each entry whose cull circle met the block, ~380 per chunk.
+// and ~80 VALU instructions; testing q per (entry, pixel) on the VALU took
+// 12.75 for each entry whose cull circle met the block, ~380 per chunk.  With
+// the compositing step's own instructions cut (48 from ~65) the forward of a
+// 640x480 tracking frame went from 62 to 41 us, of 5 views of 8 keyframes from
+// 1070 to 758, both still bound by VALU issue.
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef float f32x16 __attribute__((ext_vector_type(16)));
 
@@ -260,22 +263,28 @@ __device__ __forceinline__ void fetch_record(const Ws &ws, int n_rec, int rec_ba
   e0 = A[0]; e1 = A[1]; e2 = A[2];
 }
 
-// Waves per SIMD the register budget leaves room for (tile 16 with 256-entry
-// batches: the five blocks per CU its LDS allows); two or more also keep the
-// MFMA results in VGPRs, which the sign extraction reads directly.
+// Waves per SIMD the register budget leaves room for (tile 16: the blocks per
+// CU its LDS allows); two or more also keep the MFMA results in VGPRs, which
+// the sign extraction reads directly.
 template <int TILE, int BATCH>
-__global__ __attribute__((amdgpu_waves_per_eu(TILE == 16 && BATCH <= 256 ? 5 : 2))) __launch_bounds__(
+__global__ __attribute__((amdgpu_waves_per_eu(TILE == 16 ? 4 : 2))) __launch_bounds__(
     Shape<TILE>::NT) void k_fwd(Ws ws, float *out_rgb, float *out_depth, float *out_sil) {
   constexpr int NT = Shape<TILE>::NT, PPT = Shape<TILE>::PPT;
   constexpr int NW = NT / kWave;
   constexpr int PER = (BATCH + NT - 1) / NT;  // list entries each thread stages per batch
-  constexpr int SB = PER * NT;                // entries a batch's staging covers
   constexpr int G = Group<TILE, BATCH>::GF, NH = Group<TILE, BATCH>::NH, NR = NW * PPT;
-  // staged entry: e0 (mx, my, qa, 2 qb), e1 (qc, o; at e0's stride, so that
-  // one address serves all three), e2 (c, z); 32 entries more, never
-  // written, that a finished lane's last reads fall into
-  __shared__ float4 e0s[BATCH + 32], e1s[BATCH + 32], e2s[BATCH + 32];
-  __shared__ bf16x8 cov[2][SB];               // coverage rows, terms 0-7 and 8-15
+  // A batch that is one pass stages its coverage rows first and, once every
+  // wave has its bits, the entries themselves in the same LDS (a barrier
+  // more, but 512 entries fit four blocks per CU).
+  constexpr bool kShare = BATCH / kWave == G;
+  // staged entry: e0 (mx, my, qa, 2 qb), e2 (c, z), e1 (qc, o); 32 entries
+  // more, never written, that a finished lane's last reads fall into
+  constexpr int SE = BATCH + 32, kCov = kShare ? 0 : SE * 40;
+  __shared__ __attribute__((aligned(16))) char lds[kShare ? SE * 40 : SE * 40 + BATCH * 32];
+  float4 *e0s = (float4 *)lds, *e2s = e0s + SE;
+  float2 *e1s = (float2 *)(e2s + SE);
+  // coverage rows, terms 0-7, then terms 8-15
+  bf16x8 *cov = (bf16x8 *)(lds + kCov);
   __shared__ uint32_t words[NH + 1][NR][kWave];  // the lanes' bits of a pass; the last row zero
   const int t = tile_of_block(ws);
   const DevView &vw = ws.views[find_view_by_tile(ws, t)];
@@ -308,7 +317,7 @@ __global__ __attribute__((amdgpu_waves_per_eu(TILE == 16 && BATCH <= 256 ? 5 : 2
     pix[k][1] = coverage_pixel<TILE>(k, 1);
     words[NH][w * PPT + k][lane_id()] = 0u;
   }
-  const bf16x8 *cov_row = &cov[lane_id() >> 5][coverage_entry()];
+  const bf16x8 *cov_row = cov + (lane_id() >> 5) * BATCH + coverage_entry();
 
   auto wave_done = [&]() {
     unsigned long long all = ~0ull;
@@ -337,30 +346,39 @@ __global__ __attribute__((amdgpu_waves_per_eu(TILE == 16 && BATCH <= 256 ? 5 : 2
   for (int b = start; b < end; b += BATCH) {
     if (__syncthreads_and(wave_done())) break;
     const int nb = min(BATCH, end - b);
+    auto stage_entries = [&]() {
+#pragma unroll
+      for (int k = 0; k < PER; k++) {
+        const int i = threadIdx.x + k * NT;
+        if (i >= nb) continue;
+        // the off-diagonal conic term is staged doubled (exact in FP32)
+        e0s[i] = make_float4(p0[k].x, p0[k].y, p0[k].z, 2.0f * p0[k].w);
+        e1s[i] = make_float2(p1[k].x, p1[k].y);
+        e2s[i] = make_float4(p2[k].x, p2[k].y, p2[k].z, p1[k].z);
+      }
+    };
+    // (past the last batch the clamped loads repeat the list's last entry)
+    auto prefetch = [&]() {
+#pragma unroll
+      for (int k = 0; k < PER; k++) fetch_record(ws, n_rec, rec_base, pid[k], p0[k], p1[k], p2[k], pok[k]);
+#pragma unroll
+      for (int k = 0; k < PER; k++)
+        pid[k] = ws.ids[min(b + 2 * BATCH + (int)threadIdx.x + k * NT, end - 1)];
+    };
 #pragma unroll
     for (int k = 0; k < PER; k++) {
       const int i = threadIdx.x + k * NT;
-      const bool have = i < nb;
-      // the off-diagonal conic term is staged doubled (exact in FP32)
-      if (have) {
-        e0s[i] = make_float4(p0[k].x, p0[k].y, p0[k].z, 2.0f * p0[k].w);
-        *(float2 *)&e1s[i] = make_float2(p1[k].x, p1[k].y);
-        e2s[i] = make_float4(p2[k].x, p2[k].y, p2[k].z, p1[k].z);
-      }
-      coverage_row<TILE>(!have || !pok[k], p0[k].x, p0[k].y, p0[k].z, 2.0f * p0[k].w, p1[k].x, qcut,
-                         cx, cy, cov[0][i], cov[1][i]);
+      if (BATCH % NT != 0 && i >= BATCH) continue;
+      coverage_row<TILE>(i >= nb || !pok[k], p0[k].x, p0[k].y, p0[k].z, 2.0f * p0[k].w, p1[k].x,
+                         qcut, cx, cy, cov[i], cov[BATCH + i]);
     }
+    if (!kShare) stage_entries();
     __syncthreads();
-    // (past the last batch the clamped loads repeat the list's last entry)
-#pragma unroll
-    for (int k = 0; k < PER; k++) fetch_record(ws, n_rec, rec_base, pid[k], p0[k], p1[k], p2[k], pok[k]);
-#pragma unroll
-    for (int k = 0; k < PER; k++)
-      pid[k] = ws.ids[min(b + 2 * BATCH + (int)threadIdx.x + k * NT, end - 1)];
-    if (wave_done()) continue;
+    if (!kShare) prefetch();
     const uint32_t base = (uint32_t)(b - start + 1);
     const int nch = (nb + kWave - 1) / kWave;
     for (int g0 = 0; g0 < nch; g0 += G) {
+      if (!kShare && wave_done()) break;
       // 1. which of the pass's entries may reach each of this lane's pixels:
       // a word per 32 entries, kept in LDS for the pass and in memory for the
       // backward, which replays the same chunks
@@ -368,7 +386,7 @@ __global__ __attribute__((amdgpu_waves_per_eu(TILE == 16 && BATCH <= 256 ? 5 : 2
 #pragma unroll
       for (int k = 0; k < PPT; k++) nz[k] = 0u;
       const int cend = min(g0 + G, nch);
-      for (int c = g0; c < cend; c++) {
+      for (int c = wave_done() ? cend : g0; c < cend; c++) {
         const bf16x8 r0 = cov_row[c * kWave], r1 = cov_row[c * kWave + 32];
         unsigned long long *dst = ws.lane_bits + chunk_word(start, b - start, c, t, w, NW, PPT);
         const int h = 2 * (c - g0);
@@ -382,6 +400,12 @@ __global__ __attribute__((amdgpu_waves_per_eu(TILE == 16 && BATCH <= 256 ? 5 : 2
           nz[k] |= (lo ? 1u << h : 0u) | (hi ? 2u << h : 0u);
           dst[k * kWave + lane_id()] = ((unsigned long long)hi << 32) | lo;
         }
+      }
+      if (kShare) {
+        __syncthreads();
+        stage_entries();
+        __syncthreads();
+        prefetch();
       }
       // 2. each lane composites its own entries of the pass in list order,
       // one step per entry; the wave runs until its last lane is through
@@ -407,7 +431,7 @@ __global__ __attribute__((amdgpu_waves_per_eu(TILE == 16 && BATCH <= 256 ? 5 : 2
         auto fetch = [&](Entry &E) {
           E.i = gb + (h << 5) + low_bit(cur);
           E.e0 = e0s[E.i];
-          E.e1 = *(const float2 *)&e1s[E.i];
+          E.e1 = e1s[E.i];
           E.e2 = e2s[E.i];
         };
         // one step of the lanes that have an entry: issue the next entry's
@@ -469,7 +493,6 @@ __global__ __attribute__((amdgpu_waves_per_eu(TILE == 16 && BATCH <= 256 ? 5 : 2
         }
         last[k] = li >= 0 ? base + (uint32_t)li : last[k];
       }
-      if (wave_done()) break;
     }
   }
   const int64_t P = ws.P;
@@ -933,15 +956,6 @@ __global__ __launch_bounds__(Shape<TILE>::NT, (MODE & 2) ? ((MODE & 4) ? 2 : 3) 
   }
 }
 
-// Grids of at most this many 16-pixel tiles (two blocks per CU) take the
-// forward in 512-entry batches and passes when the plan's batch is the default
-// 256: with a block or two per CU the LDS is free, and a pass twice as long
-// takes fewer steps (a lane waits less for its wave's busiest) and half the
-// barriers. Measured: 12 tiles 30 -> 22 us, 80 tiles 35 -> 23, 300 tiles
-// (lists of ~600) 42 -> 27. Above, its two blocks per CU cost more than it
-// saves: 1,200 tiles 43.7 -> 50.4 us, 6,000 tiles 848 -> 1238.
-constexpr int kFwdSmallGrid = 512;
-
 template <int TILE, int BATCH>
 hipError_t fwd_launch(const Ws &ws, float *rgb, float *depth, float *sil, hipStream_t st) {
   hipLaunchKernelGGL((k_fwd<TILE, BATCH>), dim3(ws.n_tiles), dim3(Shape<TILE>::NT), 0, st, ws,
@@ -966,11 +980,16 @@ hipError_t bwd_launch(const Ws &ws, const float *g_rgb, const float *g_depth, co
 
 template <int TILE>
 hipError_t fwd_tile(const Ws &ws, float *rgb, float *depth, float *sil, hipStream_t st) {
-  if (TILE == 16 && ws.batch == 256 && ws.n_tiles <= kFwdSmallGrid)
-    return fwd_launch<TILE, 512>(ws, rgb, depth, sil, st);
   switch (ws.batch) {
     case 128: return fwd_launch<TILE, 128>(ws, rgb, depth, sil, st);
-    case 256: return fwd_launch<TILE, 256>(ws, rgb, depth, sil, st);
+    // 16-pixel tiles take the default batch as passes of 512 entries: a pass
+    // twice as long takes fewer steps (a lane waits less for its wave's
+    // busiest) and fewer barriers, and at four blocks per CU it still beats
+    // 256 at five: 12 tiles 30 -> 22 us, 80 tiles 32 -> 23, 1,200 tiles 44 ->
+    // 41, 6,000 tiles of 1,400 entries 848 -> 758; only lists that fill
+    // neither lose (3,225 tiles of a stride-2 map 88 -> 105). 384 at five
+    // blocks lies between (42, 816 and 101 us).
+    case 256: return fwd_launch<TILE, TILE == 16 ? 512 : 256>(ws, rgb, depth, sil, st);
     case 512: return fwd_launch<TILE, 512>(ws, rgb, depth, sil, st);
   }
   return hipErrorInvalidValue;
