@@ -51,7 +51,12 @@ __device__ __forceinline__ void unpack_rect(uint2 rc, int &x0, int &y0, int &x1,
   x0 = rc.x & 0xffff; y0 = rc.x >> 16; x1 = rc.y & 0xffff; y1 = rc.y >> 16;
 }
 
-constexpr int kBoxMax = 24;  // tiles of a shared box
+// Tiles of a shared box: one per lane.  64 stride-1 records span 5-6 tiles of
+// 16 in two or three rows, stride-2 records 9-10 in two or three, so a limit
+// of 24 had left most waves of a stride-2 map to per-pair atomics: serving
+// track batches 570 -> 273 us (preprocess) and 576 -> 104 us (fill), 5 views
+// over 8 stride-1 keyframes 440 -> 412 and 243 -> 113.
+constexpr int kBoxMax = 64;
 
 // Tiles covered by a wave's rectangles (a group of 64 consecutive records).
 // When the whole wave belongs to one view and its rectangles fit in a
@@ -112,6 +117,44 @@ __device__ __forceinline__ uint32_t box_counts(const WaveBox &b, bool has, int x
   lds_order();
   return mine;
 }
+
+// Rectangles of a group without a shared box: a lane walks a small one by
+// itself; one of more than kLaneTiles tiles (a Gaussian close to the view's
+// camera plane covers thousands) is walked by the whole wave, 64 tiles at a
+// time, one such lane after the other.  A lane alone issues an atomic per
+// tile, in the fill each with the wait for its old value, while 63 lanes
+// idle: with 2,400 such records among the 2 M of a section of 10 stride-2
+// keyframes, most of them over all 3,225 tiles of a 1200x680 view, the
+// preprocess took 1.89 ms and the fill 4.60 ms, now 0.19 and 0.32 (what is
+// left is the 7.8 M atomics themselves).  The line lies where a wave of 64
+// such rectangles, walked one after the other, would take as long as its
+// lanes side by side.
+constexpr int kLaneTiles = 64;
+
+// One rectangle of the wave walked by all lanes, lane j taking tiles j, j +
+// 64, .. in row-major order, U of them per call f(tile[U], n) with the view's
+// tile indexes (the first n are the lane's), so that f can keep U round trips
+// in flight.
+template <int U, typename F>
+__device__ __forceinline__ void wave_tiles(int x0, int y0, int x1, int y1, int tiles_x, int t0, F f) {
+  const int nx = x1 - x0 + 1, ny = y1 - y0 + 1;
+  const int dq = kWave / nx, dr = kWave - dq * nx;
+  int q = lane_id() / nx, r = lane_id() - q * nx;
+  while (q < ny) {
+    int tile[U], n = 0;
+#pragma unroll
+    for (int u = 0; u < U; u++) {
+      tile[u] = t0 + (y0 + q) * tiles_x + (x0 + r);
+      n += q < ny ? 1 : 0;
+      q += dq;
+      r += dr;
+      if (r >= nx) { r -= nx; q++; }
+    }
+    f(tile, n);
+  }
+}
+
+__device__ __forceinline__ int lane_value(int v, int src) { return __builtin_amdgcn_readlane(v, src); }
 
 // A load through a descriptor's pointer, which addresses global memory:
 // read as such (the compiler cannot tell, and would issue a flat load).
@@ -245,12 +288,21 @@ __global__ __launch_bounds__(kNT) void k_preprocess(Ws ws) {
     // the atomic's old value is the group's first position in box tile j:
     // kept for the key fill, which then claims nothing for this group
     if (mine) ws.wave_off[(r & ~(kWave - 1)) + lane_id()] = atomicAdd(ws.tile_count + mt, mine);
-  } else if (has) {
+  } else {
     // the other groups' pairs take the positions after them, claimed by
     // the key fill
-    uint32_t *cnt = ws.tile_count_ns + tile_base;
-    for (int ty = y0; ty <= y1; ty++)
-      for (int tx = x0; tx <= x1; tx++) atomicAdd(cnt + ty * tiles_x + tx, 1u);
+    const bool wide = has && (x1 - x0 + 1) * (y1 - y0 + 1) > kLaneTiles;
+    if (has && !wide) {
+      uint32_t *cnt = ws.tile_count_ns + tile_base;
+      for (int ty = y0; ty <= y1; ty++)
+        for (int tx = x0; tx <= x1; tx++) atomicAdd(cnt + ty * tiles_x + tx, 1u);
+    }
+    for (unsigned long long m = ballot64(wide); m; m &= m - 1ull) {
+      const int src = (int)__builtin_ctzll(m);
+      wave_tiles<1>(lane_value(x0, src), lane_value(y0, src), lane_value(x1, src),
+                    lane_value(y1, src), lane_value(tiles_x, src), lane_value(tile_base, src),
+                    [&](const int (&t)[1], int) { atomicAdd(ws.tile_count_ns + t[0], 1u); });
+    }
   }
 }
 
@@ -441,13 +493,38 @@ __global__ __launch_bounds__(kNT) void k_fill_keys(Ws ws) {
           }
       }
       lds_order();
-    } else if (has[k]) {
-      for (int ty = y0[k]; ty <= y1[k]; ty++)
-        for (int tx = x0[k]; tx <= x1[k]; tx++) {
-          const int t = tile_base[k] + ty * tiles_x[k] + tx;
-          const uint32_t pos = ws.ranges[t].x + atomicAdd(ws.tile_fill + t, 1u);
-          if (pos < ws.ranges[t].y) ws.keys[pos] = key[k];
-        }
+    } else {
+      auto put = [&](int t, unsigned long long kv) {
+        const uint2 rg = ws.ranges[t];
+        const uint32_t pos = rg.x + atomicAdd(ws.tile_fill + t, 1u);
+        if (pos < rg.y) ws.keys[pos] = kv;
+      };
+      const bool wide = has[k] && (x1[k] - x0[k] + 1) * (y1[k] - y0[k] + 1) > kLaneTiles;
+      if (has[k] && !wide) {
+        for (int ty = y0[k]; ty <= y1[k]; ty++)
+          for (int tx = x0[k]; tx <= x1[k]; tx++) put(tile_base[k] + ty * tiles_x[k] + tx, key[k]);
+      }
+      for (unsigned long long m = ballot64(wide); m; m &= m - 1ull) {
+        const int src = (int)__builtin_ctzll(m);
+        const unsigned long long kv =
+            ((unsigned long long)(uint32_t)lane_value((int)(uint32_t)(key[k] >> 32), src) << 32) |
+            (uint32_t)lane_value((int)(uint32_t)key[k], src);
+        wave_tiles<4>(lane_value(x0[k], src), lane_value(y0[k], src), lane_value(x1[k], src),
+                      lane_value(y1[k], src), lane_value(tiles_x[k], src), lane_value(tile_base[k], src),
+                      [&](const int (&t)[4], int n) {
+                        uint2 rg[4];
+                        uint32_t at[4];
+#pragma unroll
+                        for (int u = 0; u < 4; u++)
+                          if (u < n) {
+                            rg[u] = ws.ranges[t[u]];
+                            at[u] = atomicAdd(ws.tile_fill + t[u], 1u);
+                          }
+#pragma unroll
+                        for (int u = 0; u < 4; u++)
+                          if (u < n && rg[u].x + at[u] < rg[u].y) ws.keys[rg[u].x + at[u]] = kv;
+                      });
+      }
     }
   }
 }
