@@ -227,7 +227,6 @@ void make_ws(vtgs_plan *p) {
   w.n_pairs = reinterpret_cast<unsigned long long *>(b + p->r_hdr.off + 8);
   w.iter = reinterpret_cast<uint32_t *>(b + p->r_hdr.off + 16);
   w.n_long = reinterpret_cast<uint32_t *>(b + p->r_hdr.off + 24);
-  w.long_next = reinterpret_cast<uint32_t *>(b + p->r_hdr.off + 28);
   w.long_tiles = at<uint32_t>(b, p->r_long);
   w.tile_order = p->tile_order ? at<uint32_t>(b, p->r_order) : nullptr;
   char *d = b + p->r_desc.off;

@@ -306,12 +306,14 @@ __global__ __launch_bounds__(kNT) void k_preprocess(Ws ws) {
   }
 }
 
-constexpr int kSmallSort = 768;  // longer tile lists go to the long-list sort
+// Longest lists of the tile sorts (keys in LDS): a 256-thread block takes up
+// to kSmallSort, a 512-thread one up to kMidSort, a 1024-thread one the rest.
+constexpr int kSmallSort = 1024, kMidSort = 4096;
 
 // One block: tile counts -> ranges (clamped to the pair capacity), total
 // pairs, capacity flag; lists longer than kSmallSort are queued for the
-// long-list sort (queue and its cursor reset here); clears the counters for
-// the next pass.
+// long-list sorts, those over kMidSort from the queue array's end; clears the
+// counters for the next pass.
 constexpr int kScanNT = 1024, kScanPer = 8;
 constexpr int kOrderBuckets = 64;
 // Bucket of a list of n entries in the longest-first order: 0 for the
@@ -325,8 +327,8 @@ __device__ __forceinline__ int order_bucket(uint32_t n) {
 __global__ __launch_bounds__(kScanNT) void k_scan_tiles(Ws ws) {
   __shared__ uint32_t lw[kScanNT / kWave];
   __shared__ unsigned long long carry_s;
-  __shared__ uint32_t nlong_s;
-  if (threadIdx.x == 0) { carry_s = 0; nlong_s = 0; }
+  __shared__ uint32_t nlong_s, nhuge_s;
+  if (threadIdx.x == 0) { carry_s = 0; nlong_s = 0; nhuge_s = 0; }
   __syncthreads();
   for (int base = 0; base < ws.n_tiles; base += kScanNT * kScanPer) {
     const int i0 = base + threadIdx.x * kScanPer;
@@ -346,7 +348,10 @@ __global__ __launch_bounds__(kScanNT) void k_scan_tiles(Ws ws) {
         const unsigned long long s = pos < (unsigned long long)ws.cap ? pos : ws.cap;
         const unsigned long long e = pos + v[k] < (unsigned long long)ws.cap ? pos + v[k] : ws.cap;
         ws.ranges[i] = make_uint2((uint32_t)s, (uint32_t)e);
-        if (e - s > (unsigned long long)kSmallSort) ws.long_tiles[atomicAdd(&nlong_s, 1u)] = i;
+        if (e - s > (unsigned long long)kMidSort)
+          ws.long_tiles[(uint32_t)ws.n_tiles - 1u - atomicAdd(&nhuge_s, 1u)] = i;
+        else if (e - s > (unsigned long long)kSmallSort)
+          ws.long_tiles[atomicAdd(&nlong_s, 1u)] = i;
         ws.tile_count[i] = 0;
         ws.tile_count_ns[i] = 0;
         ws.tile_fill[i] = vs[k];
@@ -360,8 +365,8 @@ __global__ __launch_bounds__(kScanNT) void k_scan_tiles(Ws ws) {
   if (threadIdx.x == 0) {
     *ws.n_pairs = carry_s;
     if (carry_s > (unsigned long long)ws.cap) atomicOr(ws.flags, kFlagCapacity);
-    *ws.n_long = nlong_s;
-    *ws.long_next = 0u;
+    ws.n_long[0] = nlong_s;
+    ws.n_long[1] = nhuge_s;
   }
   if (ws.tile_order) {
     // longest lists first: tiles bucketed by list length (two buckets per
@@ -544,370 +549,6 @@ __device__ __forceinline__ uint32_t wave_incl_scan_u32(uint32_t x) {
   return x;
 }
 
-// 8-bit field d (0..15) of the pair (lo: fields 0-7, hi: fields 8-15).
-__device__ __forceinline__ uint32_t field8(unsigned long long lo, unsigned long long hi, int d) {
-  const unsigned long long v = d < 8 ? lo : hi;
-  return (uint32_t)(v >> (8 * (d & 7))) & 0xffu;
-}
-
-// LDS slot of list position i: one spare slot after every 16, so that the
-// lanes reading positions t*E .. t*E+E-1 spread over the banks.
-__device__ __forceinline__ int lds_pos(int i) { return i + (i >> 4); }
-
-// Wave OR / AND of a uint32 (all 64 lanes active), uniform result.
-__device__ __forceinline__ uint32_t wave_or_u32(uint32_t x) {
-  x |= (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x128, 0xf, 0xf, false);
-  x |= (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x124, 0xf, 0xf, false);
-  x |= (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x122, 0xf, 0xf, false);
-  x |= (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x121, 0xf, 0xf, false);
-  return ((uint32_t)__builtin_amdgcn_readlane((int)x, 0) | (uint32_t)__builtin_amdgcn_readlane((int)x, 16)) |
-         ((uint32_t)__builtin_amdgcn_readlane((int)x, 32) | (uint32_t)__builtin_amdgcn_readlane((int)x, 48));
-}
-__device__ __forceinline__ uint32_t wave_and_u32(uint32_t x) {
-  x &= (uint32_t)__builtin_amdgcn_update_dpp(-1, (int)x, 0x128, 0xf, 0xf, false);
-  x &= (uint32_t)__builtin_amdgcn_update_dpp(-1, (int)x, 0x124, 0xf, 0xf, false);
-  x &= (uint32_t)__builtin_amdgcn_update_dpp(-1, (int)x, 0x122, 0xf, 0xf, false);
-  x &= (uint32_t)__builtin_amdgcn_update_dpp(-1, (int)x, 0x121, 0xf, 0xf, false);
-  return ((uint32_t)__builtin_amdgcn_readlane((int)x, 0) & (uint32_t)__builtin_amdgcn_readlane((int)x, 16)) &
-         ((uint32_t)__builtin_amdgcn_readlane((int)x, 32) & (uint32_t)__builtin_amdgcn_readlane((int)x, 48));
-}
-
-// Padding keys (~0) must end after every real key, but the depth passes
-// take only the depth nibbles in which the real keys differ: a real key
-// whose varying depth nibbles are all 15 (or any key, when the depth does
-// not vary) would tie with the padding on every depth pass and could keep
-// a place before it.  For such a list the top nibble is sorted as well; it
-// is below 8 in every real key (a finite positive depth), so it puts the
-// padding last.
-__device__ __forceinline__ unsigned long long nibbles_of(unsigned long long diff) {
-  unsigned long long nib = 0ull;
-#pragma unroll
-  for (int sh = 0; sh < 64; sh += 4) nib |= ((diff >> sh) & 15ull) != 0ull ? 15ull << sh : 0ull;
-  return nib;
-}
-constexpr unsigned long long kTopNibble = 15ull << 60;
-
-// Stable LSD radix passes, 4-bit digits, over the nibbles set in `digits`,
-// of the NT * E keys of a block.  Thread t holds keys t*E .. t*E+E-1 in
-// registers ("blocked" order).  Per pass each thread counts its keys per
-// digit (4-bit fields of one u64 for E <= 15, else 8-bit fields of two), a
-// DPP wave scan of the counts (as 16-bit fields) and the wave totals in LDS
-// give each thread its start in every digit bucket (with E <= 15 parked in
-// `starts` so that each key fetches its own), and the keys are scattered
-// through `buf` (at lds_pos) in thread-then-register order, which keeps each
-// pass stable.  On return buf and the registers hold the keys in the new
-// order.
-template <int NT, int E>
-__device__ void radix_passes(unsigned long long (&k)[E], unsigned long long digits,
-                             unsigned long long *buf, uint32_t (*wsum)[8], uint32_t *starts) {
-  constexpr int NW = NT / kWave;
-  constexpr bool k4 = E <= 15;
-  const int t = threadIdx.x, l = lane_id(), w = t / kWave;
-  for (int sh = 0; sh < 64; sh += 4) {
-    if (((digits >> sh) & 15ull) == 0ull) continue;
-    int dg[E];
-    unsigned long long clo = 0ull, chi = 0ull;
-#pragma unroll
-    for (int e = 0; e < E; e++) {
-      const int d = (int)((k[e] >> sh) & 15ull);
-      dg[e] = d;
-      if (k4) {
-        clo += 1ull << (4 * d);
-      } else {
-        const unsigned long long one = 1ull << (8 * (d & 7));
-        clo += d < 8 ? one : 0ull;
-        chi += d < 8 ? 0ull : one;
-      }
-    }
-    // counts as 16-bit fields: c[q] holds digits 2q and 2q + 1
-    uint32_t c[8], inc[8];
-#pragma unroll
-    for (int q = 0; q < 8; q++) {
-      if (k4) {
-        const uint32_t v = q < 4 ? (uint32_t)clo : (uint32_t)(clo >> 32);
-        const int o = 8 * (q & 3);
-        c[q] = ((v >> o) & 15u) | (((v >> (o + 4)) & 15u) << 16);
-      } else {
-        c[q] = field8(clo, chi, 2 * q) | (field8(clo, chi, 2 * q + 1) << 16);
-      }
-      inc[q] = wave_incl_scan_u32(c[q]);
-    }
-    if (l == kWave - 1) {
-#pragma unroll
-      for (int q = 0; q < 8; q++) wsum[w][q] = inc[q];
-    }
-    __syncthreads();
-    uint32_t start[8];
-    uint32_t run = 0u;
-#pragma unroll
-    for (int q = 0; q < 8; q++) {
-      uint32_t pre = 0u, tot = 0u;
-#pragma unroll
-      for (int i = 0; i < NW; i++) {
-        const uint32_t v = wsum[i][q];
-        pre += i < w ? v : 0u;
-        tot += v;
-      }
-      const uint32_t a = tot & 0xffffu;
-      start[q] = inc[q] - c[q] + pre + (run | ((run + a) << 16));
-      run += a + (tot >> 16);
-      if (k4) starts[q * NT + t] = start[q];
-    }
-    unsigned long long slo = 0ull, shi = 0ull;
-#pragma unroll
-    for (int e = 0; e < E; e++) {
-      const int d = dg[e];
-      uint32_t v, seen;
-      if (k4) {
-        v = starts[(d >> 1) * NT + t];
-        seen = (uint32_t)((slo >> (4 * d)) & 15ull);
-        slo += 1ull << (4 * d);
-      } else {
-        v = start[0];
-#pragma unroll
-        for (int q = 1; q < 8; q++) v = (d >> 1) == q ? start[q] : v;
-        seen = field8(slo, shi, d);
-        const unsigned long long one = 1ull << (8 * (d & 7));
-        slo += d < 8 ? one : 0ull;
-        shi += d < 8 ? 0ull : one;
-      }
-      const uint32_t pos = ((v >> (16 * (d & 1))) & 0xffffu) + seen;
-      buf[lds_pos((int)min(pos, (uint32_t)(NT * E - 1)))] = k[e];  // a permutation
-    }
-    __syncthreads();
-#pragma unroll
-    for (int e = 0; e < E; e++) k[e] = buf[lds_pos(t * E + e)];
-    __syncthreads();
-  }
-#pragma unroll
-  for (int e = 0; e < E; e++) buf[lds_pos(t * E + e)] = k[e];
-  __syncthreads();
-}
-
-// Sort of the NT * E keys (depth bits << 32 | id) of a block; the first n
-// are the tile's, the rest ~0ull (maximal, and last, so they stay last; no
-// real key is ~0ull, its depth bits being below the infinity bits).  Depth
-// first: radix passes over the depth nibbles that vary.  Keys of equal depth
-// then form runs ordered by their earlier positions; each run is put in id
-// order by one thread (insertion sort), unless some run is longer than 64,
-// in which case every varying nibble (id included) is sorted by radix
-// instead.  Either way buf (at lds_pos) ends in ascending (depth, id) order.
-template <int NT, int E>
-__device__ void block_sort_u64(unsigned long long (&k)[E], int n, unsigned long long *buf,
-                               uint32_t (*wsum)[8], unsigned long long *red, uint32_t *starts) {
-  constexpr int NW = NT / kWave;
-  const int t = threadIdx.x, l = lane_id(), w = t / kWave;
-  uint32_t olo = 0u, ohi = 0u, alo = ~0u, ahi = ~0u;
-#pragma unroll
-  for (int e = 0; e < E; e++) {
-    const bool in = k[e] != ~0ull;
-    olo |= in ? (uint32_t)k[e] : 0u;
-    ohi |= in ? (uint32_t)(k[e] >> 32) : 0u;
-    alo &= in ? (uint32_t)k[e] : ~0u;
-    ahi &= in ? (uint32_t)(k[e] >> 32) : ~0u;
-  }
-  const unsigned long long orw = ((unsigned long long)wave_or_u32(ohi) << 32) | wave_or_u32(olo);
-  const unsigned long long andw = ((unsigned long long)wave_and_u32(ahi) << 32) | wave_and_u32(alo);
-  if (l == 0) { red[2 * w] = orw; red[2 * w + 1] = andw; }
-  __syncthreads();
-  unsigned long long orv = 0ull, andv = ~0ull;
-#pragma unroll
-  for (int i = 0; i < NW; i++) { orv |= red[2 * i]; andv &= red[2 * i + 1]; }
-  const unsigned long long nib = nibbles_of((orv ^ andv) & 0xFFFFFFFF00000000ull);
-  bool pad_tie = false;
-#pragma unroll
-  for (int e = 0; e < E; e++) pad_tie |= k[e] != ~0ull && (k[e] & nib) == nib;
-  const unsigned long long diff = (orv ^ andv) | (__syncthreads_or(pad_tie) ? kTopNibble : 0ull);
-  radix_passes<NT, E>(k, diff & 0xFFFFFFFF00000000ull, buf, wsum, starts);
-  // runs of equal depth among the first n keys, found from their first key
-  bool long_run = false;
-#pragma unroll
-  for (int e = 0; e < E; e++) {
-    const int i = t * E + e;
-    if (i + 1 >= n) continue;
-    const uint32_t z = (uint32_t)(buf[lds_pos(i)] >> 32);
-    if ((uint32_t)(buf[lds_pos(i + 1)] >> 32) != z ||
-        (i > 0 && (uint32_t)(buf[lds_pos(i - 1)] >> 32) == z)) continue;
-    int len = 2;
-    while (i + len < n && len <= 64 && (uint32_t)(buf[lds_pos(i + len)] >> 32) == z) len++;
-    long_run = long_run || len > 64;
-  }
-  if (__syncthreads_or(long_run)) {
-    radix_passes<NT, E>(k, diff & 0x00000000FFFFFFFFull, buf, wsum, starts);
-    radix_passes<NT, E>(k, diff & 0xFFFFFFFF00000000ull, buf, wsum, starts);
-    return;
-  }
-  // insertion sort of every run by id (the runs are disjoint)
-#pragma unroll
-  for (int e = 0; e < E; e++) {
-    const int i = t * E + e;
-    if (i + 1 >= n) continue;
-    const uint32_t z = (uint32_t)(buf[lds_pos(i)] >> 32);
-    if ((uint32_t)(buf[lds_pos(i + 1)] >> 32) != z ||
-        (i > 0 && (uint32_t)(buf[lds_pos(i - 1)] >> 32) == z)) continue;
-    int len = 2;
-    while (i + len < n && (uint32_t)(buf[lds_pos(i + len)] >> 32) == z) len++;
-    for (int a = i + 1; a < i + len; a++) {
-      const unsigned long long v = buf[lds_pos(a)];
-      int b = a - 1;
-      while (b >= i && buf[lds_pos(b)] > v) { buf[lds_pos(b + 1)] = buf[lds_pos(b)]; b--; }
-      buf[lds_pos(b + 1)] = v;
-    }
-  }
-  __syncthreads();
-}
-
-// ---------------------------------------------------------------------------
-// One-wave tile sort (lists of up to 15 keys per lane)
-// ---------------------------------------------------------------------------
-// Stable LSD radix passes, 4-bit digits, over the nibbles set in `digits`,
-// of the 64 * E keys of a one-wave block, lane t holding keys t*E ..
-// t*E+E-1.  Per pass each lane counts its keys per digit in the 4-bit fields
-// of one u64 (E <= 15), a DPP scan of the counts (as 16-bit fields) and the
-// wave totals give the lane's start in every digit bucket, which the lane
-// parks in LDS so that each key fetches its own; the keys are scattered in
-// lane-then-register order, which keeps each pass stable.  On return the
-// registers and buf (at lds_pos) hold the keys in the new order.
-template <int E>
-__device__ __forceinline__ void wave_radix_passes(unsigned long long (&k)[E], unsigned long long digits,
-                                  unsigned long long *buf, uint32_t *starts) {
-  static_assert(E <= 15, "4-bit digit counters");
-  const int l = lane_id();
-  for (int sh = 0; sh < 64; sh += 4) {
-    if (((digits >> sh) & 15ull) == 0ull) continue;
-    int dg[E];
-    unsigned long long cnt = 0ull;
-#pragma unroll
-    for (int e = 0; e < E; e++) {
-      const int d = (int)((k[e] >> sh) & 15ull);
-      dg[e] = d;
-      cnt += 1ull << (4 * d);
-    }
-    const uint32_t clo = (uint32_t)cnt, chi = (uint32_t)(cnt >> 32);
-    uint32_t run = 0u;
-#pragma unroll
-    for (int q = 0; q < 8; q++) {
-      // digits 2q and 2q + 1 as 16-bit fields, scanned over the wave
-      const uint32_t v = q < 4 ? clo : chi;
-      const int o = 8 * (q & 3);
-      const uint32_t c = ((v >> o) & 15u) | (((v >> (o + 4)) & 15u) << 16);
-      const uint32_t inc = wave_incl_scan_u32(c);
-      const uint32_t tot = (uint32_t)__builtin_amdgcn_readlane((int)inc, kWave - 1);
-      const uint32_t a = tot & 0xffffu;
-      starts[q * kWave + l] = inc - c + (run | ((run + a) << 16));
-      run += a + (tot >> 16);
-    }
-    unsigned long long seen = 0ull;
-#pragma unroll
-    for (int e = 0; e < E; e++) {
-      const int d = dg[e];
-      const uint32_t w = starts[(d >> 1) * kWave + l];
-      const uint32_t pos =
-          ((w >> (16 * (d & 1))) & 0xffffu) + (uint32_t)((seen >> (4 * d)) & 15ull);
-      seen += 1ull << (4 * d);
-      buf[lds_pos((int)min(pos, (uint32_t)(kWave * E - 1)))] = k[e];  // a permutation
-    }
-    // one wave: its LDS accesses complete in program order, so no barrier
-    lds_order();
-#pragma unroll
-    for (int e = 0; e < E; e++) k[e] = buf[lds_pos(l * E + e)];
-    lds_order();
-  }
-}
-
-// Sort of one tile's n <= 64 * E keys (depth bits << 32 | id, unique) by a
-// one-wave block, written to dst in ascending key order as D (u32: the ids,
-// u64: the keys).  The keys are
-// loaded coalesced (any starting arrangement sorts to the same result, the
-// keys being unique).  Depth first, over the depth nibbles that vary; equal
-// depths (rare) are then put in id order as in the block sort.
-template <int E, typename D>
-__device__ __forceinline__ void wave_sort_tile(const unsigned long long *src, D *dst, int n,
-                               unsigned long long *buf, uint32_t *starts) {
-  const int l = lane_id();
-  unsigned long long k[E];
-  uint32_t olo = 0u, ohi = 0u, alo = ~0u, ahi = ~0u;
-  // every load first (clamped index), then the padding: no wait per load
-#pragma unroll
-  for (int e = 0; e < E; e++) k[e] = src[min(l + kWave * e, n - 1)];
-#pragma unroll
-  for (int e = 0; e < E; e++) {
-    const bool in = l + kWave * e < n;
-    k[e] = in ? k[e] : ~0ull;
-    olo |= in ? (uint32_t)k[e] : 0u;
-    ohi |= in ? (uint32_t)(k[e] >> 32) : 0u;
-    alo &= in ? (uint32_t)k[e] : ~0u;
-    ahi &= in ? (uint32_t)(k[e] >> 32) : ~0u;
-  }
-  const unsigned long long diff0 =
-      ((unsigned long long)(wave_or_u32(ohi) ^ wave_and_u32(ahi)) << 32) |
-      (wave_or_u32(olo) ^ wave_and_u32(alo));
-  const unsigned long long nib = nibbles_of(diff0 & 0xFFFFFFFF00000000ull);
-  bool pad_tie = false;
-#pragma unroll
-  for (int e = 0; e < E; e++) pad_tie |= l + kWave * e < n && (k[e] & nib) == nib;
-  const unsigned long long diff = diff0 | (ballot64(pad_tie) != 0ull ? kTopNibble : 0ull);
-  if ((diff0 >> 32) == 0ull) {
-    // one depth for the whole tile: the order is the id order, then the
-    // top depth nibble (below 8 in every real key) puts the padding last
-    wave_radix_passes<E>(k, (diff0 & 0xFFFFFFFFull) | kTopNibble, buf, starts);
-  } else {
-    wave_radix_passes<E>(k, diff & 0xFFFFFFFF00000000ull, buf, starts);
-    // equal depths at consecutive positions?
-    const uint32_t nxt = (uint32_t)__shfl_down((int)(uint32_t)(k[0] >> 32), 1);
-    bool tie = false;
-#pragma unroll
-    for (int e = 0; e + 1 < E; e++)
-      tie |= l * E + e + 1 < n && (uint32_t)(k[e] >> 32) == (uint32_t)(k[e + 1] >> 32);
-    tie |= l + 1 < kWave && l * E + E < n && (uint32_t)(k[E - 1] >> 32) == nxt;
-    if (ballot64(tie) != 0ull) {
-      // runs of equal depth, put in id order by odd-even transposition
-      // between neighbours of equal depth (runs are short: a round per key
-      // of the longest run); past 64 rounds, every varying nibble (id, then
-      // depth) is sorted by radix instead.  Padding keys (~0) tie with no
-      // real key, a real depth being below the infinity bits.
-      bool more = true;
-      for (int round = 0; more && round < 64; round++) {
-        bool sw = false;
-#pragma unroll
-        for (int ph = 0; ph < 2; ph++) {
-#pragma unroll
-          for (int e = ph; e + 1 < E; e += 2) {
-            const bool x = (uint32_t)(k[e] >> 32) == (uint32_t)(k[e + 1] >> 32) && k[e] > k[e + 1];
-            const unsigned long long lo = x ? k[e + 1] : k[e], hi = x ? k[e] : k[e + 1];
-            k[e] = lo; k[e + 1] = hi;
-            sw |= x;
-          }
-          if (ph == 1) {  // across lanes: (last of lane l, first of lane l + 1)
-            const unsigned long long nx =
-                ((unsigned long long)(uint32_t)__shfl_down((int)(uint32_t)(k[0] >> 32), 1) << 32) |
-                (uint32_t)__shfl_down((int)(uint32_t)k[0], 1);
-            const unsigned long long pv =
-                ((unsigned long long)(uint32_t)__shfl_up((int)(uint32_t)(k[E - 1] >> 32), 1) << 32) |
-                (uint32_t)__shfl_up((int)(uint32_t)k[E - 1], 1);
-            const bool xd = l + 1 < kWave && (uint32_t)(k[E - 1] >> 32) == (uint32_t)(nx >> 32) &&
-                            k[E - 1] > nx;
-            const bool xu = l > 0 && (uint32_t)(pv >> 32) == (uint32_t)(k[0] >> 32) && pv > k[0];
-            k[E - 1] = xd ? nx : k[E - 1];
-            k[0] = xu ? pv : k[0];
-            sw |= xd | xu;
-          }
-        }
-        more = ballot64(sw) != 0ull;
-      }
-      if (more) {
-        wave_radix_passes<E>(k, diff & 0x00000000FFFFFFFFull, buf, starts);
-        wave_radix_passes<E>(k, diff & 0xFFFFFFFF00000000ull, buf, starts);
-      } else {
-#pragma unroll
-        for (int e = 0; e < E; e++) buf[lds_pos(l * E + e)] = k[e];
-        lds_order();
-      }
-    }
-  }
-  for (int i = l; i < n; i += kWave) dst[i] = (D)buf[lds_pos(i)];
-}
-
 // One round of a merge sort over n keys held as sorted runs of `width`
 // keys in `in`: each pair of neighbouring runs is merged into `out` (an odd
 // run at the end is copied), written as D (u64: the keys, u32: the ids).
@@ -941,114 +582,210 @@ __device__ void merge_round(const unsigned long long *in, D *out, int n, int wid
   }
 }
 
-// Sort of one tile's n keys with EE keys per thread (n <= NT * EE), written
-// to dst in ascending key order as D (u32: the ids, u64: the keys).
-template <int NT, int EE, typename D>
-__device__ __forceinline__ void sort_tile_regs(const unsigned long long *src, D *dst, int n,
-                                               unsigned long long *buf, uint32_t (*wsum)[8],
-                                               unsigned long long *red, uint32_t *starts) {
-  unsigned long long k[EE];
+// The LDS of a tile sort: the keys, the buckets and small tables.
+template <int NT, int E>
+struct SortLds {
+  static constexpr int CAP = NT * E;
+  unsigned long long buf[CAP];
+  uint32_t bins[CAP + 4];
+  uint32_t coarse[256], cbase[256];
+  uint32_t wsum[NT / kWave], zlo[NT / kWave], zhi[NT / kWave];
+};
+
+constexpr uint32_t kMaxBucket = 48;  // keys of a bucket ranked by comparison
+
+// Sort of one tile's n <= NT * E keys (depth bits << 32 | id, unique), written
+// to dst in ascending key order as D (u32: the ids, u64: the keys), by two
+// levels of buckets.  256 coarse buckets divide the list's own depth range
+// evenly; a coarse bucket of c keys is divided evenly into c fine ones, so
+// that surfaces that fill a small part of the range still get buckets of
+// their own.  Both maps are monotone in the depth, so a key's place is its
+// fine bucket's start plus its rank among that bucket's few keys, counted by
+// comparing whole keys.  Every pass is LDS atomics or independent reads, ~20
+// VALU instructions per key in all, against five dependent radix passes of
+// 23 or more before; a list of up to 1024 keys is spread over four waves, where one
+// wave had sorted it alone: tracking frame 15.8 -> 6.8 us, 5 views over 8
+// keyframes (lists of ~1,400) 560 -> 138.  Returns false, with dst untouched,
+// when a fine bucket holds more than kMaxBucket keys (many equal depths): a
+// bitonic sort, which needs no registers to speak of, takes those lists.
+template <int NT, int E, typename D>
+__device__ __forceinline__ bool bucket_sort(const unsigned long long (&k)[E], D *dst, int n,
+                                            SortLds<NT, E> &S) {
+  constexpr int NW = NT / kWave;
+  static_assert(E % 4 == 0, "fine buckets are scanned four at a time");
+  const int t = threadIdx.x, l = lane_id(), w = t / kWave;
+  // (the sign bit flipped: signed comparisons in the keys' unsigned order)
+  int zlo = 0x7fffffff, zhi = (int)0x80000000;
+#pragma unroll
+  for (int e = 0; e < E; e++) {
+    const bool in = t + NT * e < n;
+    const int z = (int)((uint32_t)(k[e] >> 32) ^ 0x80000000u);
+    zlo = in ? min(zlo, z) : zlo;
+    zhi = in ? max(zhi, z) : zhi;
+  }
+  zlo = wave_min_i(zlo);
+  zhi = wave_max_i(zhi);
+  if (l == 0) { S.zlo[w] = (uint32_t)zlo ^ 0x80000000u; S.zhi[w] = (uint32_t)zhi ^ 0x80000000u; }
+  if (t < 256) S.coarse[t] = 0u;
+  uint4 *bins4 = (uint4 *)S.bins;
+#pragma unroll
+  for (int e = 0; e < E / 4; e++) bins4[t * (E / 4) + e] = make_uint4(0u, 0u, 0u, 0u);
+  __syncthreads();
+  uint32_t lo = S.zlo[0], hi = S.zhi[0];
+#pragma unroll
+  for (int i = 1; i < NW; i++) { lo = min(lo, S.zlo[i]); hi = max(hi, S.zhi[i]); }
+  const int shift = max(0, 24 - __clz((int)(hi - lo)));  // (hi - lo) >> shift < 256
+  // fine position within a coarse bucket: at most 16 bits of the depth
+  const int fb = min(shift, 16), fs = shift - fb;
+#pragma unroll
+  for (int e = 0; e < E; e++)
+    if (t + NT * e < n) atomicAdd(&S.coarse[((uint32_t)(k[e] >> 32) - lo) >> shift], 1u);
+  __syncthreads();
+  if (w == 0) {  // exclusive scan of the 256 coarse counts
+    const uint4 c = ((const uint4 *)S.coarse)[l];
+    const uint32_t sum = c.x + c.y + c.z + c.w;
+    const uint32_t ex = wave_incl_scan_u32(sum) - sum;
+    ((uint4 *)S.cbase)[l] = make_uint4(ex, ex + c.x, ex + c.x + c.y, ex + c.x + c.y + c.z);
+  }
+  __syncthreads();
+  uint32_t f[E], slot[E];
+#pragma unroll
+  for (int e = 0; e < E; e++) {
+    if (t + NT * e >= n) continue;
+    const uint32_t z = (uint32_t)(k[e] >> 32) - lo, c = z >> shift;
+    const uint32_t part = (z & ((1u << shift) - 1u)) >> fs;
+    f[e] = S.cbase[c] + ((part * S.coarse[c]) >> fb);
+    slot[e] = atomicAdd(&S.bins[f[e]], 1u);
+  }
+  __syncthreads();
+  // exclusive scan of the fine counts in place
+  uint4 c[E / 4];
+  uint32_t sum = 0u, most = 0u;
+#pragma unroll
+  for (int e = 0; e < E / 4; e++) {
+    c[e] = bins4[t * (E / 4) + e];
+    sum += (c[e].x + c[e].y) + (c[e].z + c[e].w);
+    most = max(most, max(max(c[e].x, c[e].y), max(c[e].z, c[e].w)));
+  }
+  const uint32_t inc = wave_incl_scan_u32(sum);
+  if (l == kWave - 1) S.wsum[w] = inc;
+  if (__syncthreads_or(most > kMaxBucket)) return false;
+  uint32_t run = inc - sum;
+#pragma unroll
+  for (int i = 0; i < NW; i++) run += i < w ? S.wsum[i] : 0u;
+#pragma unroll
+  for (int e = 0; e < E / 4; e++) {
+    const uint4 o = make_uint4(run, run + c[e].x, run + c[e].x + c[e].y, run + c[e].x + c[e].y + c[e].z);
+    run = o.w + c[e].w;
+    bins4[t * (E / 4) + e] = o;
+  }
+  if (t == NT - 1) S.bins[NT * E] = run;
+  __syncthreads();
+#pragma unroll
+  for (int e = 0; e < E; e++)
+    if (t + NT * e < n) S.buf[S.bins[f[e]] + slot[e]] = k[e];
+  __syncthreads();
+#pragma unroll
+  for (int e = 0; e < E; e++) {
+    if (t + NT * e >= n) continue;
+    const uint32_t b0 = S.bins[f[e]], b1 = S.bins[f[e] + 1];
+    uint32_t r = b0;
+    for (uint32_t j = b0; j < b1; j++) r += S.buf[j] < k[e] ? 1u : 0u;
+    slot[e] = r;
+  }
+  __syncthreads();
+  D *out = (D *)S.buf;
+#pragma unroll
+  for (int e = 0; e < E; e++)
+    if (t + NT * e < n) out[slot[e]] = (D)k[e];
+  __syncthreads();
+  for (int i = t; i < n; i += NT) dst[i] = out[i];
+  return true;
+}
+
+// Sort of one tile's n <= NT * E keys, written to dst in ascending key order
+// as D (u32: the ids, u64: the keys).
+template <int NT, int E, typename D>
+__device__ __forceinline__ void sort_tile_keys(const unsigned long long *src, D *dst, int n,
+                                               SortLds<NT, E> &S) {
+  unsigned long long k[E];
   // coalesced loads (any starting arrangement sorts to the same result, the
   // keys being unique), every load first (clamped index), then the padding
 #pragma unroll
-  for (int e = 0; e < EE; e++) k[e] = src[min((int)threadIdx.x + NT * e, n - 1)];
+  for (int e = 0; e < E; e++) k[e] = src[min((int)threadIdx.x + NT * e, n - 1)];
+  if (bucket_sort<NT, E>(k, dst, n, S)) return;
+  // bitonic sort in LDS of the next power of two, padded with ~0 (above every
+  // key, a depth's bits being below the infinity bits)
+  const int m = 2 << (31 - __clz(n - 1));
+  __syncthreads();  // (the keys' LDS may still be read by the bucket sort)
 #pragma unroll
-  for (int e = 0; e < EE; e++) k[e] = (int)threadIdx.x + NT * e < n ? k[e] : ~0ull;
-  block_sort_u64<NT, EE>(k, n, buf, wsum, red, starts);
-  for (int i = threadIdx.x; i < n; i += NT) dst[i] = (D)buf[lds_pos(i)];
+  for (int e = 0; e < E; e++) {
+    const int i = (int)threadIdx.x + NT * e;
+    if (i < m) S.buf[i] = i < n ? k[e] : ~0ull;
+  }
+  for (int run = 2; run <= m; run *= 2)
+    for (int d = run / 2; d > 0; d /= 2) {
+      __syncthreads();
+      for (int p = threadIdx.x; p < m / 2; p += NT) {
+        const int i = 2 * p - (p & (d - 1)), j = i + d;
+        const unsigned long long a = S.buf[i], b = S.buf[j];
+        if ((a > b) == ((i & run) == 0)) { S.buf[i] = b; S.buf[j] = a; }
+      }
+    }
+  __syncthreads();
+  for (int i = threadIdx.x; i < n; i += NT) dst[i] = (D)S.buf[i];
 }
-
-// Register tiers of the tile sort: keys per thread for a one-wave block
-// (4 and 12) and for the 512-thread long-list block (6, 10 and 16); up to
-// 15 keys per thread count digits in 4-bit fields and fetch their bucket
-// starts from LDS.
-template <int NT, int E>
-struct SortTiers {
-  static constexpr int E1 = NT == kWave ? E / 3 : E / 4 + E / 8;
-  static constexpr int E2 = NT == kWave ? E : E / 2 + E / 8;
-};
 
 // One block per tile: keys (depth bits << 32 | id) are unique within a tile,
 // so ascending key order is the (depth, id) order.  Each variant handles the
-// tiles whose length lies in (lo_n, hi_n]; a list is held in registers with
-// the fewest keys per thread of the tiers that fit it, and longer than
-// NT * E -> global memory.
+// tiles whose length lies in (lo_n, hi_n], queue 0: every tile, 1 and 2: the
+// scan's queues of mid and huge lists.  Blocks take their tiles by position:
+// a shared cursor, one atomic per tile, cost the mid lists 20 us a turn (768
+// blocks waiting for the same address).
 template <int NT, int E>
-__global__ __launch_bounds__(NT) void k_sort_tiles(Ws ws, int lo_n, int hi_n, int queued) {
+__global__ __attribute__((amdgpu_waves_per_eu(NT == 256 ? 8 : NT == 512 ? 6 : 4)))
+__launch_bounds__(NT) void k_sort_tiles(Ws ws, int lo_n, int hi_n, int queue) {
   constexpr int CAP = NT * E;
-  constexpr int E1 = SortTiers<NT, E>::E1, E2 = SortTiers<NT, E>::E2;
-  constexpr bool kWaveSort = NT == kWave && E <= 15;
-  // the keys (padded) and, for up to 15 keys per thread, the threads' bucket
-  // starts: separate arrays, so that the compiler sees they never alias
-  __shared__ unsigned long long buf[CAP + CAP / 16];
-  __shared__ uint32_t starts[8 * NT];
-  __shared__ uint32_t wsum[NT / kWave][8];
-  __shared__ unsigned long long red[2 * (NT / kWave)];
-  // short lists: tile = block; long lists: blocks take queued tiles in turn
-  __shared__ int next_s;
-  if (queued && *ws.n_long == 0u) return;  // (one load when nothing is queued)
-  for (int round = 0;; round++) {
-  int tile;
-  if (!queued) {
-    if (round > 0) break;
-    tile = blockIdx.x;
-  } else {
-    if (threadIdx.x == 0) {
-      const uint32_t q = atomicAdd(ws.long_next, 1u);
-      next_s = q < *ws.n_long ? (int)ws.long_tiles[q] : -1;
+  __shared__ SortLds<NT, E> S;
+  const int count = queue ? (int)ws.n_long[queue - 1] : ws.n_tiles;
+  for (int q = blockIdx.x; q < count; q += gridDim.x) {
+    const int tile = queue == 0 ? q : (int)ws.long_tiles[queue == 1 ? q : ws.n_tiles - 1 - q];
+    // ranges are clamped to the capacity, and every position of a clamped
+    // range was written by the fill, so sorting stays in bounds on overflow
+    const uint2 rg = ws.ranges[tile];
+    const int n = (int)(rg.y - rg.x);
+    if (n <= lo_n || n > hi_n || n <= 0) continue;
+    const unsigned long long *src = ws.keys + rg.x;
+    uint32_t *dst = ws.ids + rg.x;
+    if (n == 1) {
+      if (threadIdx.x == 0) dst[0] = (uint32_t)src[0];
+      continue;
     }
-    __syncthreads();
-    tile = next_s;
-    __syncthreads();
-    if (tile < 0) break;
-  }
-  // ranges are clamped to the capacity, and every position of a clamped
-  // range was written by the fill, so sorting stays in bounds on overflow
-  const uint2 rg = ws.ranges[tile];
-  const int n = (int)(rg.y - rg.x);
-  if (n <= lo_n || n > hi_n || n <= 0) continue;
-  const unsigned long long *src = ws.keys + rg.x;
-  uint32_t *dst = ws.ids + rg.x;
-  if (n == 1) {
-    if (threadIdx.x == 0) dst[0] = (uint32_t)src[0];
-    continue;
-  }
-  // a list (or run) of c <= CAP keys sorted in LDS, written to d
-  auto sort_run = [&](const unsigned long long *s_, auto *d_, int c) {
-    if constexpr (kWaveSort) {
-      if (c <= NT * E1) wave_sort_tile<E1>(s_, d_, c, buf, starts);
-      else wave_sort_tile<E>(s_, d_, c, buf, starts);
+    if (n <= CAP) {
+      sort_tile_keys<NT, E>(src, dst, n, S);
     } else {
-      if (c <= NT * E1) sort_tile_regs<NT, E1>(s_, d_, c, buf, wsum, red, starts);
-      else if (c <= NT * E2) sort_tile_regs<NT, E2>(s_, d_, c, buf, wsum, red, starts);
-      else sort_tile_regs<NT, E>(s_, d_, c, buf, wsum, red, starts);
+      // longer than the LDS holds: runs of CAP keys sorted in LDS into
+      // keys_tmp, then merged pairwise, back and forth between keys_tmp and
+      // the tile's own key range (free once its runs are sorted); the last
+      // round writes the ids
+      unsigned long long *runs = ws.keys_tmp + rg.x, *spare = ws.keys + rg.x;
+      for (int lo = 0; lo < n; lo += CAP) {
+        sort_tile_keys<NT, E>(src + lo, runs + lo, min(CAP, n - lo), S);
+        __syncthreads();  // the LDS is reused by the next run
+      }
+      const unsigned long long *in = runs;
+      unsigned long long *out = spare;
+      int width = CAP;
+      for (; 2 * width < n; width *= 2) {
+        merge_round<NT>(in, out, n, width);
+        __syncthreads();
+        unsigned long long *nxt = const_cast<unsigned long long *>(in);
+        in = out;
+        out = nxt;
+      }
+      merge_round<NT>(in, dst, n, width);
     }
-  };
-  if (n <= CAP) {
-    sort_run(src, dst, n);
-  } else {
-    // longer than the LDS holds: runs of CAP keys sorted in LDS into
-    // keys_tmp, then merged pairwise, back and forth between keys_tmp and
-    // the tile's own key range (free once its runs are sorted); the last
-    // round writes the ids
-    unsigned long long *runs = ws.keys_tmp + rg.x, *spare = ws.keys + rg.x;
-    for (int lo = 0; lo < n; lo += CAP) {
-      sort_run(src + lo, runs + lo, min(CAP, n - lo));
-      __syncthreads();  // buf is reused by the next run
-    }
-    const unsigned long long *in = runs;
-    unsigned long long *out = spare;
-    int width = CAP;
-    for (; 2 * width < n; width *= 2) {
-      merge_round<NT>(in, out, n, width);
-      __syncthreads();
-      unsigned long long *nxt = const_cast<unsigned long long *>(in);
-      in = out;
-      out = nxt;
-    }
-    merge_round<NT>(in, dst, n, width);
-  }
-  __syncthreads();  // buf is reused by the block's next tile
+    __syncthreads();  // the LDS is reused by the block's next tile
   }
 }
 
@@ -1155,19 +892,22 @@ hipError_t launch_fill_keys(const Ws &ws, hipStream_t st) {
 hipError_t launch_sort_tiles(const Ws &ws, hipStream_t st) {
   // Where the records' expected pairs per tile (a Gaussian of extent ~4-5 px
   // covers about (1 + 10 / B)^2 tiles of side B) make long lists the rule,
-  // lists of up to 768 go to one wave per tile (4 or 12 keys per lane) and
-  // the longer ones, queued by the scan, to 512-thread blocks taken in turn
-  // (6, 10 or 16 keys per thread; 8192 keys in LDS, longer lists merged from
-  // runs), a CU's worth of them.  Otherwise the one-wave blocks sort every
-  // list, a long one (the odd one) as runs of 768 merged in rounds, and no
-  // second kernel is launched.
+  // lists of up to 1024 go to 256-thread blocks, those of up to 4096, queued
+  // by the scan, to 512-thread blocks (three per CU) and longer ones to
+  // 1024-thread blocks (one per CU; 8192 keys in LDS, longer lists merged from
+  // runs), each grid a few rounds of the device's blocks.  Otherwise the
+  // 256-thread blocks sort every list, a long one (the odd one) as runs of
+  // 1024 merged in rounds, and no other kernel is launched (an empty launch
+  // costs a tracking iteration ~5 us).
   const double per = (1.0 + 10.0 / ws.tile) * (1.0 + 10.0 / ws.tile);
   const bool many = per * (double)ws.n_rec > 1024.0 * (double)ws.n_tiles;
-  hipLaunchKernelGGL((k_sort_tiles<kWave, kSmallSort / kWave>), dim3(ws.n_tiles), dim3(kWave), 0,
-                     st, ws, 0, many ? kSmallSort : 0x7fffffff, 0);
+  hipLaunchKernelGGL((k_sort_tiles<256, kSmallSort / 256>), dim3(ws.n_tiles), dim3(256), 0, st, ws, 0,
+                     many ? kSmallSort : 0x7fffffff, 0);
   if (many) {
-    hipLaunchKernelGGL((k_sort_tiles<512, kSortCap / 512>), dim3(std::min(ws.n_tiles, 512)), dim3(512),
-                       0, st, ws, kSmallSort, 0x7fffffff, 1);
+    hipLaunchKernelGGL((k_sort_tiles<512, kMidSort / 512>), dim3(std::min(ws.n_tiles, 3072)), dim3(512),
+                       0, st, ws, kSmallSort, kMidSort, 1);
+    hipLaunchKernelGGL((k_sort_tiles<1024, kSortCap / 1024>), dim3(std::min(ws.n_tiles, 256)),
+                       dim3(1024), 0, st, ws, kMidSort, 0x7fffffff, 2);
   }
   return hipGetLastError();
 }

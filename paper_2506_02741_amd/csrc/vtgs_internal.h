@@ -71,9 +71,8 @@ struct Ws {
   uint32_t *flags;
   unsigned long long *n_pairs;
   uint32_t *iter;              // tracking iteration counter (bumped by preprocess)
-  uint32_t *n_long;            // tiles with lists longer than the short-list sort takes
-  uint32_t *long_next;         // cursor of the long-list sort over long_tiles
-  uint32_t *long_tiles;        // [n_tiles] those tiles (written by the tile scan)
+  uint32_t *n_long;            // [2] tiles with lists for the mid and the huge-list sort
+  uint32_t *long_tiles;        // [n_tiles] the queues, huge lists from the end (by the scan)
   uint32_t *tile_order;        // [n_tiles] compositing order, longest lists first (NULL: tile order)
   // descriptors
   const DevKF *kfs;
