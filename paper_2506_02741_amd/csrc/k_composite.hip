@@ -59,9 +59,11 @@ namespace {
 
 constexpr float kNegHalfLog2e = -0.72134752044448170368f;  // -log2(e) / 2
 
-// Eq. 1 evaluated inside the tracking backward.
+// Eq. 1 evaluated inside the tracking backward (on = 0: upstream gradients
+// come from the caller's arrays).
 struct TrackArgs {
   float alpha, beta, sil_thr;
+  int on;
 };
 
 __device__ __forceinline__ float sgn(float x) { return (float)((x > 0.f) - (x < 0.f)); }
@@ -510,8 +512,8 @@ __global__ __attribute__((amdgpu_waves_per_eu(TILE == 16 ? 4 : 2))) __launch_bou
   }
 }
 
-// Staging of one list entry for the backward to slots: the forward record,
-// the camera-frame centre and learnable flag, the record's tile rectangle and
+// Backward staging of one list entry: the forward record, the camera-frame
+// centre and learnable flag, and (slot mode) the record's tile rectangle and
 // first slot.  Gathered without branches, as in the forward.
 struct BwdEntry {
   float4 e0, e1, e2, eb;
@@ -520,6 +522,7 @@ struct BwdEntry {
   bool ok;
 };
 
+template <bool kSlots>
 __device__ __forceinline__ void fetch_bwd_entry(const Ws &ws, int n_rec, int rec_base, uint32_t id,
                                                 BwdEntry &E) {
   E.ok = id < (uint32_t)n_rec;
@@ -527,8 +530,7 @@ __device__ __forceinline__ void fetch_bwd_entry(const Ws &ws, int n_rec, int rec
   const float4 *A = ws.recA + 3 * rec;
   E.e0 = A[0]; E.e1 = A[1]; E.e2 = A[2];
   E.eb = ws.recB[rec];
-  E.rc = ws.rect[rec];
-  E.off = ws.rec_off[rec];
+  if (kSlots) { E.rc = ws.rect[rec]; E.off = ws.rec_off[rec]; }
 }
 
 // The (record, tile) slot of a staged entry of tile (tx, ty), or ~0u when
@@ -551,42 +553,64 @@ __device__ __forceinline__ void kLdsOrder() { asm volatile("" ::: "memory"); }
 template <bool kGeo>
 using AccB = typename std::conditional<kGeo, f32x4, float>::type;
 
-// The per-pixel state of a backward: the forward's transmittance and last
-// contributor, the upstream gradient (Eq. 1's where kTrack, alpha W |V - V'| +
-// beta W |D - D'| with W = vis & (D > 0) & (S' > thr), and this lane's share
-// of the tile's loss, else the caller's arrays) and the difference recurrence
-// at the back: E = (1 - alpha_b) g.(x_b - B_b) of the contributor b behind (0),
-// its colour and depth XP (the background and 0), and GS1 = g_S (1 - its
-// coverage).
-template <int PPT>
-struct BwdPixels {
-  float px[PPT], py[PPT], T[PPT], gC0[PPT], gC1[PPT], gC2[PPT], gD[PPT];
+// Slot modes hold three waves per SIMD (their LDS allows three blocks per CU)
+// unless they carry geometry (two).
+template <int TILE, int BATCH, int MODE>
+__global__ __launch_bounds__(Shape<TILE>::NT, (MODE & 2) ? ((MODE & 4) ? 2 : 3) : 1) void k_bwd(Ws ws, const float *g_rgb,
+                                                         const float *g_depth,
+                                                         const float *g_sil, TrackArgs tr) {
+  constexpr int NT = Shape<TILE>::NT, PPT = Shape<TILE>::PPT;
+  constexpr int NW = NT / kWave;
+  constexpr int PER = (BATCH + NT - 1) / NT;
+  constexpr bool kTwist = (MODE & 1) != 0, kSlots = (MODE & 2) != 0;
+  constexpr bool kGeo = kSlots && (MODE & 4) != 0;  // slots also carry dL/dp
+  constexpr int NA = kGeo ? 8 : 5;                   // floats per slot
+  constexpr int AB = kSlots ? BATCH : 1;
+  constexpr int G = Group<TILE, BATCH>::G, NS = Group<TILE, BATCH>::NS, NR = NW * PPT;
+  // staged entry: e0 (mx, my, qa, 2 qb), e1 (qc, o, z, qb), e2 (c, r)
+  __shared__ float4 e0s[BATCH], e1s[BATCH], e2s[BATCH];
+  __shared__ float4 ejs[BATCH];   // (fx/z, fy/z, -fx px/z^2, -fy py/z^2)
+  __shared__ float4 eps_[BATCH];  // (px, py, 2 r^2 / z, learnable)
+  __shared__ uint32_t slot_s[AB];
+  // per-wave slot accumulators: floats 0-3 in accA, 4 (4-7 with geometry)
+  // in accB, and the claim tags of their read-modify-write
+  __shared__ f32x4 accA[NW][AB];
+  __shared__ AccB<kGeo> accB[NW][AB];
+  __shared__ uint8_t tag_s[kSlots ? NW : 1][AB + kWave];  // + a tag per lane
+  __shared__ int maxlast_s;
+  __shared__ float red_s[NW][7];
+  __shared__ uint32_t words[NS][NR][kWave];
+
+  const int t = tile_of_block(ws);
+  const DevView &vw = ws.views[find_view_by_tile(ws, t)];
+  const int lt = t - vw.tile_base;
+  const int tx = lt % vw.tiles_x, ty = lt / vw.tiles_x;
+  const int ox = tx * TILE, oy = ty * TILE;
+  const uint2 rg = ws.ranges[t];
+  const int start = (int)rg.x, end = (int)rg.y;
+  const int64_t P = ws.P;
+  const int w = threadIdx.x / kWave;
+
+  float px[PPT], py[PPT], T[PPT], gC0[PPT], gC1[PPT], gC2[PPT], gD[PPT], gS[PPT];
+  // the difference recurrence: (1 - alpha_b) g.(x_b - B_b) of the
+  // contributor b behind (0 at the back), its colour and depth (the
+  // background and 0 at the back) and g_S (1 - its coverage x_S)
   float E[PPT], XP0[PPT], XP1[PPT], XP2[PPT], XPZ[PPT], GS1[PPT];
   uint32_t last[PPT];
-  uint32_t mylast;
-  float lsum;
-};
-
-template <int TILE, bool kTrack>
-__device__ __forceinline__ void load_pixels(const Ws &ws, const DevView &vw, int ox, int oy,
-                                            const float *g_rgb, const float *g_depth,
-                                            const float *g_sil, const TrackArgs &tr,
-                                            BwdPixels<Shape<TILE>::PPT> &S) {
-  const int64_t P = ws.P;
-  S.mylast = 0u;
-  S.lsum = 0.f;
+  uint32_t mylast = 0;
+  float lsum = 0.f;  // this lane's share of the tile's Eq. 1 loss
 #pragma unroll
-  for (int k = 0; k < Shape<TILE>::PPT; k++) {
+  for (int k = 0; k < PPT; k++) {
     int x, y;
     lane_pixel<TILE>(k, x, y);
-    S.px[k] = (float)(ox + x);
-    S.py[k] = (float)(oy + y);
+    px[k] = (float)(ox + x);
+    py[k] = (float)(oy + y);
     const bool valid = (ox + x) < vw.width && (oy + y) < vw.height;
     const int64_t p = vw.pix_off + (int64_t)(oy + y) * vw.width + (ox + x);
-    S.T[k] = valid ? ws.t_final[p] : 1.f;
-    S.last[k] = valid ? ws.last[p] : 0u;
-    float gS = 0.f;
-    if constexpr (kTrack) {
+    T[k] = valid ? ws.t_final[p] : 1.f;
+    last[k] = valid ? ws.last[p] : 0u;
+    if (tr.on) {
+      // Eq. 1: alpha W |V - V'| + beta W |D - D'|, W = vis & (D > 0) & (S' > thr)
       const int64_t lp = p - vw.pix_off;
       const int64_t Pv = (int64_t)vw.width * vw.height;
       float od = 0.f;
@@ -599,305 +623,24 @@ __device__ __forceinline__ void load_pixels(const Ws &ws, const DevView &vw, int
       const float r1 = valid ? vw.obs_rgb[Pv + lp] - ws.img[P + p] : 0.f;
       const float r2 = valid ? vw.obs_rgb[2 * Pv + lp] - ws.img[2 * P + p] : 0.f;
       const float rd = valid ? od - ws.img[3 * P + p] : 0.f;
-      S.gC0[k] = W ? -tr.alpha * sgn(r0) : 0.f;
-      S.gC1[k] = W ? -tr.alpha * sgn(r1) : 0.f;
-      S.gC2[k] = W ? -tr.alpha * sgn(r2) : 0.f;
-      S.gD[k] = W ? -tr.beta * sgn(rd) : 0.f;
-      S.lsum += W ? tr.alpha * ((fabsf(r0) + fabsf(r1)) + fabsf(r2)) + tr.beta * fabsf(rd) : 0.f;
+      gC0[k] = W ? -tr.alpha * sgn(r0) : 0.f;
+      gC1[k] = W ? -tr.alpha * sgn(r1) : 0.f;
+      gC2[k] = W ? -tr.alpha * sgn(r2) : 0.f;
+      gD[k] = W ? -tr.beta * sgn(rd) : 0.f;
+      gS[k] = 0.f;
+      lsum += W ? tr.alpha * ((fabsf(r0) + fabsf(r1)) + fabsf(r2)) + tr.beta * fabsf(rd) : 0.f;
     } else {
-      S.gC0[k] = (valid && g_rgb) ? g_rgb[p] : 0.f;
-      S.gC1[k] = (valid && g_rgb) ? g_rgb[P + p] : 0.f;
-      S.gC2[k] = (valid && g_rgb) ? g_rgb[2 * P + p] : 0.f;
-      S.gD[k] = (valid && g_depth) ? g_depth[p] : 0.f;
-      gS = (valid && g_sil) ? g_sil[p] : 0.f;
+      gC0[k] = (valid && g_rgb) ? g_rgb[p] : 0.f;
+      gC1[k] = (valid && g_rgb) ? g_rgb[P + p] : 0.f;
+      gC2[k] = (valid && g_rgb) ? g_rgb[2 * P + p] : 0.f;
+      gD[k] = (valid && g_depth) ? g_depth[p] : 0.f;
+      gS[k] = (valid && g_sil) ? g_sil[p] : 0.f;
     }
-    S.E[k] = 0.f;
-    S.XP0[k] = ws.bg[0]; S.XP1[k] = ws.bg[1]; S.XP2[k] = ws.bg[2]; S.XPZ[k] = 0.f;
-    S.GS1[k] = gS;
-    S.mylast = max(S.mylast, S.last[k]);
+    E[k] = 0.f;
+    XP0[k] = ws.bg[0]; XP1[k] = ws.bg[1]; XP2[k] = ws.bg[2]; XPZ[k] = 0.f;
+    GS1[k] = gS[k];
+    mylast = max(mylast, last[k]);
   }
-}
-
-// Per tile: the lanes' six twist sums and the Eq. 1 loss, wave by wave.
-template <int NW>
-__device__ __forceinline__ void store_twist(const Ws &ws, int t, const float (&tw)[6], float lsum,
-                                            float (*red)[7]) {
-  const int w = threadIdx.x / kWave;
-#pragma unroll
-  for (int c = 0; c < 6; c++) {
-    const float s = wave_sum(tw[c]);
-    if (lane_id() == 0) red[w][c] = s;
-  }
-  const float ls = wave_sum(lsum);
-  if (lane_id() == 0) red[w][6] = ls;
-  __syncthreads();
-  if (threadIdx.x < 7) {
-    float s = 0.f;
-#pragma unroll
-    for (int ww = 0; ww < NW; ww++) s += red[ww][threadIdx.x];
-    ws.twist_part[8 * (int64_t)t + threadIdx.x] = s;
-  }
-}
-
-// Backward to the twist alone (tracking): like the forward, a pass is a long
-// stretch of the list (no per-entry state is kept: the twist is summed in
-// registers) and its steps alternate between two register sets.  Staged
-// entries hold the step's operands only, the list's last entry first:
-//   e0 (mx, my, qa, 2 qb), e1 (qc, o, z, k = 2 r^2 / z), e2 (c, fx / z),
-//   e3 (u, v) = (px, py) / z
-// and with t = J^T w = (fx/z w0, fy/z w1, -(u t0 + v t1)), h = dL/dq:
-//   dL/dp = (-a0 m, -a1 m, 2 a2 + k (a0 t0 + a1 t1 + 2 a2 n) + wgt g_D),
-//   n = u t0 + v t1, a = h (t0, t1, n), m = k n + 2,
-//   p x dL/dp = z ((u, v, 1) x dL/dp).
-// A step whose alpha falls under alpha_min goes through as a contributor of
-// alpha 0, which leaves T and the difference recurrence where they were.
-// Measured against the slots kernel's form without slots (five 16-byte reads
-// and ~94 VALU instructions a step, now 56 bytes and 84, in 256-entry passes):
-// 640x480 tracking frame 55 -> 47 us, 160x120 42 -> 27; bound by VALU issue
-// (55 %) and the waits of three waves per SIMD.
-template <int TILE, int BATCH, bool kTrack>
-__global__ __attribute__((amdgpu_waves_per_eu(TILE == 16 ? 3 : 2))) __launch_bounds__(
-    Shape<TILE>::NT) void k_bwd_twist(Ws ws, const float *g_rgb, const float *g_depth,
-                                      const float *g_sil, TrackArgs tr) {
-  constexpr int NT = Shape<TILE>::NT, PPT = Shape<TILE>::PPT;
-  constexpr int NW = NT / kWave;
-  constexpr int PER = (BATCH + NT - 1) / NT;
-  constexpr int NCB = BATCH / kWave, G = PPT > 1 ? 1 : NCB;  // chunks of a pass's stream
-  constexpr int NH = 2 * G, NR = NW * PPT, SE = BATCH + 32;
-  __shared__ float4 e0s[SE], e1s[SE], e2s[SE];
-  __shared__ float2 e3s[SE];
-  __shared__ uint32_t words[NH + 1][NR][kWave];  // the last row zero
-  __shared__ int maxlast_s;
-  __shared__ float red_s[NW][7];
-
-  const int t = tile_of_block(ws);
-  const DevView &vw = ws.views[find_view_by_tile(ws, t)];
-  const int lt = t - vw.tile_base;
-  const int ox = (lt % vw.tiles_x) * TILE, oy = (lt / vw.tiles_x) * TILE;
-  const uint2 rg = ws.ranges[t];
-  const int start = (int)rg.x;
-  const int w = threadIdx.x / kWave;
-  BwdPixels<PPT> S;
-  if (threadIdx.x == 0) maxlast_s = 0;
-  load_pixels<TILE, kTrack>(ws, vw, ox, oy, g_rgb, g_depth, g_sil, tr, S);
-#pragma unroll
-  for (int k = 0; k < PPT; k++) words[NH][w * PPT + k][lane_id()] = 0u;
-  const int wlast = __builtin_amdgcn_readfirstlane(wave_max_i((int)S.mylast));
-  __syncthreads();
-  if (lane_id() == 0) atomicMax(&maxlast_s, wlast);
-  __syncthreads();
-  const int len = maxlast_s;
-
-  float tw[6] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f};  // (tw[0], tw[1], tw[4] negated)
-  const float amin = ws.amin, amax = ws.amax;
-  const float vfx = vw.fx, vfy = vw.fy, fyx = vw.fy / vw.fx;
-
-  // the pass below is gathered while the current one is replayed, its ids one
-  // pass ahead (positions clamped to the list, extra loads unused)
-  float4 r0[PER], r1[PER], r2[PER], rb[PER];
-  uint32_t pid[PER];
-  const int n_rec = vw.n_rec, rec_base = vw.rec_base;
-  auto fetch_ids = [&](int top) {
-#pragma unroll
-    for (int k = 0; k < PER; k++)
-      pid[k] = ws.ids[start + min(max(kWave * top - 1 - (int)threadIdx.x - k * NT, 0), len - 1)];
-  };
-  auto fetch_records = [&]() {
-#pragma unroll
-    for (int k = 0; k < PER; k++) {
-      const int64_t rec = (int64_t)rec_base + (pid[k] < (uint32_t)n_rec ? pid[k] : 0u);
-      const float4 *A = ws.recA + 3 * rec;
-      r0[k] = A[0]; r1[k] = A[1]; r2[k] = A[2];
-      rb[k] = ws.recB[rec];
-    }
-  };
-  const int nchunk = (len + kWave - 1) / kWave;
-  if (len > 0) {
-    fetch_ids(nchunk);
-    fetch_records();
-    fetch_ids(nchunk - NCB);
-  }
-  for (int top = nchunk; top > 0; top -= NCB) {
-    // the pass's lane bits, all loads issued at once (a chunk past the wave's
-    // last contributor may hold anything: nothing below cuts it away)
-    unsigned long long lb[G][PPT];
-    auto fetch_bits = [&](int g0) {
-#pragma unroll
-      for (int j = 0; j < G; j++) {
-        const unsigned long long *src =
-            ws.lane_bits + chunk_word(start, 0, max(top - 1 - g0 - j, 0), t, w, NW, PPT);
-#pragma unroll
-        for (int k = 0; k < PPT; k++) lb[j][k] = src[k * kWave + lane_id()];
-      }
-    };
-    fetch_bits(0);
-    __syncthreads();
-#pragma unroll
-    for (int k = 0; k < PER; k++) {
-      const int i = threadIdx.x + k * NT;
-      if (BATCH % NT != 0 && i >= BATCH) continue;
-      const float iz = 1.0f / r1[k].z;
-      e0s[i] = make_float4(r0[k].x, r0[k].y, r0[k].z, 2.0f * r0[k].w);
-      e1s[i] = make_float4(r1[k].x, r1[k].y, r1[k].z, 2.0f * r2[k].w * r2[k].w * iz);
-      e2s[i] = make_float4(r2[k].x, r2[k].y, r2[k].z, vfx * iz);
-      e3s[i] = make_float2(rb[k].x * iz, rb[k].y * iz);
-    }
-    __syncthreads();
-    fetch_records();
-    fetch_ids(top - 2 * NCB);
-    for (int g0 = 0; g0 < min(top, NCB); g0 += G) {
-      if (g0 > 0) fetch_bits(g0);
-      // 1. the entries that reached each of this lane's pixels in the forward,
-      // cut at the pixel's last contributor; the words go in bit-reversed,
-      // top half first, so the lowest set bit is the next entry to the front
-      uint32_t nz[PPT];
-#pragma unroll
-      for (int k = 0; k < PPT; k++) nz[k] = 0u;
-#pragma unroll
-      for (int j = 0; j < G; j++) {
-        const int c = top - 1 - g0 - j;
-#pragma unroll
-        for (int k = 0; k < PPT; k++) {
-          const int lim = c < 0 ? 0 : (int)S.last[k] - c * kWave;
-          const unsigned long long below =
-              lim >= kWave ? ~0ull : (lim <= 0 ? 0ull : (1ull << lim) - 1ull);
-          const unsigned long long own = lb[j][k] & below;
-          const uint32_t hi = __builtin_bitreverse32((uint32_t)(own >> 32));
-          const uint32_t lo = __builtin_bitreverse32((uint32_t)own);
-          words[2 * j][w * PPT + k][lane_id()] = hi;
-          words[2 * j + 1][w * PPT + k][lane_id()] = lo;
-          nz[k] |= (hi ? 1u << (2 * j) : 0u) | (lo ? 2u << (2 * j) : 0u);
-        }
-      }
-      // 2. each lane replays its own entries of the pass, last to first, one
-      // step per entry; the wave runs until its last lane is through
-#pragma unroll
-      for (int k = 0; k < PPT; k++) {
-        const int row = w * PPT + k;
-        auto first = [](uint32_t v) { return __builtin_ctz(v | (1u << NH)); };
-        uint32_t left = nz[k];
-        int h = first(left);
-        left &= left - 1u;
-        int hn = first(left);
-        uint32_t cur = words[h][row][lane_id()], nxt = words[hn][row][lane_id()];
-        struct Entry {
-          float4 e0, e1, e2;
-          float2 e3;
-        };
-        auto fetch = [&](Entry &N) {
-          const int i = g0 * kWave + (h << 5) + low_bit(cur);
-          N.e0 = e0s[i]; N.e1 = e1s[i]; N.e2 = e2s[i]; N.e3 = e3s[i];
-        };
-        auto step = [&](const Entry &A, Entry &N) {
-          cur &= cur - 1u;
-          const bool z = cur == 0u;
-          cur = z ? nxt : cur;
-          h = z ? hn : h;
-          left = z ? left & (left - 1u) : left;
-          hn = first(left);
-          nxt = words[hn][row][lane_id()];
-          fetch(N);
-          const float dx = S.px[k] - A.e0.x, dy = S.py[k] - A.e0.y;
-          // q in the forward's order of operations
-          const float ax = A.e0.z * dx, bx = A.e0.w * dx, cy = A.e1.x * dy;
-          const float q = fmaf(cy, dy, fmaf(bx, dy, ax * dx));
-          const float oG = A.e1.y * __builtin_amdgcn_exp2f(q * kNegHalfLog2e);
-          float a = fminf(amax, oG);
-          const bool ok = a >= amin;
-          a = ok ? a : 0.f;
-          const float om = 1.0f - a;
-          const float Tk = S.T[k] * __builtin_amdgcn_rcpf(om);
-          S.T[k] = Tk;
-          const float wgt = a * Tk;
-          // g . (x - B) for this Gaussian, x = (colour, depth, 1)
-          const float back = kTrack ? S.E[k] : S.GS1[k] + S.E[k];
-          const float gdi =
-              fmaf(S.gC0[k], A.e2.x - S.XP0[k],
-                   fmaf(S.gC1[k], A.e2.y - S.XP1[k],
-                        fmaf(S.gC2[k], A.e2.z - S.XP2[k], fmaf(S.gD[k], A.e1.z - S.XPZ[k], back))));
-          S.E[k] = om * gdi;
-          S.XP0[k] = A.e2.x; S.XP1[k] = A.e2.y; S.XP2[k] = A.e2.z; S.XPZ[k] = A.e1.z;
-          if (!kTrack) S.GS1[k] = 0.f;
-          const float hq = (ok && oG <= amax ? oG : 0.f) * -0.5f * (gdi * Tk);
-          const float hy = A.e0.w * dy;
-          const float w0 = fmaf(0.5f, hy, ax), w1 = fmaf(0.5f, bx, cy);
-          const float t0 = A.e2.w * w0, t1 = A.e2.w * (fyx * w1);
-          const float nn = fmaf(A.e3.x, t0, A.e3.y * t1);
-          const float a0 = hq * t0, a1 = hq * t1, a2 = hq * nn, d2 = a2 + a2;
-          const float mm = fmaf(A.e1.w, nn, 2.0f);
-          const float g0n = a0 * mm, g1n = a1 * mm;  // -dL/dp_x, -dL/dp_y
-          const float g2 =
-              fmaf(wgt, S.gD[k], fmaf(A.e1.w, fmaf(d2, nn, fmaf(a1, t1, a0 * t0)), d2));
-          tw[0] += g0n;
-          tw[1] += g1n;
-          tw[2] += g2;
-          tw[3] = fmaf(A.e1.z, fmaf(A.e3.y, g2, g1n), tw[3]);
-          tw[4] = fmaf(A.e1.z, fmaf(A.e3.x, g2, g0n), tw[4]);
-          tw[5] = fmaf(A.e1.z, fmaf(A.e3.y, g0n, -A.e3.x * g1n), tw[5]);
-        };
-        Entry A, B;
-        fetch(A);
-        while (true) {  // (uniform; the lanes with an entry left step)
-          unsigned long long live = lanes(cur != 0u);
-          if (live == 0ull) break;
-          if (in_lanes(live)) step(A, B);
-          live = lanes(cur != 0u);
-          if (live == 0ull) break;
-          if (in_lanes(live)) step(B, A);
-        }
-      }
-    }
-  }
-  tw[0] = -tw[0];
-  tw[1] = -tw[1];
-  tw[4] = -tw[4];
-  store_twist<NW>(ws, t, tw, S.lsum, red_s);
-}
-
-// Backward to the slots (MODE bit 1), with the twist (bit 0) and geometry
-// (bit 2) where asked.  Three waves per SIMD (the LDS allows three blocks per
-// CU), two with geometry.
-template <int TILE, int BATCH, int MODE>
-__global__ __launch_bounds__(Shape<TILE>::NT, (MODE & 4) ? 2 : 3) void k_bwd(Ws ws, const float *g_rgb,
-                                                         const float *g_depth,
-                                                         const float *g_sil) {
-  constexpr int NT = Shape<TILE>::NT, PPT = Shape<TILE>::PPT;
-  constexpr int NW = NT / kWave;
-  constexpr int PER = (BATCH + NT - 1) / NT;
-  static_assert((MODE & 2) != 0, "the twist alone has its own kernel");
-  constexpr bool kTwist = (MODE & 1) != 0;
-  constexpr bool kGeo = (MODE & 4) != 0;  // slots also carry dL/dp
-  constexpr int NA = kGeo ? 8 : 5;        // floats per slot
-  constexpr int G = Group<TILE, BATCH>::G, NS = Group<TILE, BATCH>::NS, NR = NW * PPT;
-  // staged entry: e0 (mx, my, qa, 2 qb), e1 (qc, o, z, qb), e2 (c, r)
-  __shared__ float4 e0s[BATCH], e1s[BATCH], e2s[BATCH];
-  __shared__ float4 ejs[BATCH];   // (fx/z, fy/z, -fx px/z^2, -fy py/z^2)
-  __shared__ float4 eps_[BATCH];  // (px, py, 2 r^2 / z, learnable)
-  __shared__ uint32_t slot_s[BATCH];
-  // per-wave slot accumulators: floats 0-3 in accA, 4 (4-7 with geometry)
-  // in accB, and the claim tags of their read-modify-write
-  __shared__ f32x4 accA[NW][BATCH];
-  __shared__ AccB<kGeo> accB[NW][BATCH];
-  __shared__ uint8_t tag_s[NW][BATCH + kWave];  // + a tag per lane
-  __shared__ int maxlast_s;
-  __shared__ float red_s[NW][7];
-  __shared__ uint32_t words[NS][NR][kWave];
-
-  const int t = tile_of_block(ws);
-  const DevView &vw = ws.views[find_view_by_tile(ws, t)];
-  const int lt = t - vw.tile_base;
-  const int tx = lt % vw.tiles_x, ty = lt / vw.tiles_x;
-  const int ox = tx * TILE, oy = ty * TILE;
-  const uint2 rg = ws.ranges[t];
-  const int start = (int)rg.x, end = (int)rg.y;
-  const int w = threadIdx.x / kWave;
-
-  BwdPixels<PPT> S;
-  load_pixels<TILE, false>(ws, vw, ox, oy, g_rgb, g_depth, g_sil, TrackArgs{}, S);
-  auto &px = S.px, &py = S.py, &T = S.T, &gC0 = S.gC0, &gC1 = S.gC1, &gC2 = S.gC2, &gD = S.gD;
-  auto &E = S.E, &XP0 = S.XP0, &XP1 = S.XP1, &XP2 = S.XP2, &XPZ = S.XPZ, &GS1 = S.GS1;
-  auto &last = S.last;
-  const uint32_t mylast = S.mylast;
   if (threadIdx.x == 0) maxlast_s = 0;
   __syncthreads();
   atomicMax(&maxlast_s, (int)mylast);
@@ -929,7 +672,7 @@ __global__ __launch_bounds__(Shape<TILE>::NT, (MODE & 4) ? 2 : 3) void k_bwd(Ws 
 #pragma unroll
     for (int k = 0; k < PER; k++) pid[k] = ws.ids[min(lo + (int)threadIdx.x + k * NT, stop - 1)];
 #pragma unroll
-    for (int k = 0; k < PER; k++) fetch_bwd_entry(ws, n_rec, rec_base, pid[k], st[k]);
+    for (int k = 0; k < PER; k++) fetch_bwd_entry<kSlots>(ws, n_rec, rec_base, pid[k], st[k]);
 #pragma unroll
     for (int k = 0; k < PER; k++) pid[k] = ws.ids[bpos(lo - BATCH, k)];
   }
@@ -949,21 +692,23 @@ __global__ __launch_bounds__(Shape<TILE>::NT, (MODE & 4) ? 2 : 3) void k_bwd(Ws 
       e2s[i] = E.e2;
       const float iz = 1.0f / E.e1.z;
       ejs[i] = make_float4(vfx * iz, vfy * iz, -vfx * E.eb.x * iz * iz, -vfy * E.eb.y * iz * iz);
-      const uint32_t sl = entry_slot(ws, E, tx, ty);
+      const uint32_t sl = kSlots ? entry_slot(ws, E, tx, ty) : 0xffffffffu;
       // no slot (only after a capacity overflow): the entry learns nothing
-      const float learn = sl != 0xffffffffu ? E.eb.z : 0.f;
+      const float learn = !kSlots || sl != 0xffffffffu ? E.eb.z : 0.f;
       eps_[i] = make_float4(E.eb.x, E.eb.y, 2.0f * E.e2.w * E.e2.w * iz, learn);
-      slot_s[i] = sl;
+      if (kSlots) {
+        slot_s[i] = sl;
 #pragma unroll
-      for (int ww = 0; ww < NW; ww++) {
-        accA[ww][i] = f32x4{0.f, 0.f, 0.f, 0.f};
-        accB[ww][i] = AccB<kGeo>{};
+        for (int ww = 0; ww < NW; ww++) {
+          accA[ww][i] = f32x4{0.f, 0.f, 0.f, 0.f};
+          accB[ww][i] = AccB<kGeo>{};
+        }
       }
     }
     __syncthreads();
     // the batches below are full ones (below the first: clamped, unused)
 #pragma unroll
-    for (int k = 0; k < PER; k++) fetch_bwd_entry(ws, n_rec, rec_base, pid[k], st[k]);
+    for (int k = 0; k < PER; k++) fetch_bwd_entry<kSlots>(ws, n_rec, rec_base, pid[k], st[k]);
 #pragma unroll
     for (int k = 0; k < PER; k++) pid[k] = ws.ids[bpos(lo - 2 * BATCH, k)];
     // this wave's entries, last to first, below its own last contributor
@@ -1049,9 +794,9 @@ __global__ __launch_bounds__(Shape<TILE>::NT, (MODE & 4) ? 2 : 3) void k_bwd(Ws 
         // the loop is entered, as it is re-entered, with a claim's LDS
         // operations behind the first entry's reads (here one on the lane's
         // own tag, not settled)
-        claim(BATCH + me, 0);
-        while (cur != 0u || pp) {
-          const bool live = cur != 0u;
+        if constexpr (kSlots) claim(AB + me, 0);
+        while (cur != 0u || (kSlots && pp)) {
+          const bool live = !kSlots || cur != 0u;
           const float4 e0 = n0, e1 = n1, e2 = n2, ej = nj, ep = np;
           const int cur_i = i;  // this entry's batch position
           {
@@ -1108,85 +853,107 @@ __global__ __launch_bounds__(Shape<TILE>::NT, (MODE & 4) ? 2 : 3) void k_bwd(Ws 
             tw[4] += pz * g0v - ep.x * g2v;
             tw[5] += ep.x * g1v - ep.y * g0v;
           }
-          // this step's values
-          const bool real = ok && ep.w != 0.f;
-          const float tt = fmaf(t0, t0, fmaf(t1, t1, t2 * t2));
-          const f32x4 nva = {wgt * gC0[k], wgt * gC1[k], wgt * gC2[k], pass ? gau * dLda : 0.f};
-          const float v4 = dLdq * (-2.0f * e2.w * tt);
-          AccB<kGeo> nvb;
-          if constexpr (kGeo) nvb = f32x4{v4, g0v, g1v, g2v};
-          else nvb = v4;
-          // the settle below waits for the previous claim's reads: after
-          // the step's arithmetic (which this empty statement consumes)
-          asm volatile("" ::"v"(nva[0]), "v"(nva[1]), "v"(nva[2]), "v"(nva[3]), "v"(v4) : "memory");
-          // settle the previous step's claim: the lane whose number stayed
-          // in the tag writes its sum back; then the lanes that lost add
-          // theirs with LDS atomics (after that write, in the LDS's order)
-          const bool won = pp && rt == me;
-          if (won) {
-            *(f32x4 LDS_AS *)&accA[w][pidx] = ra + pva;
-            *(AccB<kGeo> LDS_AS *)&accB[w][pidx] = rb + pvb;
-          }
-          kLdsOrder();
-          if (pp && !won) {
-            float *fa = (float *)&accA[w][pidx];
-            float *fb = (float *)&accB[w][pidx];
-            atomicAdd(fa + 0, pva[0]);
-            atomicAdd(fa + 1, pva[1]);
-            atomicAdd(fa + 2, pva[2]);
-            atomicAdd(fa + 3, pva[3]);
-            if constexpr (kGeo) {
-#pragma unroll
-              for (int c = 0; c < 4; c++) atomicAdd(fb + c, pvb[c]);
-            } else {
-              atomicAdd(fb, pvb);
+          if constexpr (kSlots) {
+            // this step's values
+            const bool real = ok && ep.w != 0.f;
+            const float tt = fmaf(t0, t0, fmaf(t1, t1, t2 * t2));
+            const f32x4 nva = {wgt * gC0[k], wgt * gC1[k], wgt * gC2[k], pass ? gau * dLda : 0.f};
+            const float v4 = dLdq * (-2.0f * e2.w * tt);
+            AccB<kGeo> nvb;
+            if constexpr (kGeo) nvb = f32x4{v4, g0v, g1v, g2v};
+            else nvb = v4;
+            // the settle below waits for the previous claim's reads: after
+            // the step's arithmetic (which this empty statement consumes)
+            asm volatile("" ::"v"(nva[0]), "v"(nva[1]), "v"(nva[2]), "v"(nva[3]), "v"(v4) : "memory");
+            // settle the previous step's claim: the lane whose number stayed
+            // in the tag writes its sum back; then the lanes that lost add
+            // theirs with LDS atomics (after that write, in the LDS's order)
+            const bool won = pp && rt == me;
+            if (won) {
+              *(f32x4 LDS_AS *)&accA[w][pidx] = ra + pva;
+              *(AccB<kGeo> LDS_AS *)&accB[w][pidx] = rb + pvb;
             }
+            kLdsOrder();
+            if (pp && !won) {
+              float *fa = (float *)&accA[w][pidx];
+              float *fb = (float *)&accB[w][pidx];
+              atomicAdd(fa + 0, pva[0]);
+              atomicAdd(fa + 1, pva[1]);
+              atomicAdd(fa + 2, pva[2]);
+              atomicAdd(fa + 3, pva[3]);
+              if constexpr (kGeo) {
+#pragma unroll
+                for (int c = 0; c < 4; c++) atomicAdd(fb + c, pvb[c]);
+              } else {
+                atomicAdd(fb, pvb);
+              }
+            }
+            kLdsOrder();
+            // this step's claim; every lane makes one (a lane with nothing to
+            // add on its own tag), so that the LDS operations behind the next
+            // entry's reads are the same on every path and the next step
+            // waits for those reads only
+            pp = ok && ep.w != 0.f;
+            pva = nva;
+            pvb = nvb;
+            pidx = cur_i;
+            claim(pp ? cur_i : AB + me, cur_i);
           }
-          kLdsOrder();
-          // this step's claim; every lane makes one (a lane with nothing to
-          // add on its own tag), so that the LDS operations behind the next
-          // entry's reads are the same on every path and the next step
-          // waits for those reads only
-          pp = ok && ep.w != 0.f;
-          pva = nva;
-          pvb = nvb;
-          pidx = cur_i;
-          claim(pp ? cur_i : BATCH + me, cur_i);
         }
       }
     }
-    __syncthreads();
-    for (int i = threadIdx.x; i < nb; i += NT) {
-      if (eps_[i].w == 0.f) continue;
-      float *o = ws.slots + NA * (int64_t)slot_s[i];
-      f32x4 sa = accA[0][i];
-      AccB<kGeo> sb = accB[0][i];
+    if (kSlots) {
+      __syncthreads();
+      for (int i = threadIdx.x; i < nb; i += NT) {
+        if (eps_[i].w == 0.f) continue;
+        float *o = ws.slots + NA * (int64_t)slot_s[i];
+        f32x4 sa = accA[0][i];
+        AccB<kGeo> sb = accB[0][i];
 #pragma unroll
-      for (int ww = 1; ww < NW; ww++) {
-        sa = sa + accA[ww][i];
-        sb = sb + accB[ww][i];
-      }
+        for (int ww = 1; ww < NW; ww++) {
+          sa = sa + accA[ww][i];
+          sb = sb + accB[ww][i];
+        }
 #pragma unroll
-      for (int c = 0; c < 4; c++) o[c] = sa[c];
-      if constexpr (kGeo) {
+        for (int c = 0; c < 4; c++) o[c] = sa[c];
+        if constexpr (kGeo) {
 #pragma unroll
-        for (int c = 0; c < 4; c++) o[4 + c] = sb[c];
-      } else {
-        o[4] = sb;
+          for (int c = 0; c < 4; c++) o[4 + c] = sb[c];
+        } else {
+          o[4] = sb;
+        }
       }
     }
   }
-  // list entries past every pixel's last contributor: zero slots
-  for (int i = stop + (int)threadIdx.x; i < end; i += NT) {
-    BwdEntry E;
-    fetch_bwd_entry(ws, n_rec, rec_base, ws.ids[i], E);
-    const uint32_t sl = entry_slot(ws, E, tx, ty);
-    if (sl == 0xffffffffu) continue;
-    float *o = ws.slots + NA * (int64_t)sl;
+  if (kSlots) {
+    // list entries past every pixel's last contributor: zero slots
+    for (int i = stop + (int)threadIdx.x; i < end; i += NT) {
+      BwdEntry E;
+      fetch_bwd_entry<true>(ws, n_rec, rec_base, ws.ids[i], E);
+      const uint32_t sl = entry_slot(ws, E, tx, ty);
+      if (sl == 0xffffffffu) continue;
+      float *o = ws.slots + NA * (int64_t)sl;
 #pragma unroll
-    for (int c = 0; c < NA; c++) o[c] = 0.f;
+      for (int c = 0; c < NA; c++) o[c] = 0.f;
+    }
   }
-  if (kTwist) store_twist<NW>(ws, t, tw, 0.f, red_s);
+  if (kTwist) {
+    // per tile: the six twist sums and (tracking) the Eq. 1 loss
+#pragma unroll
+    for (int c = 0; c < 6; c++) {
+      const float s = wave_sum(tw[c]);
+      if (lane_id() == 0) red_s[w][c] = s;
+    }
+    const float ls = wave_sum(lsum);
+    if (lane_id() == 0) red_s[w][6] = ls;
+    __syncthreads();
+    if (threadIdx.x < 7) {
+      float s = 0.f;
+#pragma unroll
+      for (int ww = 0; ww < NW; ww++) s += red_s[ww][threadIdx.x];
+      ws.twist_part[8 * (int64_t)t + threadIdx.x] = s;
+    }
+  }
 }
 
 template <int TILE, int BATCH>
@@ -1198,28 +965,15 @@ hipError_t fwd_launch(const Ws &ws, float *rgb, float *depth, float *sil, hipStr
 
 template <int TILE, int BATCH>
 hipError_t bwd_launch(const Ws &ws, const float *g_rgb, const float *g_depth, const float *g_sil,
-                      int mode, hipStream_t st) {
+                      int mode, hipStream_t st, TrackArgs tr) {
   const dim3 g(ws.n_tiles), b(Shape<TILE>::NT);
   switch (mode) {
-    case 2: hipLaunchKernelGGL((k_bwd<TILE, BATCH, 2>), g, b, 0, st, ws, g_rgb, g_depth, g_sil); break;
-    case 3: hipLaunchKernelGGL((k_bwd<TILE, BATCH, 3>), g, b, 0, st, ws, g_rgb, g_depth, g_sil); break;
-    case 6: hipLaunchKernelGGL((k_bwd<TILE, BATCH, 6>), g, b, 0, st, ws, g_rgb, g_depth, g_sil); break;
-    case 7: hipLaunchKernelGGL((k_bwd<TILE, BATCH, 7>), g, b, 0, st, ws, g_rgb, g_depth, g_sil); break;
+    case 1: hipLaunchKernelGGL((k_bwd<TILE, BATCH, 1>), g, b, 0, st, ws, g_rgb, g_depth, g_sil, tr); break;
+    case 2: hipLaunchKernelGGL((k_bwd<TILE, BATCH, 2>), g, b, 0, st, ws, g_rgb, g_depth, g_sil, tr); break;
+    case 3: hipLaunchKernelGGL((k_bwd<TILE, BATCH, 3>), g, b, 0, st, ws, g_rgb, g_depth, g_sil, tr); break;
+    case 6: hipLaunchKernelGGL((k_bwd<TILE, BATCH, 6>), g, b, 0, st, ws, g_rgb, g_depth, g_sil, tr); break;
+    case 7: hipLaunchKernelGGL((k_bwd<TILE, BATCH, 7>), g, b, 0, st, ws, g_rgb, g_depth, g_sil, tr); break;
     default: return hipErrorInvalidValue;
-  }
-  return hipGetLastError();
-}
-
-template <int TILE, int BATCH>
-hipError_t twist_launch(const Ws &ws, const float *g_rgb, const float *g_depth, const float *g_sil,
-                        hipStream_t st, const vtgs_track_cfg *track) {
-  const dim3 g(ws.n_tiles), b(Shape<TILE>::NT);
-  if (track) {
-    const TrackArgs tr{track->alpha, track->beta, track->sil_thr};
-    hipLaunchKernelGGL((k_bwd_twist<TILE, BATCH, true>), g, b, 0, st, ws, nullptr, nullptr, nullptr, tr);
-  } else {
-    hipLaunchKernelGGL((k_bwd_twist<TILE, BATCH, false>), g, b, 0, st, ws, g_rgb, g_depth, g_sil,
-                       TrackArgs{});
   }
   return hipGetLastError();
 }
@@ -1243,23 +997,11 @@ hipError_t fwd_tile(const Ws &ws, float *rgb, float *depth, float *sil, hipStrea
 
 template <int TILE>
 hipError_t bwd_tile(const Ws &ws, const float *a, const float *b, const float *c, int mode,
-                    hipStream_t st, const vtgs_track_cfg *track) {
-  if (mode == 1) {
-    switch (ws.batch) {
-      case 128: return twist_launch<TILE, 128>(ws, a, b, c, st, track);
-      // the forward's rule: 512 entries a pass at three blocks per CU (1,200
-      // tiles 47.4 us, 80 tiles 26.8, a batch of served tracks 940) against
-      // 256 at five (50.5, 36.2 and 1000); 384 at four lies beside it (46.8,
-      // 28.6, 940)
-      case 256: return twist_launch<TILE, TILE == 16 ? 512 : 256>(ws, a, b, c, st, track);
-      case 512: return twist_launch<TILE, 512>(ws, a, b, c, st, track);
-    }
-    return hipErrorInvalidValue;
-  }
+                    hipStream_t st, TrackArgs tr) {
   switch (ws.batch) {
-    case 128: return bwd_launch<TILE, 128>(ws, a, b, c, mode, st);
-    case 256: return bwd_launch<TILE, 256>(ws, a, b, c, mode, st);
-    case 512: return bwd_launch<TILE, 512>(ws, a, b, c, mode, st);
+    case 128: return bwd_launch<TILE, 128>(ws, a, b, c, mode, st, tr);
+    case 256: return bwd_launch<TILE, 256>(ws, a, b, c, mode, st, tr);
+    case 512: return bwd_launch<TILE, 512>(ws, a, b, c, mode, st, tr);
   }
   return hipErrorInvalidValue;
 }
@@ -1281,12 +1023,16 @@ hipError_t launch_composite_bwd(const Ws &ws, const float *g_rgb, const float *g
                                 const float *g_sil, int mode, hipStream_t st,
                                 const vtgs_track_cfg *track) {
   if (ws.n_tiles == 0) return hipSuccess;
+  TrackArgs tr{0.f, 0.f, 0.f, 0};
   if (((mode & 4) != 0) != (ws.slot_w == 8) && (mode & 2)) return hipErrorInvalidValue;
-  if (track && mode != 1) return hipErrorInvalidValue;
+  if (track) {
+    if (mode != 1) return hipErrorInvalidValue;
+    tr = TrackArgs{track->alpha, track->beta, track->sil_thr, 1};
+  }
   switch (ws.tile) {
-    case 8: return bwd_tile<8>(ws, g_rgb, g_depth, g_sil, mode, st, track);
-    case 16: return bwd_tile<16>(ws, g_rgb, g_depth, g_sil, mode, st, track);
-    case 32: return bwd_tile<32>(ws, g_rgb, g_depth, g_sil, mode, st, track);
+    case 8: return bwd_tile<8>(ws, g_rgb, g_depth, g_sil, mode, st, tr);
+    case 16: return bwd_tile<16>(ws, g_rgb, g_depth, g_sil, mode, st, tr);
+    case 32: return bwd_tile<32>(ws, g_rgb, g_depth, g_sil, mode, st, tr);
   }
   return hipErrorInvalidValue;
 }
