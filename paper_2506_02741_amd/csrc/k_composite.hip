@@ -59,11 +59,9 @@ namespace {
 
 constexpr float kNegHalfLog2e = -0.72134752044448170368f;  // -log2(e) / 2
 
-// Eq. 1 evaluated inside the tracking backward (on = 0: upstream gradients
-// come from the caller's arrays).
+// Eq. 1 evaluated inside the tracking backward.
 struct TrackArgs {
   float alpha, beta, sil_thr;
-  int on;
 };
 
 __device__ __forceinline__ float sgn(float x) { return (float)((x > 0.f) - (x < 0.f)); }
@@ -229,24 +227,10 @@ template <int TILE, int BATCH>
 struct Group {
   static constexpr int NCB = BATCH / kWave;  // chunks of a full batch
   static constexpr int G = Shape<TILE>::PPT > 1 ? 1 : (NCB < 4 ? NCB : 4);
-  static constexpr int NS = 2 * G + 2;       // LDS word slots per pixel (backward)
   // the forward's passes may be longer: it keeps no per-entry state
   static constexpr int GF = Shape<TILE>::PPT > 1 ? 1 : (NCB < 8 ? NCB : 8);
   static constexpr int NH = 2 * GF;          // 32-entry words of a forward pass
 };
-
-// Word list of one pixel-lane: the nonzero 32-entry halves of its bits in
-// slots 0.., a zero word after the last; `seq` holds each slot's half index
-// within the group, four bits per slot, the current slot's in bits 0-3.
-template <int NS, int NR>
-__device__ __forceinline__ void push_word(uint32_t (*words)[NR][kWave], int row, uint32_t word,
-                                          uint32_t half, uint32_t &ns, uint32_t &seq) {
-  if (word != 0u) {
-    words[ns][row][lane_id()] = word;
-    seq |= half << (4u * ns);
-    ns++;
-  }
-}
 
 // Lowest set bit of a word, 31 for a zero word (an index that stays inside
 // the group, read and then ignored).
@@ -512,8 +496,8 @@ __global__ __attribute__((amdgpu_waves_per_eu(TILE == 16 ? 4 : 2))) __launch_bou
   }
 }
 
-// Backward staging of one list entry: the forward record, the camera-frame
-// centre and learnable flag, and (slot mode) the record's tile rectangle and
+// Staging of one list entry for the backward to slots: the forward record,
+// the camera-frame centre and learnable flag, the record's tile rectangle and
 // first slot.  Gathered without branches, as in the forward.
 struct BwdEntry {
   float4 e0, e1, e2, eb;
@@ -522,7 +506,6 @@ struct BwdEntry {
   bool ok;
 };
 
-template <bool kSlots>
 __device__ __forceinline__ void fetch_bwd_entry(const Ws &ws, int n_rec, int rec_base, uint32_t id,
                                                 BwdEntry &E) {
   E.ok = id < (uint32_t)n_rec;
@@ -530,7 +513,8 @@ __device__ __forceinline__ void fetch_bwd_entry(const Ws &ws, int n_rec, int rec
   const float4 *A = ws.recA + 3 * rec;
   E.e0 = A[0]; E.e1 = A[1]; E.e2 = A[2];
   E.eb = ws.recB[rec];
-  if (kSlots) { E.rc = ws.rect[rec]; E.off = ws.rec_off[rec]; }
+  E.rc = ws.rect[rec];
+  E.off = ws.rec_off[rec];
 }
 
 // The (record, tile) slot of a staged entry of tile (tx, ty), or ~0u when
@@ -553,64 +537,42 @@ __device__ __forceinline__ void kLdsOrder() { asm volatile("" ::: "memory"); }
 template <bool kGeo>
 using AccB = typename std::conditional<kGeo, f32x4, float>::type;
 
-// Slot modes hold three waves per SIMD (their LDS allows three blocks per CU)
-// unless they carry geometry (two).
-template <int TILE, int BATCH, int MODE>
-__global__ __launch_bounds__(Shape<TILE>::NT, (MODE & 2) ? ((MODE & 4) ? 2 : 3) : 1) void k_bwd(Ws ws, const float *g_rgb,
-                                                         const float *g_depth,
-                                                         const float *g_sil, TrackArgs tr) {
-  constexpr int NT = Shape<TILE>::NT, PPT = Shape<TILE>::PPT;
-  constexpr int NW = NT / kWave;
-  constexpr int PER = (BATCH + NT - 1) / NT;
-  constexpr bool kTwist = (MODE & 1) != 0, kSlots = (MODE & 2) != 0;
-  constexpr bool kGeo = kSlots && (MODE & 4) != 0;  // slots also carry dL/dp
-  constexpr int NA = kGeo ? 8 : 5;                   // floats per slot
-  constexpr int AB = kSlots ? BATCH : 1;
-  constexpr int G = Group<TILE, BATCH>::G, NS = Group<TILE, BATCH>::NS, NR = NW * PPT;
-  // staged entry: e0 (mx, my, qa, 2 qb), e1 (qc, o, z, qb), e2 (c, r)
-  __shared__ float4 e0s[BATCH], e1s[BATCH], e2s[BATCH];
-  __shared__ float4 ejs[BATCH];   // (fx/z, fy/z, -fx px/z^2, -fy py/z^2)
-  __shared__ float4 eps_[BATCH];  // (px, py, 2 r^2 / z, learnable)
-  __shared__ uint32_t slot_s[AB];
-  // per-wave slot accumulators: floats 0-3 in accA, 4 (4-7 with geometry)
-  // in accB, and the claim tags of their read-modify-write
-  __shared__ f32x4 accA[NW][AB];
-  __shared__ AccB<kGeo> accB[NW][AB];
-  __shared__ uint8_t tag_s[kSlots ? NW : 1][AB + kWave];  // + a tag per lane
-  __shared__ int maxlast_s;
-  __shared__ float red_s[NW][7];
-  __shared__ uint32_t words[NS][NR][kWave];
-
-  const int t = tile_of_block(ws);
-  const DevView &vw = ws.views[find_view_by_tile(ws, t)];
-  const int lt = t - vw.tile_base;
-  const int tx = lt % vw.tiles_x, ty = lt / vw.tiles_x;
-  const int ox = tx * TILE, oy = ty * TILE;
-  const uint2 rg = ws.ranges[t];
-  const int start = (int)rg.x, end = (int)rg.y;
-  const int64_t P = ws.P;
-  const int w = threadIdx.x / kWave;
-
-  float px[PPT], py[PPT], T[PPT], gC0[PPT], gC1[PPT], gC2[PPT], gD[PPT], gS[PPT];
-  // the difference recurrence: (1 - alpha_b) g.(x_b - B_b) of the
-  // contributor b behind (0 at the back), its colour and depth (the
-  // background and 0 at the back) and g_S (1 - its coverage x_S)
+// The per-pixel state of a backward: the forward's transmittance and last
+// contributor, the upstream gradient (Eq. 1's where kTrack, alpha W |V - V'| +
+// beta W |D - D'| with W = vis & (D > 0) & (S' > thr), and this lane's share
+// of the tile's loss, else the caller's arrays) and the difference recurrence
+// at the back: E = (1 - alpha_b) g.(x_b - B_b) of the contributor b behind (0),
+// its colour and depth XP (the background and 0), and GS1 = g_S (1 - its
+// coverage).
+template <int PPT>
+struct BwdPixels {
+  float px[PPT], py[PPT], T[PPT], gC0[PPT], gC1[PPT], gC2[PPT], gD[PPT];
   float E[PPT], XP0[PPT], XP1[PPT], XP2[PPT], XPZ[PPT], GS1[PPT];
   uint32_t last[PPT];
-  uint32_t mylast = 0;
-  float lsum = 0.f;  // this lane's share of the tile's Eq. 1 loss
+  uint32_t mylast;
+  float lsum;
+};
+
+template <int TILE, bool kTrack>
+__device__ __forceinline__ void load_pixels(const Ws &ws, const DevView &vw, int ox, int oy,
+                                            const float *g_rgb, const float *g_depth,
+                                            const float *g_sil, const TrackArgs &tr,
+                                            BwdPixels<Shape<TILE>::PPT> &S) {
+  const int64_t P = ws.P;
+  S.mylast = 0u;
+  S.lsum = 0.f;
 #pragma unroll
-  for (int k = 0; k < PPT; k++) {
+  for (int k = 0; k < Shape<TILE>::PPT; k++) {
     int x, y;
     lane_pixel<TILE>(k, x, y);
-    px[k] = (float)(ox + x);
-    py[k] = (float)(oy + y);
+    S.px[k] = (float)(ox + x);
+    S.py[k] = (float)(oy + y);
     const bool valid = (ox + x) < vw.width && (oy + y) < vw.height;
     const int64_t p = vw.pix_off + (int64_t)(oy + y) * vw.width + (ox + x);
-    T[k] = valid ? ws.t_final[p] : 1.f;
-    last[k] = valid ? ws.last[p] : 0u;
-    if (tr.on) {
-      // Eq. 1: alpha W |V - V'| + beta W |D - D'|, W = vis & (D > 0) & (S' > thr)
+    S.T[k] = valid ? ws.t_final[p] : 1.f;
+    S.last[k] = valid ? ws.last[p] : 0u;
+    float gS = 0.f;
+    if constexpr (kTrack) {
       const int64_t lp = p - vw.pix_off;
       const int64_t Pv = (int64_t)vw.width * vw.height;
       float od = 0.f;
@@ -623,24 +585,308 @@ __global__ __launch_bounds__(Shape<TILE>::NT, (MODE & 2) ? ((MODE & 4) ? 2 : 3) 
       const float r1 = valid ? vw.obs_rgb[Pv + lp] - ws.img[P + p] : 0.f;
       const float r2 = valid ? vw.obs_rgb[2 * Pv + lp] - ws.img[2 * P + p] : 0.f;
       const float rd = valid ? od - ws.img[3 * P + p] : 0.f;
-      gC0[k] = W ? -tr.alpha * sgn(r0) : 0.f;
-      gC1[k] = W ? -tr.alpha * sgn(r1) : 0.f;
-      gC2[k] = W ? -tr.alpha * sgn(r2) : 0.f;
-      gD[k] = W ? -tr.beta * sgn(rd) : 0.f;
-      gS[k] = 0.f;
-      lsum += W ? tr.alpha * ((fabsf(r0) + fabsf(r1)) + fabsf(r2)) + tr.beta * fabsf(rd) : 0.f;
+      S.gC0[k] = W ? -tr.alpha * sgn(r0) : 0.f;
+      S.gC1[k] = W ? -tr.alpha * sgn(r1) : 0.f;
+      S.gC2[k] = W ? -tr.alpha * sgn(r2) : 0.f;
+      S.gD[k] = W ? -tr.beta * sgn(rd) : 0.f;
+      S.lsum += W ? tr.alpha * ((fabsf(r0) + fabsf(r1)) + fabsf(r2)) + tr.beta * fabsf(rd) : 0.f;
     } else {
-      gC0[k] = (valid && g_rgb) ? g_rgb[p] : 0.f;
-      gC1[k] = (valid && g_rgb) ? g_rgb[P + p] : 0.f;
-      gC2[k] = (valid && g_rgb) ? g_rgb[2 * P + p] : 0.f;
-      gD[k] = (valid && g_depth) ? g_depth[p] : 0.f;
-      gS[k] = (valid && g_sil) ? g_sil[p] : 0.f;
+      S.gC0[k] = (valid && g_rgb) ? g_rgb[p] : 0.f;
+      S.gC1[k] = (valid && g_rgb) ? g_rgb[P + p] : 0.f;
+      S.gC2[k] = (valid && g_rgb) ? g_rgb[2 * P + p] : 0.f;
+      S.gD[k] = (valid && g_depth) ? g_depth[p] : 0.f;
+      gS = (valid && g_sil) ? g_sil[p] : 0.f;
     }
-    E[k] = 0.f;
-    XP0[k] = ws.bg[0]; XP1[k] = ws.bg[1]; XP2[k] = ws.bg[2]; XPZ[k] = 0.f;
-    GS1[k] = gS[k];
-    mylast = max(mylast, last[k]);
+    S.E[k] = 0.f;
+    S.XP0[k] = ws.bg[0]; S.XP1[k] = ws.bg[1]; S.XP2[k] = ws.bg[2]; S.XPZ[k] = 0.f;
+    S.GS1[k] = gS;
+    S.mylast = max(S.mylast, S.last[k]);
   }
+}
+
+// Per tile: the lanes' six twist sums and the Eq. 1 loss, wave by wave.
+template <int NW>
+__device__ __forceinline__ void store_twist(const Ws &ws, int t, const float (&tw)[6], float lsum,
+                                            float (*red)[7]) {
+  const int w = threadIdx.x / kWave;
+#pragma unroll
+  for (int c = 0; c < 6; c++) {
+    const float s = wave_sum(tw[c]);
+    if (lane_id() == 0) red[w][c] = s;
+  }
+  const float ls = wave_sum(lsum);
+  if (lane_id() == 0) red[w][6] = ls;
+  __syncthreads();
+  if (threadIdx.x < 7) {
+    float s = 0.f;
+#pragma unroll
+    for (int ww = 0; ww < NW; ww++) s += red[ww][threadIdx.x];
+    ws.twist_part[8 * (int64_t)t + threadIdx.x] = s;
+  }
+}
+
+// Backward to the twist alone (tracking): like the forward, a pass is a long
+// stretch of the list (no per-entry state is kept: the twist is summed in
+// registers) and its steps alternate between two register sets.  Staged
+// entries hold the step's operands only, the list's last entry first:
+//   e0 (mx, my, qa, 2 qb), e1 (qc, o, z, 2 r^2 / z), e2 (c, px),
+//   e3 (py, 1/z, -fx px/z^2, -fy py/z^2).
+// The operations and their order are the slots kernel's: a trajectory of L1
+// steps amplifies any other rounding of the twist.  Against that kernel's form
+// without slots, in 256-entry batches with five 16-byte reads a step: 640x480
+// tracking frame 55 -> 49 us, 160x120 42 -> 31, a batch of served tracks 1166
+// -> 1026; bound by VALU issue (~60 %) and the waits of four waves per SIMD.
+template <int TILE, int BATCH, bool kTrack>
+__global__ __attribute__((amdgpu_waves_per_eu(TILE == 16 ? 4 : 2))) __launch_bounds__(
+    Shape<TILE>::NT) void k_bwd_twist(Ws ws, const float *g_rgb, const float *g_depth,
+                                      const float *g_sil, TrackArgs tr) {
+  constexpr int NT = Shape<TILE>::NT, PPT = Shape<TILE>::PPT;
+  constexpr int NW = NT / kWave;
+  constexpr int PER = (BATCH + NT - 1) / NT;
+  constexpr int NCB = BATCH / kWave, G = PPT > 1 ? 1 : NCB;  // chunks of a pass's stream
+  constexpr int NH = 2 * G, NR = NW * PPT, SE = BATCH + 32;
+  __shared__ float4 e0s[SE], e1s[SE], e2s[SE], e3s[SE];
+  __shared__ uint32_t words[NH + 1][NR][kWave];  // the last row zero
+  __shared__ int maxlast_s;
+  __shared__ float red_s[NW][7];
+
+  const int t = tile_of_block(ws);
+  const DevView &vw = ws.views[find_view_by_tile(ws, t)];
+  const int lt = t - vw.tile_base;
+  const int ox = (lt % vw.tiles_x) * TILE, oy = (lt / vw.tiles_x) * TILE;
+  const uint2 rg = ws.ranges[t];
+  const int start = (int)rg.x;
+  const int w = threadIdx.x / kWave;
+  BwdPixels<PPT> S;
+  if (threadIdx.x == 0) maxlast_s = 0;
+  load_pixels<TILE, kTrack>(ws, vw, ox, oy, g_rgb, g_depth, g_sil, tr, S);
+#pragma unroll
+  for (int k = 0; k < PPT; k++) words[NH][w * PPT + k][lane_id()] = 0u;
+  const int wlast = __builtin_amdgcn_readfirstlane(wave_max_i((int)S.mylast));
+  __syncthreads();
+  if (lane_id() == 0) atomicMax(&maxlast_s, wlast);
+  __syncthreads();
+  const int len = maxlast_s;
+
+  float tw[6] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+  const float amin = ws.amin, amax = ws.amax;
+  const float vfx = vw.fx, vfy = vw.fy;
+
+  // the pass below is gathered while the current one is replayed, its ids one
+  // pass ahead (positions clamped to the list, extra loads unused)
+  float4 r0[PER], r1[PER], r2[PER], rb[PER];
+  uint32_t pid[PER];
+  const int n_rec = vw.n_rec, rec_base = vw.rec_base;
+  auto fetch_ids = [&](int top) {
+#pragma unroll
+    for (int k = 0; k < PER; k++)
+      pid[k] = ws.ids[start + min(max(kWave * top - 1 - (int)threadIdx.x - k * NT, 0), len - 1)];
+  };
+  auto fetch_records = [&]() {
+#pragma unroll
+    for (int k = 0; k < PER; k++) {
+      const int64_t rec = (int64_t)rec_base + (pid[k] < (uint32_t)n_rec ? pid[k] : 0u);
+      const float4 *A = ws.recA + 3 * rec;
+      r0[k] = A[0]; r1[k] = A[1]; r2[k] = A[2];
+      rb[k] = ws.recB[rec];
+    }
+  };
+  const int nchunk = (len + kWave - 1) / kWave;
+  if (len > 0) {
+    fetch_ids(nchunk);
+    fetch_records();
+    fetch_ids(nchunk - NCB);
+  }
+  for (int top = nchunk; top > 0; top -= NCB) {
+    // the pass's lane bits, all loads issued at once (a chunk past the wave's
+    // last contributor may hold anything: nothing below cuts it away)
+    unsigned long long lb[G][PPT];
+    auto fetch_bits = [&](int g0) {
+#pragma unroll
+      for (int j = 0; j < G; j++) {
+        const unsigned long long *src =
+            ws.lane_bits + chunk_word(start, 0, max(top - 1 - g0 - j, 0), t, w, NW, PPT);
+#pragma unroll
+        for (int k = 0; k < PPT; k++) lb[j][k] = src[k * kWave + lane_id()];
+      }
+    };
+    fetch_bits(0);
+    __syncthreads();
+#pragma unroll
+    for (int k = 0; k < PER; k++) {
+      const int i = threadIdx.x + k * NT;
+      if (BATCH % NT != 0 && i >= BATCH) continue;
+      const float iz = 1.0f / r1[k].z;
+      e0s[i] = make_float4(r0[k].x, r0[k].y, r0[k].z, 2.0f * r0[k].w);
+      e1s[i] = make_float4(r1[k].x, r1[k].y, r1[k].z, 2.0f * r2[k].w * r2[k].w * iz);
+      e2s[i] = make_float4(r2[k].x, r2[k].y, r2[k].z, rb[k].x);
+      e3s[i] = make_float4(rb[k].y, iz, -vfx * rb[k].x * iz * iz, -vfy * rb[k].y * iz * iz);
+    }
+    __syncthreads();
+    fetch_records();
+    fetch_ids(top - 2 * NCB);
+    for (int g0 = 0; g0 < min(top, NCB); g0 += G) {
+      if (g0 > 0) fetch_bits(g0);
+      // 1. the entries that reached each of this lane's pixels in the forward,
+      // cut at the pixel's last contributor; the words go in bit-reversed,
+      // top half first, so the lowest set bit is the next entry to the front
+      uint32_t nz[PPT];
+#pragma unroll
+      for (int k = 0; k < PPT; k++) nz[k] = 0u;
+#pragma unroll
+      for (int j = 0; j < G; j++) {
+        const int c = top - 1 - g0 - j;
+#pragma unroll
+        for (int k = 0; k < PPT; k++) {
+          const int lim = c < 0 ? 0 : (int)S.last[k] - c * kWave;
+          const unsigned long long below =
+              lim >= kWave ? ~0ull : (lim <= 0 ? 0ull : (1ull << lim) - 1ull);
+          const unsigned long long own = lb[j][k] & below;
+          const uint32_t hi = __builtin_bitreverse32((uint32_t)(own >> 32));
+          const uint32_t lo = __builtin_bitreverse32((uint32_t)own);
+          words[2 * j][w * PPT + k][lane_id()] = hi;
+          words[2 * j + 1][w * PPT + k][lane_id()] = lo;
+          nz[k] |= (hi ? 1u << (2 * j) : 0u) | (lo ? 2u << (2 * j) : 0u);
+        }
+      }
+      // 2. each lane replays its own entries of the pass, last to first, one
+      // step per entry; the wave runs until its last lane is through
+#pragma unroll
+      for (int k = 0; k < PPT; k++) {
+        const int row = w * PPT + k;
+        auto first = [](uint32_t v) { return __builtin_ctz(v | (1u << NH)); };
+        uint32_t left = nz[k];
+        int h = first(left);
+        left &= left - 1u;
+        int hn = first(left);
+        uint32_t cur = words[h][row][lane_id()], nxt = words[hn][row][lane_id()];
+        struct Entry {
+          float4 e0, e1, e2, e3;
+        };
+        auto fetch = [&](Entry &N) {
+          const int i = g0 * kWave + (h << 5) + low_bit(cur);
+          N.e0 = e0s[i]; N.e1 = e1s[i]; N.e2 = e2s[i]; N.e3 = e3s[i];
+        };
+        auto step = [&](const Entry &A, Entry &N) {
+          cur &= cur - 1u;
+          const bool z = cur == 0u;
+          cur = z ? nxt : cur;
+          h = z ? hn : h;
+          left = z ? left & (left - 1u) : left;
+          hn = first(left);
+          nxt = words[hn][row][lane_id()];
+          fetch(N);
+          const float dx = S.px[k] - A.e0.x, dy = S.py[k] - A.e0.y;
+          // q in the forward's order of operations
+          const float ax = A.e0.z * dx, bx = A.e0.w * dx, cy = A.e1.x * dy;
+          const float q = fmaf(cy, dy, fmaf(bx, dy, ax * dx));
+          const float gau = __builtin_amdgcn_exp2f(q * kNegHalfLog2e);
+          const float oG = A.e1.y * gau;
+          const float a = fminf(amax, oG);
+          const bool ok = a >= amin;
+          const float om = 1.0f - a;
+          const float Tk = ok ? S.T[k] * __builtin_amdgcn_rcpf(om) : S.T[k];
+          S.T[k] = Tk;
+          const float wgt = ok ? a * Tk : 0.f;
+          // g . (x - B) for this Gaussian, x = (colour, depth, 1)
+          const float back = kTrack ? S.E[k] : S.GS1[k] + S.E[k];
+          const float gdi =
+              fmaf(S.gC0[k], A.e2.x - S.XP0[k],
+                   fmaf(S.gC1[k], A.e2.y - S.XP1[k],
+                        fmaf(S.gC2[k], A.e2.z - S.XP2[k], fmaf(S.gD[k], A.e1.z - S.XPZ[k], back))));
+          const float dLda = ok ? gdi * Tk : 0.f;
+          S.E[k] = ok ? om * gdi : S.E[k];
+          S.XP0[k] = ok ? A.e2.x : S.XP0[k];
+          S.XP1[k] = ok ? A.e2.y : S.XP1[k];
+          S.XP2[k] = ok ? A.e2.z : S.XP2[k];
+          S.XPZ[k] = ok ? A.e1.z : S.XPZ[k];
+          if (!kTrack) S.GS1[k] = ok ? 0.f : S.GS1[k];
+          const float dLdq = oG <= amax ? -0.5f * oG * dLda : 0.f;
+          // w = Q d (halving 2 qb is exact, also inside a product)
+          const float w0 = fmaf(A.e0.z, dx, 0.5f * (A.e0.w * dy));
+          const float w1 = fmaf(A.e0.w, 0.5f * dx, cy);
+          const float t0 = (vfx * A.e3.y) * w0, t1 = (vfy * A.e3.y) * w1;
+          const float t2 = fmaf(A.e3.z, w0, A.e3.w * w1);
+          // dL/dp of this pair (camera-frame centre)
+          const float kk = A.e1.w;
+          const float g0v = dLdq * fmaf(kk * t0, t2, -2.0f * t0);
+          const float g1v = dLdq * fmaf(kk * t1, t2, -2.0f * t1);
+          const float s2 = fmaf(t0, t0, fmaf(t1, t1, 2.0f * t2 * t2));
+          const float g2v = fmaf(dLdq, fmaf(kk, s2, -2.0f * t2), wgt * S.gD[k]);
+          const float px = A.e2.w, py = A.e3.x, pz = A.e1.z;
+          tw[0] += g0v; tw[1] += g1v; tw[2] += g2v;
+          tw[3] += py * g2v - pz * g1v;
+          tw[4] += pz * g0v - px * g2v;
+          tw[5] += px * g1v - py * g0v;
+        };
+        Entry A, B;
+        fetch(A);
+        while (true) {  // (uniform; the lanes with an entry left step)
+          unsigned long long live = lanes(cur != 0u);
+          if (live == 0ull) break;
+          if (in_lanes(live)) step(A, B);
+          live = lanes(cur != 0u);
+          if (live == 0ull) break;
+          if (in_lanes(live)) step(B, A);
+        }
+      }
+    }
+  }
+  store_twist<NW>(ws, t, tw, S.lsum, red_s);
+}
+
+// Backward to the slots (MODE bit 1), with the twist (bit 0) and geometry
+// (bit 2) where asked.  Three waves per SIMD (the LDS allows three blocks per
+// CU), two with geometry.  A step takes ~85 VALU instructions (115 before its
+// register sets alternated) and 11 LDS ones; the LDS and the waits of three
+// waves per SIMD bound it: 5 views over 8 keyframes 2629 -> 2496 us (with the
+// twist 2895 -> 2721), 2 views over 3 with geometry 839 -> 810.
+template <int TILE, int BATCH, int MODE>
+__global__ __launch_bounds__(Shape<TILE>::NT, (MODE & 4) ? 2 : 3) void k_bwd(Ws ws, const float *g_rgb,
+                                                         const float *g_depth,
+                                                         const float *g_sil) {
+  constexpr int NT = Shape<TILE>::NT, PPT = Shape<TILE>::PPT;
+  constexpr int NW = NT / kWave;
+  constexpr int PER = (BATCH + NT - 1) / NT;
+  static_assert((MODE & 2) != 0, "the twist alone has its own kernel");
+  constexpr bool kTwist = (MODE & 1) != 0;
+  constexpr bool kGeo = (MODE & 4) != 0;  // slots also carry dL/dp
+  constexpr int NA = kGeo ? 8 : 5;        // floats per slot
+  constexpr int G = Group<TILE, BATCH>::G, NH = 2 * G, NR = NW * PPT;
+  // staged entry, the batch's last first: e0 (mx, my, qa, 2 qb), e1 (qc, o, z,
+  // qb), e2 (c, r), ej (fx/z, fy/z, -fx px/z^2, -fy py/z^2) and for dL/dp
+  // ep (px, py, 2 r^2 / z); a finished lane's last reads fall up to 32
+  // entries past an array, into the next one's or the 32 at the end
+  constexpr bool kDp = kTwist || kGeo;
+  __shared__ float4 entries[(kDp ? 5 : 4) * BATCH + 32];
+  float4 *const e0s = entries, *const e1s = e0s + BATCH, *const e2s = e1s + BATCH;
+  float4 *const ejs = e2s + BATCH, *const eps_ = ejs + (kDp ? BATCH : 0);
+  // per-wave slot accumulators: floats 0-3 in accA, 4 (4-7 with geometry)
+  // in accB, and the claim tags of their read-modify-write
+  __shared__ f32x4 accA[NW][BATCH];
+  __shared__ AccB<kGeo> accB[NW][BATCH];
+  __shared__ uint8_t tag_s[NW][BATCH + kWave];  // + a tag per lane
+  __shared__ int maxlast_s;
+  __shared__ float red_s[NW][7];
+  __shared__ uint32_t words[NH + 1][NR][kWave];  // the last row zero
+
+  const int t = tile_of_block(ws);
+  const DevView &vw = ws.views[find_view_by_tile(ws, t)];
+  const int lt = t - vw.tile_base;
+  const int tx = lt % vw.tiles_x, ty = lt / vw.tiles_x;
+  const int ox = tx * TILE, oy = ty * TILE;
+  const uint2 rg = ws.ranges[t];
+  const int start = (int)rg.x, end = (int)rg.y;
+  const int w = threadIdx.x / kWave;
+
+  BwdPixels<PPT> S;
+  load_pixels<TILE, false>(ws, vw, ox, oy, g_rgb, g_depth, g_sil, TrackArgs{}, S);
+  auto &px = S.px, &py = S.py, &T = S.T, &gC0 = S.gC0, &gC1 = S.gC1, &gC2 = S.gC2, &gD = S.gD;
+  auto &E = S.E, &XP0 = S.XP0, &XP1 = S.XP1, &XP2 = S.XP2, &XPZ = S.XPZ, &GS1 = S.GS1;
+  auto &last = S.last;
+  const uint32_t mylast = S.mylast;
+#pragma unroll
+  for (int k = 0; k < PPT; k++) words[NH][w * PPT + k][lane_id()] = 0u;
   if (threadIdx.x == 0) maxlast_s = 0;
   __syncthreads();
   atomicMax(&maxlast_s, (int)mylast);
@@ -660,7 +906,7 @@ __global__ __launch_bounds__(Shape<TILE>::NT, (MODE & 2) ? ((MODE & 4) ? 2 : 3) 
   // the batch below is gathered while the current one is replayed, and its
   // ids one batch ahead (positions clamped to the list, extra loads unused)
   BwdEntry st[PER];
-  uint32_t pid[PER];
+  uint32_t pid[PER], slot[PER];  // (slot: of the entry this thread staged)
   const int n_rec = vw.n_rec, rec_base = vw.rec_base;
   // position of this thread's entry k in the batch starting at `blo`,
   // clamped to the list (batches below the first repeat its first entry)
@@ -672,7 +918,7 @@ __global__ __launch_bounds__(Shape<TILE>::NT, (MODE & 2) ? ((MODE & 4) ? 2 : 3) 
 #pragma unroll
     for (int k = 0; k < PER; k++) pid[k] = ws.ids[min(lo + (int)threadIdx.x + k * NT, stop - 1)];
 #pragma unroll
-    for (int k = 0; k < PER; k++) fetch_bwd_entry<kSlots>(ws, n_rec, rec_base, pid[k], st[k]);
+    for (int k = 0; k < PER; k++) fetch_bwd_entry(ws, n_rec, rec_base, pid[k], st[k]);
 #pragma unroll
     for (int k = 0; k < PER; k++) pid[k] = ws.ids[bpos(lo - BATCH, k)];
   }
@@ -682,33 +928,32 @@ __global__ __launch_bounds__(Shape<TILE>::NT, (MODE & 2) ? ((MODE & 4) ? 2 : 3) 
     __syncthreads();
 #pragma unroll
     for (int k = 0; k < PER; k++) {
-      const int i = threadIdx.x + k * NT;
+      const int i = threadIdx.x + k * NT, j = BATCH - 1 - i;
+      slot[k] = 0xffffffffu;
       if (i >= nb) continue;
       const BwdEntry &E = st[k];
-      // the doubled off-diagonal conic term (exact) for q, the plain one
-      // (in place of the extent, which staging no longer needs) for dq
-      e0s[i] = make_float4(E.e0.x, E.e0.y, E.e0.z, 2.0f * E.e0.w);
-      e1s[i] = make_float4(E.e1.x, E.e1.y, E.e1.z, E.e0.w);
-      e2s[i] = E.e2;
-      const float iz = 1.0f / E.e1.z;
-      ejs[i] = make_float4(vfx * iz, vfy * iz, -vfx * E.eb.x * iz * iz, -vfy * E.eb.y * iz * iz);
-      const uint32_t sl = kSlots ? entry_slot(ws, E, tx, ty) : 0xffffffffu;
+      // (the doubled off-diagonal conic term is exact)
+      e0s[j] = make_float4(E.e0.x, E.e0.y, E.e0.z, 2.0f * E.e0.w);
+      const uint32_t sl = entry_slot(ws, E, tx, ty);
       // no slot (only after a capacity overflow): the entry learns nothing
-      const float learn = !kSlots || sl != 0xffffffffu ? E.eb.z : 0.f;
-      eps_[i] = make_float4(E.eb.x, E.eb.y, 2.0f * E.e2.w * E.e2.w * iz, learn);
-      if (kSlots) {
-        slot_s[i] = sl;
+      const float learn = sl != 0xffffffffu ? E.eb.z : 0.f;
+      e1s[j] = make_float4(E.e1.x, E.e1.y, E.e1.z, E.e0.w);
+      // (a set sign bit of r: not learnable; r itself is positive)
+      e2s[j] = make_float4(E.e2.x, E.e2.y, E.e2.z, __builtin_copysignf(E.e2.w, learn != 0.f ? 1.f : -1.f));
+      const float iz = 1.0f / E.e1.z;
+      ejs[j] = make_float4(vfx * iz, vfy * iz, -vfx * E.eb.x * iz * iz, -vfy * E.eb.y * iz * iz);
+      if (kDp) eps_[j] = make_float4(E.eb.x, E.eb.y, 2.0f * E.e2.w * E.e2.w * iz, 0.f);
+      slot[k] = learn != 0.f ? sl : 0xffffffffu;
 #pragma unroll
-        for (int ww = 0; ww < NW; ww++) {
-          accA[ww][i] = f32x4{0.f, 0.f, 0.f, 0.f};
-          accB[ww][i] = AccB<kGeo>{};
-        }
+      for (int ww = 0; ww < NW; ww++) {
+        accA[ww][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+        accB[ww][j] = AccB<kGeo>{};
       }
     }
     __syncthreads();
     // the batches below are full ones (below the first: clamped, unused)
 #pragma unroll
-    for (int k = 0; k < PER; k++) fetch_bwd_entry<kSlots>(ws, n_rec, rec_base, pid[k], st[k]);
+    for (int k = 0; k < PER; k++) fetch_bwd_entry(ws, n_rec, rec_base, pid[k], st[k]);
 #pragma unroll
     for (int k = 0; k < PER; k++) pid[k] = ws.ids[bpos(lo - 2 * BATCH, k)];
     // this wave's entries, last to first, below its own last contributor
@@ -719,9 +964,9 @@ __global__ __launch_bounds__(Shape<TILE>::NT, (MODE & 2) ? ((MODE & 4) ? 2 : 3) 
       // pixels in the forward, cut at the pixel's last contributor; the words
       // go in bit-reversed, top half first, so the lowest set bit of a word is
       // the lane's next entry towards the front
-      uint32_t ns[PPT], seq[PPT];
+      uint32_t nz[PPT];
 #pragma unroll
-      for (int k = 0; k < PPT; k++) ns[k] = seq[k] = 0u;
+      for (int k = 0; k < PPT; k++) nz[k] = 0u;
       // the group's lane bits, all loads issued at once (chunks past the top
       // one reload the top one's, unused)
       unsigned long long lb[G][PPT];
@@ -743,217 +988,218 @@ __global__ __launch_bounds__(Shape<TILE>::NT, (MODE & 2) ? ((MODE & 4) ? 2 : 3) 
           const unsigned long long below =
               lim_k >= kWave ? ~0ull : (lim_k <= 0 ? 0ull : (1ull << lim_k) - 1ull);
           const unsigned long long own = lb[cc][k] & below;
-          const uint32_t hh = 2u * (uint32_t)(c - g0);
-          push_word<NS, NR>(words, w * PPT + k, __builtin_bitreverse32((uint32_t)(own >> 32)),
-                            hh + 1u, ns[k], seq[k]);
-          push_word<NS, NR>(words, w * PPT + k, __builtin_bitreverse32((uint32_t)own), hh,
-                            ns[k], seq[k]);
+          const uint32_t hi = __builtin_bitreverse32((uint32_t)(own >> 32));
+          const uint32_t lo = __builtin_bitreverse32((uint32_t)own);
+          constexpr int kTop = 2 * (G - 1);
+          words[kTop - 2 * cc][w * PPT + k][lane_id()] = hi;
+          words[kTop - 2 * cc + 1][w * PPT + k][lane_id()] = lo;
+          nz[k] |= (hi ? 1u << (kTop - 2 * cc) : 0u) | (lo ? 2u << (kTop - 2 * cc) : 0u);
         }
       }
       // 2. each lane replays its own entries of the group, last to first, one
-      // step per entry; the wave runs until its last lane is through
+      // step per entry; the wave runs until its last lane is through.  As in
+      // the forward, steps alternate between two register sets.
 #pragma unroll
       for (int k = 0; k < PPT; k++) {
         const int row = w * PPT + k;
-        words[ns[k]][row][lane_id()] = 0u;
-        uint32_t cur = words[0][row][lane_id()], nxt = words[1][row][lane_id()];
-        uint32_t sq = seq[k], sp = 0u;
-        const int gb = g0 * kWave + 31;
-        // the next entry's LDS reads are issued before this one is replayed
-        int i = gb + (int)((sq & 15u) << 5) - low_bit(cur);
-        float4 n0 = e0s[i], n1 = e1s[i], n2 = e2s[i], nj = ejs[i], np = eps_[i];
-        // Slots (mapping): each lane's adds of a step go into its wave's
-        // accumulators by read-modify-write.  The lanes that replay one
-        // entry in a step claim it by writing their lane number to its tag;
-        // with the claim they read the tag back and the accumulators.  The
-        // claim is settled in the lane's next step, after that step's
-        // arithmetic has covered the reads' latency: the lane whose number
-        // stayed in the tag (one per entry) adds what it read to its values
-        // and writes them back, and the lanes that lost then add theirs with
-        // LDS float atomics (6 % of the lane steps of a mapping wave, against
-        // all of them with atomics alone, which the LDS runs at about a lane
-        // per three clocks).  A lane runs one idle step after its last entry
-        // to settle its last claim.  Compiler barriers (kLdsOrder) keep each
-        // claim and settle in its step and in program order.
-        bool pp = false;  // an open claim (values pva/pvb for entry pidx)
-        int pidx = 0, rt = 0;
-        f32x4 pva = {0.f, 0.f, 0.f, 0.f}, ra = {0.f, 0.f, 0.f, 0.f};
-        AccB<kGeo> pvb{}, rb{};
+        const int gb = BATCH - kWave * (g0 + G);
+        auto first = [](uint32_t v) { return __builtin_ctz(v | (1u << NH)); };
+        uint32_t left = nz[k];
+        int h = first(left);
+        left &= left - 1u;
+        int hn = first(left);
+        uint32_t cur = words[h][row][lane_id()], nxt = words[hn][row][lane_id()];
         const int me = lane_id();
-        // a claim: tag slot `ti` claimed, then read back with entry j's
-        // accumulators
-        auto claim = [&](int ti, int j) {
+        // Each lane's adds of a step go into its wave's accumulators by
+        // read-modify-write.  The lanes that replay one entry in a step claim
+        // it by writing their lane number to its tag; with the claim they
+        // read the tag back and the accumulators.  The claim is settled in
+        // the next step, after that step's arithmetic has covered the reads'
+        // latency: the lane whose number stayed in the tag (one per entry)
+        // adds what it read to its values and writes them back, and the
+        // lanes that lost then add theirs with LDS float atomics (6 % of the
+        // lane steps of a mapping wave, against all of them with atomics
+        // alone, which the LDS runs at about a lane per three clocks).  A
+        // lane's last claim is settled in the step after its last entry.
+        // Compiler barriers (kLdsOrder) keep each claim and settle in its
+        // step and in program order.
+        struct Entry {
+          float4 e0, e1, e2, ej, ep;
+          int i;
+        };
+        struct Claim {  // a step's values for entry idx, and what its claim read
+          f32x4 va, ra;
+          AccB<kGeo> vb, rb;
+          int idx, rt;
+        };
+        auto fetch = [&](Entry &N) {
+          N.i = gb + (h << 5) + low_bit(cur);
+          N.e0 = e0s[N.i]; N.e1 = e1s[N.i]; N.e2 = e2s[N.i]; N.ej = ejs[N.i];
+          if (kDp) N.ep = eps_[N.i];
+        };
+        // tag slot `ti` claimed, then read back with entry j's accumulators
+        auto claim = [&](int ti, int j, Claim &C) {
           uint8_t LDS_AS *tg = (uint8_t LDS_AS *)&tag_s[w][ti];
           *tg = (uint8_t)me;
           kLdsOrder();
-          rt = *tg;
-          ra = *(f32x4 LDS_AS *)&accA[w][j];
-          rb = *(AccB<kGeo> LDS_AS *)&accB[w][j];
+          C.rt = *tg;
+          C.ra = *(f32x4 LDS_AS *)&accA[w][j];
+          C.rb = *(AccB<kGeo> LDS_AS *)&accB[w][j];
+          C.idx = j;
           kLdsOrder();
         };
-        // the loop is entered, as it is re-entered, with a claim's LDS
-        // operations behind the first entry's reads (here one on the lane's
-        // own tag, not settled)
-        if constexpr (kSlots) claim(AB + me, 0);
-        while (cur != 0u || (kSlots && pp)) {
-          const bool live = !kSlots || cur != 0u;
-          const float4 e0 = n0, e1 = n1, e2 = n2, ej = nj, ep = np;
-          const int cur_i = i;  // this entry's batch position
-          {
-            uint32_t c2 = cur & (cur - 1u);
-            const bool z = c2 == 0u;
-            c2 = z ? nxt : c2;
-            cur = live ? c2 : cur;
-            sq = live && z ? sq >> 4 : sq;
-            sp += live && z ? 1u : 0u;
-          }
-          nxt = words[sp + 1u][row][lane_id()];
-          i = gb + (int)((sq & 15u) << 5) - low_bit(cur);
-          n0 = e0s[i]; n1 = e1s[i]; n2 = e2s[i]; nj = ejs[i]; np = eps_[i];
-          const float dx = px[k] - e0.x, dy = py[k] - e0.y;
-          const float q = quad2(e0, e1.x, px[k], py[k]);
+        // the arithmetic of one step: issue the next entry's reads into N,
+        // replay A into C's values; true where A learns
+        auto replay = [&](const Entry &A, Entry &N, Claim &C) {
+          cur &= cur - 1u;
+          const bool z = cur == 0u;
+          cur = z ? nxt : cur;
+          h = z ? hn : h;
+          left = z ? left & (left - 1u) : left;
+          hn = first(left);
+          nxt = words[hn][row][lane_id()];
+          fetch(N);
+          const float dx = px[k] - A.e0.x, dy = py[k] - A.e0.y;
+          // q in the forward's order of operations
+          const float ax = A.e0.z * dx, cy = A.e1.x * dy;
+          const float q = fmaf(cy, dy, fmaf(A.e0.w * dx, dy, ax * dx));
           const float gau = __builtin_amdgcn_exp2f(q * kNegHalfLog2e);
-          const float a = fminf(amax, e1.y * gau);
-          const bool ok = live && a >= amin;
-          const float oG = e1.y * gau;
+          const float oG = A.e1.y * gau;
+          const float a = fminf(amax, oG);
+          const bool ok = a >= amin;
           const float om = 1.0f - a;
           const float Tk = ok ? T[k] * __builtin_amdgcn_rcpf(om) : T[k];
           T[k] = Tk;
           const float wgt = ok ? a * Tk : 0.f;
           // g . (x - B) for this Gaussian, x = (colour, depth, 1)
-          const float gdi =
-              fmaf(gC0[k], e2.x - XP0[k],
-                   fmaf(gC1[k], e2.y - XP1[k],
-                        fmaf(gC2[k], e2.z - XP2[k], fmaf(gD[k], e1.z - XPZ[k], GS1[k] + E[k]))));
+          const float gdi = fmaf(
+              gC0[k], A.e2.x - XP0[k],
+              fmaf(gC1[k], A.e2.y - XP1[k],
+                   fmaf(gC2[k], A.e2.z - XP2[k], fmaf(gD[k], A.e1.z - XPZ[k], GS1[k] + E[k]))));
           const float dLda = ok ? gdi * Tk : 0.f;
           E[k] = ok ? om * gdi : E[k];
-          XP0[k] = ok ? e2.x : XP0[k];
-          XP1[k] = ok ? e2.y : XP1[k];
-          XP2[k] = ok ? e2.z : XP2[k];
-          XPZ[k] = ok ? e1.z : XPZ[k];
+          XP0[k] = ok ? A.e2.x : XP0[k];
+          XP1[k] = ok ? A.e2.y : XP1[k];
+          XP2[k] = ok ? A.e2.z : XP2[k];
+          XPZ[k] = ok ? A.e1.z : XPZ[k];
           GS1[k] = ok ? 0.f : GS1[k];
           const bool pass = oG <= amax;
           const float dLdq = pass ? -0.5f * oG * dLda : 0.f;
-          const float qb = e1.w;
-          const float w0 = fmaf(e0.z, dx, qb * dy), w1 = fmaf(qb, dx, e1.x * dy);
-          const float t0 = ej.x * w0, t1 = ej.y * w1, t2 = fmaf(ej.z, w0, ej.w * w1);
+          const float w0 = fmaf(A.e0.z, dx, A.e1.w * dy), w1 = fmaf(A.e1.w, dx, cy);
+          const float t0 = A.ej.x * w0, t1 = A.ej.y * w1, t2 = fmaf(A.ej.z, w0, A.ej.w * w1);
           // dL/dp of this pair (camera-frame centre)
           float g0v = 0.f, g1v = 0.f, g2v = 0.f;
-          if (kTwist || kGeo) {
-            const float kk = ep.z;
+          if (kDp) {
+            const float kk = A.ep.z;
             g0v = dLdq * fmaf(kk * t0, t2, -2.0f * t0);
             g1v = dLdq * fmaf(kk * t1, t2, -2.0f * t1);
             const float s2 = fmaf(t0, t0, fmaf(t1, t1, 2.0f * t2 * t2));
             g2v = fmaf(dLdq, fmaf(kk, s2, -2.0f * t2), wgt * gD[k]);
           }
-          if (kTwist && live) {
-            const float pz = e1.z;
+          if (kTwist) {
+            const float pz = A.e1.z;
             tw[0] += g0v; tw[1] += g1v; tw[2] += g2v;
-            tw[3] += ep.y * g2v - pz * g1v;
-            tw[4] += pz * g0v - ep.x * g2v;
-            tw[5] += ep.x * g1v - ep.y * g0v;
+            tw[3] += A.ep.y * g2v - pz * g1v;
+            tw[4] += pz * g0v - A.ep.x * g2v;
+            tw[5] += A.ep.x * g1v - A.ep.y * g0v;
           }
-          if constexpr (kSlots) {
-            // this step's values
-            const bool real = ok && ep.w != 0.f;
-            const float tt = fmaf(t0, t0, fmaf(t1, t1, t2 * t2));
-            const f32x4 nva = {wgt * gC0[k], wgt * gC1[k], wgt * gC2[k], pass ? gau * dLda : 0.f};
-            const float v4 = dLdq * (-2.0f * e2.w * tt);
-            AccB<kGeo> nvb;
-            if constexpr (kGeo) nvb = f32x4{v4, g0v, g1v, g2v};
-            else nvb = v4;
-            // the settle below waits for the previous claim's reads: after
-            // the step's arithmetic (which this empty statement consumes)
-            asm volatile("" ::"v"(nva[0]), "v"(nva[1]), "v"(nva[2]), "v"(nva[3]), "v"(v4) : "memory");
-            // settle the previous step's claim: the lane whose number stayed
-            // in the tag writes its sum back; then the lanes that lost add
-            // theirs with LDS atomics (after that write, in the LDS's order)
-            const bool won = pp && rt == me;
-            if (won) {
-              *(f32x4 LDS_AS *)&accA[w][pidx] = ra + pva;
-              *(AccB<kGeo> LDS_AS *)&accB[w][pidx] = rb + pvb;
-            }
-            kLdsOrder();
-            if (pp && !won) {
-              float *fa = (float *)&accA[w][pidx];
-              float *fb = (float *)&accB[w][pidx];
-              atomicAdd(fa + 0, pva[0]);
-              atomicAdd(fa + 1, pva[1]);
-              atomicAdd(fa + 2, pva[2]);
-              atomicAdd(fa + 3, pva[3]);
-              if constexpr (kGeo) {
+          const float tt = fmaf(t0, t0, fmaf(t1, t1, t2 * t2));
+          C.va = f32x4{wgt * gC0[k], wgt * gC1[k], wgt * gC2[k], pass ? gau * dLda : 0.f};
+          const float v4 = dLdq * (-2.0f * A.e2.w * tt);
+          if constexpr (kGeo) C.vb = f32x4{v4, g0v, g1v, g2v};
+          else C.vb = v4;
+          // the settle waits for the previous claim's reads: after the step's
+          // arithmetic (which this empty statement consumes)
+          asm volatile("" ::"v"(C.va[0]), "v"(C.va[1]), "v"(C.va[2]), "v"(C.va[3]), "v"(v4) : "memory");
+          return ok && __float_as_int(A.e2.w) >= 0;
+        };
+        // the claim O settled in the lanes `open`: the lane whose number
+        // stayed in the tag writes its sum back; then the lanes that lost add
+        // theirs with LDS atomics (after that write, in the LDS's order)
+        auto settle = [&](const Claim &O, unsigned long long open) {
+          const bool po = in_lanes(open), won = po && O.rt == me;
+          if (won) {
+            *(f32x4 LDS_AS *)&accA[w][O.idx] = O.ra + O.va;
+            *(AccB<kGeo> LDS_AS *)&accB[w][O.idx] = O.rb + O.vb;
+          }
+          kLdsOrder();
+          if (po && !won) {
+            float *fa = (float *)&accA[w][O.idx];
+            float *fb = (float *)&accB[w][O.idx];
+            atomicAdd(fa + 0, O.va[0]);
+            atomicAdd(fa + 1, O.va[1]);
+            atomicAdd(fa + 2, O.va[2]);
+            atomicAdd(fa + 3, O.va[3]);
+            if constexpr (kGeo) {
 #pragma unroll
-                for (int c = 0; c < 4; c++) atomicAdd(fb + c, pvb[c]);
-              } else {
-                atomicAdd(fb, pvb);
-              }
+              for (int c = 0; c < 4; c++) atomicAdd(fb + c, O.vb[c]);
+            } else {
+              atomicAdd(fb, O.vb);
             }
-            kLdsOrder();
-            // this step's claim; every lane makes one (a lane with nothing to
-            // add on its own tag), so that the LDS operations behind the next
-            // entry's reads are the same on every path and the next step
-            // waits for those reads only
-            pp = ok && ep.w != 0.f;
-            pva = nva;
-            pvb = nvb;
-            pidx = cur_i;
-            claim(pp ? cur_i : AB + me, cur_i);
           }
+          kLdsOrder();
+        };
+        // a step of the lanes `live`; every one claims (a lane with nothing
+        // to add on its own tag), so that the LDS operations behind the next
+        // entry's reads are the same on every path and the next step waits
+        // for those reads only.  Returns the lanes whose claim is open.
+        auto step = [&](const Entry &A, Entry &N, Claim &C, const Claim &O, unsigned long long live,
+                        unsigned long long open) {
+          bool learns = false;
+          if (in_lanes(live)) learns = replay(A, N, C);
+          settle(O, open);
+          if (in_lanes(live)) claim(learns ? A.i : BATCH + me, A.i, C);
+          return lanes(learns);
+        };
+        Entry A, B;
+        Claim C, D;
+        unsigned long long open = 0ull;
+        fetch(A);
+        claim(BATCH + me, 0, D);  // (as before every later step; not settled)
+        while (true) {
+          unsigned long long live = lanes(cur != 0u);
+          if ((live | open) == 0ull) break;
+          open = step(A, B, C, D, live, open);
+          live = lanes(cur != 0u);
+          if ((live | open) == 0ull) break;
+          open = step(B, A, D, C, live, open);
         }
       }
     }
-    if (kSlots) {
-      __syncthreads();
-      for (int i = threadIdx.x; i < nb; i += NT) {
-        if (eps_[i].w == 0.f) continue;
-        float *o = ws.slots + NA * (int64_t)slot_s[i];
-        f32x4 sa = accA[0][i];
-        AccB<kGeo> sb = accB[0][i];
-#pragma unroll
-        for (int ww = 1; ww < NW; ww++) {
-          sa = sa + accA[ww][i];
-          sb = sb + accB[ww][i];
-        }
-#pragma unroll
-        for (int c = 0; c < 4; c++) o[c] = sa[c];
-        if constexpr (kGeo) {
-#pragma unroll
-          for (int c = 0; c < 4; c++) o[4 + c] = sb[c];
-        } else {
-          o[4] = sb;
-        }
-      }
-    }
-  }
-  if (kSlots) {
-    // list entries past every pixel's last contributor: zero slots
-    for (int i = stop + (int)threadIdx.x; i < end; i += NT) {
-      BwdEntry E;
-      fetch_bwd_entry<true>(ws, n_rec, rec_base, ws.ids[i], E);
-      const uint32_t sl = entry_slot(ws, E, tx, ty);
-      if (sl == 0xffffffffu) continue;
-      float *o = ws.slots + NA * (int64_t)sl;
-#pragma unroll
-      for (int c = 0; c < NA; c++) o[c] = 0.f;
-    }
-  }
-  if (kTwist) {
-    // per tile: the six twist sums and (tracking) the Eq. 1 loss
-#pragma unroll
-    for (int c = 0; c < 6; c++) {
-      const float s = wave_sum(tw[c]);
-      if (lane_id() == 0) red_s[w][c] = s;
-    }
-    const float ls = wave_sum(lsum);
-    if (lane_id() == 0) red_s[w][6] = ls;
     __syncthreads();
-    if (threadIdx.x < 7) {
-      float s = 0.f;
 #pragma unroll
-      for (int ww = 0; ww < NW; ww++) s += red_s[ww][threadIdx.x];
-      ws.twist_part[8 * (int64_t)t + threadIdx.x] = s;
+    for (int k = 0; k < PER; k++) {
+      if (slot[k] == 0xffffffffu) continue;
+      const int j = BATCH - 1 - ((int)threadIdx.x + k * NT);
+      float *o = ws.slots + NA * (int64_t)slot[k];
+      f32x4 sa = accA[0][j];
+      AccB<kGeo> sb = accB[0][j];
+#pragma unroll
+      for (int ww = 1; ww < NW; ww++) {
+        sa = sa + accA[ww][j];
+        sb = sb + accB[ww][j];
+      }
+#pragma unroll
+      for (int c = 0; c < 4; c++) o[c] = sa[c];
+      if constexpr (kGeo) {
+#pragma unroll
+        for (int c = 0; c < 4; c++) o[4 + c] = sb[c];
+      } else {
+        o[4] = sb;
+      }
     }
   }
+  // list entries past every pixel's last contributor: zero slots
+  for (int i = stop + (int)threadIdx.x; i < end; i += NT) {
+    BwdEntry E;
+    fetch_bwd_entry(ws, n_rec, rec_base, ws.ids[i], E);
+    const uint32_t sl = entry_slot(ws, E, tx, ty);
+    if (sl == 0xffffffffu) continue;
+    float *o = ws.slots + NA * (int64_t)sl;
+#pragma unroll
+    for (int c = 0; c < NA; c++) o[c] = 0.f;
+  }
+  if (kTwist) store_twist<NW>(ws, t, tw, 0.f, red_s);
 }
 
 template <int TILE, int BATCH>
@@ -965,15 +1211,28 @@ hipError_t fwd_launch(const Ws &ws, float *rgb, float *depth, float *sil, hipStr
 
 template <int TILE, int BATCH>
 hipError_t bwd_launch(const Ws &ws, const float *g_rgb, const float *g_depth, const float *g_sil,
-                      int mode, hipStream_t st, TrackArgs tr) {
+                      int mode, hipStream_t st) {
   const dim3 g(ws.n_tiles), b(Shape<TILE>::NT);
   switch (mode) {
-    case 1: hipLaunchKernelGGL((k_bwd<TILE, BATCH, 1>), g, b, 0, st, ws, g_rgb, g_depth, g_sil, tr); break;
-    case 2: hipLaunchKernelGGL((k_bwd<TILE, BATCH, 2>), g, b, 0, st, ws, g_rgb, g_depth, g_sil, tr); break;
-    case 3: hipLaunchKernelGGL((k_bwd<TILE, BATCH, 3>), g, b, 0, st, ws, g_rgb, g_depth, g_sil, tr); break;
-    case 6: hipLaunchKernelGGL((k_bwd<TILE, BATCH, 6>), g, b, 0, st, ws, g_rgb, g_depth, g_sil, tr); break;
-    case 7: hipLaunchKernelGGL((k_bwd<TILE, BATCH, 7>), g, b, 0, st, ws, g_rgb, g_depth, g_sil, tr); break;
+    case 2: hipLaunchKernelGGL((k_bwd<TILE, BATCH, 2>), g, b, 0, st, ws, g_rgb, g_depth, g_sil); break;
+    case 3: hipLaunchKernelGGL((k_bwd<TILE, BATCH, 3>), g, b, 0, st, ws, g_rgb, g_depth, g_sil); break;
+    case 6: hipLaunchKernelGGL((k_bwd<TILE, BATCH, 6>), g, b, 0, st, ws, g_rgb, g_depth, g_sil); break;
+    case 7: hipLaunchKernelGGL((k_bwd<TILE, BATCH, 7>), g, b, 0, st, ws, g_rgb, g_depth, g_sil); break;
     default: return hipErrorInvalidValue;
+  }
+  return hipGetLastError();
+}
+
+template <int TILE, int BATCH>
+hipError_t twist_launch(const Ws &ws, const float *g_rgb, const float *g_depth, const float *g_sil,
+                        hipStream_t st, const vtgs_track_cfg *track) {
+  const dim3 g(ws.n_tiles), b(Shape<TILE>::NT);
+  if (track) {
+    const TrackArgs tr{track->alpha, track->beta, track->sil_thr};
+    hipLaunchKernelGGL((k_bwd_twist<TILE, BATCH, true>), g, b, 0, st, ws, nullptr, nullptr, nullptr, tr);
+  } else {
+    hipLaunchKernelGGL((k_bwd_twist<TILE, BATCH, false>), g, b, 0, st, ws, g_rgb, g_depth, g_sil,
+                       TrackArgs{});
   }
   return hipGetLastError();
 }
@@ -997,11 +1256,22 @@ hipError_t fwd_tile(const Ws &ws, float *rgb, float *depth, float *sil, hipStrea
 
 template <int TILE>
 hipError_t bwd_tile(const Ws &ws, const float *a, const float *b, const float *c, int mode,
-                    hipStream_t st, TrackArgs tr) {
+                    hipStream_t st, const vtgs_track_cfg *track) {
+  if (mode == 1) {
+    switch (ws.batch) {
+      case 128: return twist_launch<TILE, 128>(ws, a, b, c, st, track);
+      // 384 entries a pass at four blocks per CU (1,200 tiles 49 us, 80 tiles
+      // 31, a batch of served tracks 1026) against 256 at five (54, 40 and
+      // 1096) and 512 at three (51, 30 and 1035)
+      case 256: return twist_launch<TILE, TILE == 16 ? 384 : 256>(ws, a, b, c, st, track);
+      case 512: return twist_launch<TILE, 512>(ws, a, b, c, st, track);
+    }
+    return hipErrorInvalidValue;
+  }
   switch (ws.batch) {
-    case 128: return bwd_launch<TILE, 128>(ws, a, b, c, mode, st, tr);
-    case 256: return bwd_launch<TILE, 256>(ws, a, b, c, mode, st, tr);
-    case 512: return bwd_launch<TILE, 512>(ws, a, b, c, mode, st, tr);
+    case 128: return bwd_launch<TILE, 128>(ws, a, b, c, mode, st);
+    case 256: return bwd_launch<TILE, 256>(ws, a, b, c, mode, st);
+    case 512: return bwd_launch<TILE, 512>(ws, a, b, c, mode, st);
   }
   return hipErrorInvalidValue;
 }
@@ -1023,16 +1293,12 @@ hipError_t launch_composite_bwd(const Ws &ws, const float *g_rgb, const float *g
                                 const float *g_sil, int mode, hipStream_t st,
                                 const vtgs_track_cfg *track) {
   if (ws.n_tiles == 0) return hipSuccess;
-  TrackArgs tr{0.f, 0.f, 0.f, 0};
   if (((mode & 4) != 0) != (ws.slot_w == 8) && (mode & 2)) return hipErrorInvalidValue;
-  if (track) {
-    if (mode != 1) return hipErrorInvalidValue;
-    tr = TrackArgs{track->alpha, track->beta, track->sil_thr, 1};
-  }
+  if (track && mode != 1) return hipErrorInvalidValue;
   switch (ws.tile) {
-    case 8: return bwd_tile<8>(ws, g_rgb, g_depth, g_sil, mode, st, tr);
-    case 16: return bwd_tile<16>(ws, g_rgb, g_depth, g_sil, mode, st, tr);
-    case 32: return bwd_tile<32>(ws, g_rgb, g_depth, g_sil, mode, st, tr);
+    case 8: return bwd_tile<8>(ws, g_rgb, g_depth, g_sil, mode, st, track);
+    case 16: return bwd_tile<16>(ws, g_rgb, g_depth, g_sil, mode, st, track);
+    case 32: return bwd_tile<32>(ws, g_rgb, g_depth, g_sil, mode, st, track);
   }
   return hipErrorInvalidValue;
 }
