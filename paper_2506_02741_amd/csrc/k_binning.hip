@@ -173,6 +173,7 @@ __global__ __launch_bounds__(kNT) void k_preprocess(Ws ws) {
   // with one take it without a search)
   __shared__ int seg_start[kSegLds];
   __shared__ uint32_t box_cnt[kNT / kWave][kBoxMax];
+  __shared__ uint32_t slot_cnt[kNT / kWave];
   const bool seg_lds = ws.n_segs > 1 && ws.n_segs <= kSegLds;
   if (seg_lds) {
     for (int k = threadIdx.x; k < ws.n_segs; k += kNT) seg_start[k] = ws.segs[k].rec_start;
@@ -266,7 +267,6 @@ __global__ __launch_bounds__(kNT) void k_preprocess(Ws ws) {
     ws.recB[r] = make_float4(px, py, learn, 0.f);
     if (!has) { x0 = 1; y0 = 0; x1 = 0; y1 = 0; }
     ws.rect[r] = make_uint2((uint32_t)x0 | ((uint32_t)y0 << 16), (uint32_t)x1 | ((uint32_t)y1 << 16));
-    ws.rec_cnt[r] = has ? (uint32_t)((x1 - x0 + 1) * (y1 - y0 + 1)) : 0u;
     // the depth again on its own, so that the key fill reads 4 B per record
     ws.zbits[r] = __float_as_uint(pz);
     // the segment's relative pose, kept for the gradient gathers
@@ -274,6 +274,13 @@ __global__ __launch_bounds__(kNT) void k_preprocess(Ws ws) {
 #pragma unroll
       for (int c = 0; c < 12; c++) ws.segs[seg].M[c] = M[c];
     }
+  }
+  if (ws.slots) {
+    // plans with gradients per Gaussian: the records' tiles, summed up to
+    // and with this one over the block, for the slot offsets
+    const uint32_t n = has ? (uint32_t)((x1 - x0 + 1) * (y1 - y0 + 1)) : 0u;
+    const uint32_t before = block_exclusive_scan<kNT>(n, slot_cnt, nullptr);
+    if (active) ws.rec_cnt[r] = before + n;
   }
   const WaveBox box = wave_box(has, view, x0, y0, x1, y1);
   if (box.shared) {
@@ -324,11 +331,33 @@ __device__ __forceinline__ int order_bucket(uint32_t n) {
   const int sb = bl >= 2 ? (int)((n >> (bl - 2)) & 1u) : 0;
   return kOrderBuckets - 2 - min(2 * bl + sb - 2, kOrderBuckets - 2);
 }
-__global__ __launch_bounds__(kScanNT) void k_scan_tiles(Ws ws) {
+
+// Groups of records for the slot offsets: kRecBlocks blocks of the
+// preprocess, whose sums the blocks of the tile scan past the first add up.
+constexpr int kRecBlocks = 8, kRecGroup = kNT * kRecBlocks;
+
+// The tiles of the kNT records from b on (0 past the end): the block's last
+// running sum.
+__device__ __forceinline__ uint32_t block_tiles(const Ws &ws, int64_t b) {
+  return b < ws.n_rec ? ws.rec_cnt[min(b + kNT, (int64_t)ws.n_rec) - 1] : 0u;
+}
+
+__global__ __launch_bounds__(kScanNT) void k_scan_tiles(Ws ws, int n_groups) {
+  if (blockIdx.x > 0) {
+    // one lane per preprocess block: the words lie 1 KB apart
+    const int b = (blockIdx.x - 1) * kScanNT + threadIdx.x;
+    uint32_t s = block_tiles(ws, (int64_t)b * kNT);
+#pragma unroll
+    for (int o = 1; o < kRecBlocks; o <<= 1) s += (uint32_t)__shfl_xor((int)s, o);
+    if (b % kRecBlocks == 0 && b / kRecBlocks < n_groups) ws.scan_part[b / kRecBlocks] = s;
+    return;
+  }
   __shared__ uint32_t lw[kScanNT / kWave];
   __shared__ unsigned long long carry_s;
   __shared__ uint32_t nlong_s, nhuge_s;
+  __shared__ uint32_t bk[kOrderBuckets];
   if (threadIdx.x == 0) { carry_s = 0; nlong_s = 0; nhuge_s = 0; }
+  if (threadIdx.x < kOrderBuckets) bk[threadIdx.x] = 0u;
   __syncthreads();
   for (int base = 0; base < ws.n_tiles; base += kScanNT * kScanPer) {
     const int i0 = base + threadIdx.x * kScanPer;
@@ -355,6 +384,7 @@ __global__ __launch_bounds__(kScanNT) void k_scan_tiles(Ws ws) {
         ws.tile_count[i] = 0;
         ws.tile_count_ns[i] = 0;
         ws.tile_fill[i] = vs[k];
+        if (ws.tile_order) atomicAdd(&bk[order_bucket((uint32_t)(e - s))], 1u);
       }
       pos += v[k];
     }
@@ -374,19 +404,10 @@ __global__ __launch_bounds__(kScanNT) void k_scan_tiles(Ws ws) {
     // grid, dispatched in block order, starts its heaviest tiles first and
     // ends on light ones; the order within a bucket is whatever the atomics
     // give (each tile's results do not depend on it)
-    __shared__ uint32_t bk[kOrderBuckets];
-    if (threadIdx.x < kOrderBuckets) bk[threadIdx.x] = 0u;
-    __syncthreads();
-    for (int i = threadIdx.x; i < ws.n_tiles; i += kScanNT)
-      atomicAdd(&bk[order_bucket(ws.ranges[i].y - ws.ranges[i].x)], 1u);
-    __syncthreads();
-    if (threadIdx.x == 0) {
-      uint32_t run = 0u;
-      for (int b = 0; b < kOrderBuckets; b++) {
-        const uint32_t c = bk[b];
-        bk[b] = run;
-        run += c;
-      }
+    // (the last round's barriers stand between the counts and here)
+    if (threadIdx.x < kOrderBuckets) {
+      const uint32_t c = bk[threadIdx.x];
+      bk[threadIdx.x] = wave_incl_scan_u32(c) - c;
     }
     __syncthreads();
     for (int i = threadIdx.x; i < ws.n_tiles; i += kScanNT)
@@ -535,19 +556,6 @@ __global__ __launch_bounds__(kNT) void k_fill_keys(Ws ws) {
 }
 
 constexpr int kSortCap = 8192;
-
-// Wave-wide inclusive prefix sum of a u32 (DPP row_shr 1, 2, 4, 8 within
-// rows, then row_bcast:15 and row_bcast:31 across rows).  Packed 16-bit
-// fields scan independently while no field total exceeds 0xffff.
-__device__ __forceinline__ uint32_t wave_incl_scan_u32(uint32_t x) {
-  x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x111, 0xf, 0xf, false);
-  x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x112, 0xf, 0xf, false);
-  x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x114, 0xf, 0xf, false);
-  x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x118, 0xf, 0xf, false);
-  x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x142, 0xa, 0xf, false);
-  x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x143, 0xc, 0xf, false);
-  return x;
-}
 
 // One round of a merge sort over n keys held as sorted runs of `width`
 // keys in `in`: each pair of neighbouring runs is merged into `out` (an odd
@@ -789,44 +797,36 @@ __launch_bounds__(NT) void k_sort_tiles(Ws ws, int lo_n, int hi_n, int queue) {
   }
 }
 
-// Device-wide exclusive scan of rec_cnt -> rec_off (3 phases).
-constexpr int kRecPer = 8, kRecBlock = kNT * kRecPer;
-__global__ __launch_bounds__(kNT) void k_rec_scan_a(Ws ws) {
+// Records' slot offsets: the exclusive sums of their tile counts over all
+// records.  The preprocess leaves sums within its blocks, the tile scan adds
+// up the groups of kRecGroup records; what is left is one pass over the
+// records, in which each block adds up the groups before its own (at most
+// 1024 blocks, so that this stays linear in the groups).  Scanning the counts
+// themselves took three launches of 26 + 8 + 50 us at 12.3 M records, this
+// one takes 26 us (98 MB).
+__global__ __launch_bounds__(kNT) void k_scan_records(Ws ws, int n_groups, int per) {
   __shared__ uint32_t lw[kNT / kWave];
-  const int64_t i0 = (int64_t)blockIdx.x * kRecBlock + threadIdx.x * kRecPer;
-  uint32_t s = 0;
-  for (int k = 0; k < kRecPer; k++)
-    if (i0 + k < ws.n_rec) s += ws.rec_cnt[i0 + k];
-  uint32_t tot;
-  block_exclusive_scan<kNT>(s, lw, &tot);
-  if (threadIdx.x == 0) ws.scan_part[blockIdx.x] = tot;
-}
-__global__ __launch_bounds__(1024) void k_rec_scan_b(Ws ws, int nb) {
-  __shared__ uint32_t lw[1024 / kWave];
-  uint32_t carry = 0;
-  for (int base = 0; base < nb; base += 1024) {
-    const int i = base + threadIdx.x;
-    const uint32_t v = i < nb ? ws.scan_part[i] : 0u;
-    uint32_t tot;
-    const uint32_t ex = block_exclusive_scan<1024>(v, lw, &tot);
-    if (i < nb) ws.scan_part[i] = carry + ex;
-    carry += tot;
+  const int g0 = blockIdx.x * per, g1 = min(g0 + per, n_groups);
+  if (g0 >= n_groups) return;
+  uint32_t s = 0, base;
+  for (int g = threadIdx.x; g < g0; g += kNT) s += ws.scan_part[g];
+  block_exclusive_scan<kNT>(s, lw, &base);
+  for (int g = g0; g < g1; g++) {
+    uint32_t before[kRecBlocks], sum[kRecBlocks];
+#pragma unroll
+    for (int k = 0; k < kRecBlocks; k++) {
+      const int64_t b = ((int64_t)g * kRecBlocks + k) * kNT, r = b + threadIdx.x;
+      before[k] = threadIdx.x > 0 && r < ws.n_rec ? ws.rec_cnt[r - 1] : 0u;
+      sum[k] = block_tiles(ws, b);
+    }
+#pragma unroll
+    for (int k = 0; k < kRecBlocks; k++) {
+      const int64_t r = ((int64_t)g * kRecBlocks + k) * kNT + threadIdx.x;
+      if (r < ws.n_rec) ws.rec_off[r] = base + before[k];
+      base += sum[k];
+    }
   }
-  if (threadIdx.x == 0) ws.rec_off[ws.n_rec] = carry;
-}
-__global__ __launch_bounds__(kNT) void k_rec_scan_c(Ws ws) {
-  __shared__ uint32_t lw[kNT / kWave];
-  const int64_t i0 = (int64_t)blockIdx.x * kRecBlock + threadIdx.x * kRecPer;
-  uint32_t v[kRecPer], s = 0;
-  for (int k = 0; k < kRecPer; k++) {
-    v[k] = (i0 + k < ws.n_rec) ? ws.rec_cnt[i0 + k] : 0u;
-    s += v[k];
-  }
-  uint32_t pos = ws.scan_part[blockIdx.x] + block_exclusive_scan<kNT>(s, lw, nullptr);
-  for (int k = 0; k < kRecPer; k++) {
-    if (i0 + k < ws.n_rec) ws.rec_off[i0 + k] = pos;
-    pos += v[k];
-  }
+  if (g1 == n_groups && threadIdx.x == 0) ws.rec_off[ws.n_rec] = base;
 }
 
 __global__ void k_debug_copy(Ws ws, float *records, int32_t *rect) {
@@ -873,7 +873,8 @@ hipError_t launch_preprocess(const Ws &ws, hipStream_t st) {
 
 
 hipError_t launch_scan_tiles(const Ws &ws, hipStream_t st) {
-  hipLaunchKernelGGL(k_scan_tiles, dim3(1), dim3(kScanNT), 0, st, ws);
+  const int ng = ws.slots ? (int)rec_scan_blocks(ws.n_rec) : 0;
+  hipLaunchKernelGGL(k_scan_tiles, dim3(1 + blocks_for((int64_t)ng * kRecBlocks, kScanNT)), dim3(kScanNT), 0, st, ws, ng);
   return hipGetLastError();
 }
 
@@ -913,15 +914,14 @@ hipError_t launch_sort_tiles(const Ws &ws, hipStream_t st) {
 }
 
 hipError_t launch_scan_records(const Ws &ws, hipStream_t st) {
-  const int nb = (int)blocks_for(ws.n_rec, kRecBlock);
-  if (nb == 0) return launch_fill_u32(ws.rec_off, 0u, 1, st);
-  hipLaunchKernelGGL(k_rec_scan_a, dim3(nb), dim3(kNT), 0, st, ws);
-  hipLaunchKernelGGL(k_rec_scan_b, dim3(1), dim3(1024), 0, st, ws, nb);
-  hipLaunchKernelGGL(k_rec_scan_c, dim3(nb), dim3(kNT), 0, st, ws);
+  const int ng = (int)rec_scan_blocks(ws.n_rec);
+  if (ng == 0) return launch_fill_u32(ws.rec_off, 0u, 1, st);
+  const int per = (ng + 1023) / 1024;
+  hipLaunchKernelGGL(k_scan_records, dim3(blocks_for(ng, per)), dim3(kNT), 0, st, ws, ng, per);
   return hipGetLastError();
 }
 
-int64_t rec_scan_blocks(int64_t n_rec) { return (n_rec + kRecBlock - 1) / kRecBlock; }
+int64_t rec_scan_blocks(int64_t n_rec) { return (n_rec + kRecGroup - 1) / kRecGroup; }
 
 hipError_t launch_debug_copy(const Ws &ws, float *records, int32_t *rect, hipStream_t st) {
   if (ws.n_rec == 0) return hipSuccess;

@@ -88,10 +88,11 @@ struct Ws {
   float4 *recA;                // [n_rec][3]: (mx,my,qa,qb) (qc,o,z,R) (c0,c1,c2,r)
   float4 *recB;                // [n_rec]: (px, py, learnable, 0)
   uint2 *rect;                 // [n_rec]: tx0|ty0<<16, tx1|ty1<<16 (tx0 > tx1: culled)
-  uint32_t *rec_cnt;           // [n_rec] tiles per record
+  uint32_t *rec_cnt;           // [n_rec] tiles of the records up to and with this one, from
+                               // its preprocess block's first (plans with slots)
   uint32_t *zbits;             // [n_rec] FP32 bits of the centre depth (the sort key's high word)
-  uint32_t *rec_off;           // [n_rec + 1] exclusive scan of rec_cnt
-  uint32_t *scan_part;         // [scan blocks + 1]
+  uint32_t *rec_off;           // [n_rec + 1] the record's first slot (backward passes)
+  uint32_t *scan_part;         // [record groups + 1] tiles of each group's records
   // per tile
   uint32_t *tile_count;        // [n_tiles] pairs of record groups with a shared tile box
   uint32_t *tile_count_ns;     // [n_tiles] pairs of the other groups
@@ -179,16 +180,25 @@ __device__ __forceinline__ int wave_max_i(int x) {
              max(__builtin_amdgcn_readlane(x, 32), __builtin_amdgcn_readlane(x, 48)));
 }
 
+// Wave-wide inclusive prefix sum of a u32 (DPP row_shr 1, 2, 4, 8 within
+// rows, then row_bcast:15 and row_bcast:31 across rows).  Packed 16-bit
+// fields scan independently while no field total exceeds 0xffff.
+__device__ __forceinline__ uint32_t wave_incl_scan_u32(uint32_t x) {
+  x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x111, 0xf, 0xf, false);
+  x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x112, 0xf, 0xf, false);
+  x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x114, 0xf, 0xf, false);
+  x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x118, 0xf, 0xf, false);
+  x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x142, 0xa, 0xf, false);
+  x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x143, 0xc, 0xf, false);
+  return x;
+}
+
 // Exclusive scan of one uint32 per thread over a block of NT threads.
 template <int NT>
 __device__ __forceinline__ uint32_t block_exclusive_scan(uint32_t v, uint32_t *lds_waves,
                                                          uint32_t *total) {
   const int l = lane_id(), w = threadIdx.x / kWave;
-  uint32_t x = v;
-  for (int o = 1; o < kWave; o <<= 1) {
-    uint32_t y = __shfl_up(x, o);
-    if (l >= o) x += y;
-  }
+  const uint32_t x = wave_incl_scan_u32(v);
   if (l == kWave - 1) lds_waves[w] = x;
   __syncthreads();
   uint32_t base = 0, tot = 0;
