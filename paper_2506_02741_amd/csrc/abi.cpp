@@ -227,6 +227,7 @@ void make_ws(vtgs_plan *p) {
   w.n_pairs = reinterpret_cast<unsigned long long *>(b + p->r_hdr.off + 8);
   w.iter = reinterpret_cast<uint32_t *>(b + p->r_hdr.off + 16);
   w.n_long = reinterpret_cast<uint32_t *>(b + p->r_hdr.off + 24);
+  w.n_wide = reinterpret_cast<uint32_t *>(b + p->r_hdr.off + 32);
   w.long_tiles = at<uint32_t>(b, p->r_long);
   w.tile_order = p->tile_order ? at<uint32_t>(b, p->r_order) : nullptr;
   char *d = b + p->r_desc.off;

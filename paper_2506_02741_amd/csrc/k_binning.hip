@@ -51,27 +51,39 @@ __device__ __forceinline__ void unpack_rect(uint2 rc, int &x0, int &y0, int &x1,
   x0 = rc.x & 0xffff; y0 = rc.x >> 16; x1 = rc.y & 0xffff; y1 = rc.y >> 16;
 }
 
+__device__ __forceinline__ uint2 pack_rect(int x0, int y0, int x1, int y1) {
+  return make_uint2((uint32_t)x0 | ((uint32_t)y0 << 16), (uint32_t)x1 | ((uint32_t)y1 << 16));
+}
+
 // Tiles of a shared box: one per lane.  64 stride-1 records span 5-6 tiles of
 // 16 in two or three rows, stride-2 records 9-10 in two or three, so a limit
 // of 24 had left most waves of a stride-2 map to per-pair atomics: serving
 // track batches 570 -> 273 us (preprocess) and 576 -> 104 us (fill), 5 views
 // over 8 stride-1 keyframes 440 -> 412 and 243 -> 113.
 constexpr int kBoxMax = 64;
+// Tiles of a group's box for its counters in LDS: a group that does not share
+// a box (a few large rectangles among it, or it goes on in the next row of
+// the image) still issues one atomic per tile, not per pair.  Pair by pair,
+// groups next to the camera plane queue for the same few tiles: 134 K such
+// records among 2 M cost the preprocess 60 us and the fill 100 us.
+constexpr int kMidBox = 512;
 
 // Tiles covered by a wave's rectangles (a group of 64 consecutive records).
 // When the whole wave belongs to one view and its rectangles fit in a
 // bounding box of at most kBoxMax tiles, box tile j (row-major) is owned by
 // lane j: the lanes count their tiles in LDS counters, and lane j issues the
 // global atomic of tile j, so one instruction serves the whole box.
-// Otherwise (mixed views or a large box) each lane adds to its own tiles'
-// counters alone.
+// Otherwise the group's records of up to kLaneTiles tiles are counted in LDS
+// if their box has at most kMidBox tiles, else (mixed views, or a larger box)
+// by the lanes that stand at the same tile together.
 struct WaveBox {
   int bx0, by0, nx, area;
   int src;  // a lane with a rectangle (when shared): its view is the box's
   bool shared;
 };
 
-__device__ __forceinline__ WaveBox wave_box(bool has, int view, int x0, int y0, int x1, int y1) {
+__device__ __forceinline__ WaveBox wave_box(bool has, int view, int x0, int y0, int x1, int y1,
+                                            int most) {
   WaveBox b;
   const int vmin = wave_min_i(has ? view : 0x7fffffff);
   const int vmax = wave_max_i(has ? view : -1);
@@ -80,7 +92,7 @@ __device__ __forceinline__ WaveBox wave_box(bool has, int view, int x0, int y0, 
   const int bx1 = wave_max_i(has ? x1 : -1), by1 = wave_max_i(has ? y1 : -1);
   b.nx = bx1 - b.bx0 + 1;
   const long area = vmax < 0 ? 0 : (long)b.nx * (long)(by1 - b.by0 + 1);
-  b.shared = vmax >= 0 && vmin == vmax && area <= kBoxMax;
+  b.shared = vmax >= 0 && vmin == vmax && area <= most;
   b.area = b.shared ? (int)area : 0;
   b.src = (int)__builtin_ctzll(ballot64(has) | (1ull << 63));
   return b;
@@ -91,70 +103,151 @@ __device__ __forceinline__ WaveBox wave_box(bool has, int view, int x0, int y0, 
 // executes a wave's accesses in that order.
 __device__ __forceinline__ void lds_order() { asm volatile("" ::: "memory"); }
 
-// Lane j's box tile (row-major in the box) as a tile index of the box's
-// view (tiles_x btx, first tile btb); lanes past the box get a tile of the
-// box's first row, unused.
-__device__ __forceinline__ int box_tile_of_lane(const WaveBox &b, int btx, int btb) {
-  const int j = lane_id(), nx = max(b.nx, 1);
+// Box tile j (row-major in the box) as a tile index of the box's view (tiles_x
+// btx, first tile btb); tiles past the box are unused.
+__device__ __forceinline__ int box_tile(const WaveBox &b, int j, int btx, int btb) {
+  const int nx = max(b.nx, 1);
   const int q = j / nx;
   return btb + (b.by0 + q) * btx + (b.bx0 + (j - q * nx));
 }
 
-// Lane j of a shared box: the number of the wave's rectangles covering box
-// tile j (0 past the box).  Every lane adds one to the counter of each box
-// tile its rectangle covers, in the wave's own LDS row `cnt` (kBoxMax).
-__device__ __forceinline__ uint32_t box_counts(const WaveBox &b, bool has, int x0, int y0, int x1,
-                                               int y1, uint32_t *cnt) {
-  const int j = lane_id();
-  if (j < kBoxMax) cnt[j] = 0u;
+// The numbers of the wave's rectangles covering each box tile, in the wave's
+// own LDS row `cnt`.
+__device__ __forceinline__ void box_counts(const WaveBox &b, bool has, int x0, int y0, int x1, int y1,
+                                           uint32_t *cnt) {
+  for (int j = lane_id(); j < b.area; j += kWave) cnt[j] = 0u;
   lds_order();
   if (has) {
     for (int ty = y0; ty <= y1; ty++)
       for (int tx = x0; tx <= x1; tx++) atomicAdd(&cnt[(ty - b.by0) * b.nx + (tx - b.bx0)], 1u);
   }
   lds_order();
-  const uint32_t mine = j < b.area ? cnt[j] : 0u;
-  lds_order();
-  return mine;
 }
 
 // Rectangles of a group without a shared box: a lane walks a small one by
-// itself; one of more than kLaneTiles tiles (a Gaussian close to the view's
-// camera plane covers thousands) is walked by the whole wave, 64 tiles at a
-// time, one such lane after the other.  A lane alone issues an atomic per
-// tile, in the fill each with the wait for its old value, while 63 lanes
-// idle: with 2,400 such records among the 2 M of a section of 10 stride-2
-// keyframes, most of them over all 3,225 tiles of a 1200x680 view, the
-// preprocess took 1.89 ms and the fill 4.60 ms, now 0.19 and 0.32 (what is
-// left is the 7.8 M atomics themselves).  The line lies where a wave of 64
-// such rectangles, walked one after the other, would take as long as its
-// lanes side by side.
+// itself, one atomic per tile.  One of more than kLaneTiles tiles (a Gaussian
+// close to the view's camera plane covers thousands) goes into a list of its
+// own: it adds to its tiles' counts as the ends of its rows in a difference
+// array over the tile indexes, which the tile scan sums up, and its pairs are
+// stored tile by tile (fill_wide), at the ends of the tiles' lists.
+// Measured on a section of 10 stride-2 keyframes in a 1200x680 view (3,225
+// tiles), 2,400 of whose 2 M records cover more than 64 tiles, most of them
+// all: preprocess and fill take 0.19 + 0.30 ms with the wave walking such a
+// rectangle together, an atomic per pair (1.89 + 4.60 ms with its lane
+// alone), 0.08 + 0.04 ms with the list and the counters of kMidBox.  The line:
+// a listed record costs a test per tile of the plan (1.2 ns in all for 3,225
+// tiles), its pairs in a lane's walk 30 ps each; at 64 the list is still no
+// slower with eight views in the plan.
 constexpr int kLaneTiles = 64;
 
-// One rectangle of the wave walked by all lanes, lane j taking tiles j, j +
-// 64, .. in row-major order, U of them per call f(tile[U], n) with the view's
-// tile indexes (the first n are the lane's), so that f can keep U round trips
-// in flight.
-template <int U, typename F>
-__device__ __forceinline__ void wave_tiles(int x0, int y0, int x1, int y1, int tiles_x, int t0, F f) {
-  const int nx = x1 - x0 + 1, ny = y1 - y0 + 1;
-  const int dq = kWave / nx, dr = kWave - dq * nx;
-  int q = lane_id() / nx, r = lane_id() - q * nx;
-  while (q < ny) {
-    int tile[U], n = 0;
-#pragma unroll
-    for (int u = 0; u < U; u++) {
-      tile[u] = t0 + (y0 + q) * tiles_x + (x0 + r);
-      n += q < ny ? 1 : 0;
-      q += dq;
-      r += dr;
-      if (r >= nx) { r -= nx; q++; }
+// The lanes standing at the same tile as this one: the first of them, their
+// number and this lane's rank among them (all lanes of the wave call this;
+// `on` where a lane stands at a tile).
+struct SameTile {
+  int first;
+  uint32_t n, rank;
+};
+__device__ __forceinline__ SameTile same_tile(bool on, int t) {
+  SameTile s = {0, 0u, 0u};
+  unsigned long long todo = ballot64(on);
+  while (todo) {
+    const int src = (int)__builtin_ctzll(todo);
+    const bool mine = on && t == __builtin_amdgcn_readlane(t, src);
+    const unsigned long long m = ballot64(mine);
+    if (mine) {
+      s.first = src;
+      s.n = (uint32_t)__popcll(m);
+      s.rank = (uint32_t)__popcll(m & lanemask_lt());
     }
-    f(tile, n);
+    todo &= ~m;
+  }
+  return s;
+}
+
+// One lane's walk over the tiles of its rectangle, row by row.
+struct TileWalk {
+  int tx, ty;
+  __device__ __forceinline__ void next(int x0, int x1) {
+    if (++tx > x1) { tx = x0; ty++; }
+  }
+};
+
+__device__ __forceinline__ bool is_wide(bool has, int x0, int y0, int x1, int y1) {
+  return has && (x1 - x0 + 1) * (y1 - y0 + 1) > kLaneTiles;
+}
+
+// The list: (record, depth bits, rectangle) in the buffer of the tile sort's
+// runs, which is free until then.
+__device__ __forceinline__ uint4 *wide_list(const Ws &ws) {
+  return reinterpret_cast<uint4 *>(ws.keys_tmp);
+}
+__device__ __forceinline__ int64_t wide_cap(const Ws &ws) { return ws.cap / 2; }
+
+// The wave's wide records into the list (records past its capacity are left
+// out: each has more than kLaneTiles pairs, so the pass is over the pair
+// capacity anyway; it counts its pairs and leaves all lists empty) and their rows into
+// the difference array, one interval for all rows of a rectangle as wide as
+// the view.
+__device__ __forceinline__ void add_wide(const Ws &ws, bool wide, int r, uint32_t zbits, int x0, int y0,
+                                         int x1, int y1, int tiles_x, int t0) {
+  const unsigned long long m = ballot64(wide);
+  if (!m) return;
+  uint32_t first = 0u;
+  if (lane_id() == 0) first = atomicAdd(ws.n_wide, (uint32_t)__popcll(m));
+  first = (uint32_t)__builtin_amdgcn_readlane((int)first, 0);
+  if (!wide) return;
+  const int64_t i = (int64_t)first + __popcll(m & lanemask_lt());
+  const uint2 rc = pack_rect(x0, y0, x1, y1);
+  if (i < wide_cap(ws)) wide_list(ws)[i] = make_uint4((uint32_t)r, zbits, rc.x, rc.y);
+  const bool full = x0 == 0 && x1 == tiles_x - 1;
+  const int rows = full ? 1 : y1 - y0 + 1, len = full ? (y1 - y0 + 1) * tiles_x : x1 - x0 + 1;
+  for (int q = 0; q < rows; q++) {
+    // (rectangles over all of the view begin and end at the same two tiles)
+    const int a = t0 + (y0 + q) * tiles_x + x0, b = a + len;
+    const SameTile sa = same_tile(true, a), sb = same_tile(b < ws.n_tiles, b);
+    if (sa.rank == 0u) atomicAdd(ws.tile_fill + a, sa.n);
+    if (b < ws.n_tiles && sb.rank == 0u) atomicSub(ws.tile_fill + b, sb.n);
   }
 }
 
-__device__ __forceinline__ int lane_value(int v, int src) { return __builtin_amdgcn_readlane(v, src); }
+// The wide records' keys, at the ends of the lists of the tiles that they
+// cover: a wave takes a tile, its lanes the list's records, 64 at a time, U
+// of these chunks in flight.
+template <int U>
+__device__ __forceinline__ void fill_wide(const Ws &ws, int wave, int n_waves) {
+  const uint32_t n = ws.n_wide[1];
+  if (n == 0u || (int64_t)n > wide_cap(ws)) return;
+  for (int t = wave; t < ws.n_tiles; t += n_waves) {
+    const uint2 rg = ws.ranges[t];
+    int lo = 0, hi = ws.n_views - 1;
+    while (lo < hi) {
+      const int mid = (lo + hi + 1) >> 1;
+      if (ws.views[mid].tile_base <= t) lo = mid; else hi = mid - 1;
+    }
+    const uint32_t r0 = ws.views[lo].rec_base, r1 = lo + 1 < ws.n_views ? ws.views[lo + 1].rec_base : ws.n_rec;
+    const int tiles_x = ws.views[lo].tiles_x, at = t - ws.views[lo].tile_base;
+    const int ty = at / tiles_x, tx = at - ty * tiles_x;
+    uint32_t left = rg.y - rg.x;
+    for (uint32_t c = 0; c < n && left; c += U * kWave) {
+      uint4 e[U];
+#pragma unroll
+      for (int u = 0; u < U; u++) e[u] = wide_list(ws)[min(c + u * kWave + lane_id(), n - 1)];
+#pragma unroll
+      for (int u = 0; u < U; u++) {
+        int x0, y0, x1, y1;
+        unpack_rect(make_uint2(e[u].z, e[u].w), x0, y0, x1, y1);
+        const bool in = c + u * kWave + lane_id() < n && e[u].x >= r0 && e[u].x < r1 && x0 <= tx &&
+                        tx <= x1 && y0 <= ty && ty <= y1;
+        const unsigned long long m = ballot64(in);
+        const uint32_t rank = (uint32_t)__popcll(m & lanemask_lt());
+        if (in && rank < left)
+          ws.keys[rg.x + (left - 1u - rank)] = ((unsigned long long)e[u].y << 32) | (e[u].x - r0);
+        left -= min(left, (uint32_t)__popcll(m));
+      }
+    }
+  }
+}
+
 
 // A load through a descriptor's pointer, which addresses global memory:
 // read as such (the compiler cannot tell, and would issue a flat load).
@@ -172,7 +265,7 @@ __global__ __launch_bounds__(kNT) void k_preprocess(Ws ws) {
   // in LDS (plans with more segments search them in global memory, plans
   // with one take it without a search)
   __shared__ int seg_start[kSegLds];
-  __shared__ uint32_t box_cnt[kNT / kWave][kBoxMax];
+  __shared__ uint32_t box_cnt[kNT / kWave][kMidBox];
   __shared__ uint32_t slot_cnt[kNT / kWave];
   const bool seg_lds = ws.n_segs > 1 && ws.n_segs <= kSegLds;
   if (seg_lds) {
@@ -184,7 +277,8 @@ __global__ __launch_bounds__(kNT) void k_preprocess(Ws ws) {
   if (r == 0) *ws.iter += 1u;
   const bool active = r < ws.n_rec;
   bool has = false;
-  int view = 0, x0 = 1, y0 = 0, x1 = 0, y1 = 0, tiles_x = 1, tile_base = 0;
+  int view = 0, x0 = 1, y0 = 0, x1 = 0, y1 = 0, tiles_x = 1, tiles_y = 1, tile_base = 0;
+  uint32_t zbits = 0u;
   if (active) {
     int seg = 0;
     if (seg_lds) {
@@ -203,12 +297,13 @@ __global__ __launch_bounds__(kNT) void k_preprocess(Ws ws) {
     // the descriptor fields used below, read up front (not inside branches)
     const float kfx = kf.fx, kfy = kf.fy, kcx = kf.cx, kcy = kf.cy;
     const float vfx = vw.fx, vfy = vw.fy, vcx = vw.cx, vcy = vw.cy;
-    const int kwidth = kf.width, vtiles_y = vw.tiles_y, kn = kf.n, klearn = kf.learnable;
+    const int kwidth = kf.width, kn = kf.n, klearn = kf.learnable;
     const uint32_t *kpix = kf.pix;
     const float *kdepth = kf.depth, *kradius = kf.radius, *kopa = kf.opacity, *kcolor = kf.color;
     const float *vpose = vw.pose, *kpose = kf.pose;
     view = sg.view;
     tiles_x = vw.tiles_x;
+    tiles_y = vw.tiles_y;
     tile_base = vw.tile_base;
     const int i = r - sg.rec_start;
     // the two poses and every per-Gaussian load issued together, before the
@@ -252,7 +347,7 @@ __global__ __launch_bounds__(kNT) void k_preprocess(Ws ws) {
           const float fx0 = fmaxf(floorf((mx - R) * invB), 0.f);
           const float fy0 = fmaxf(floorf((my - R) * invB), 0.f);
           const float fx1 = fminf(floorf((mx + R) * invB), (float)(tiles_x - 1));
-          const float fy1 = fminf(floorf((my + R) * invB), (float)(vtiles_y - 1));
+          const float fy1 = fminf(floorf((my + R) * invB), (float)(tiles_y - 1));
           if (!(fx0 > fx1 || fy0 > fy1)) {
             x0 = (int)fx0; y0 = (int)fy0; x1 = (int)fx1; y1 = (int)fy1;
             has = true;
@@ -266,9 +361,10 @@ __global__ __launch_bounds__(kNT) void k_preprocess(Ws ws) {
     A[2] = make_float4(c0, c1, c2, rad);
     ws.recB[r] = make_float4(px, py, learn, 0.f);
     if (!has) { x0 = 1; y0 = 0; x1 = 0; y1 = 0; }
-    ws.rect[r] = make_uint2((uint32_t)x0 | ((uint32_t)y0 << 16), (uint32_t)x1 | ((uint32_t)y1 << 16));
+    ws.rect[r] = pack_rect(x0, y0, x1, y1);
     // the depth again on its own, so that the key fill reads 4 B per record
-    ws.zbits[r] = __float_as_uint(pz);
+    zbits = __float_as_uint(pz);
+    ws.zbits[r] = zbits;
     // the segment's relative pose, kept for the gradient gathers
     if (i == 0) {
 #pragma unroll
@@ -282,7 +378,8 @@ __global__ __launch_bounds__(kNT) void k_preprocess(Ws ws) {
     const uint32_t before = block_exclusive_scan<kNT>(n, slot_cnt, nullptr);
     if (active) ws.rec_cnt[r] = before + n;
   }
-  const WaveBox box = wave_box(has, view, x0, y0, x1, y1);
+  const WaveBox box = wave_box(has, view, x0, y0, x1, y1, kBoxMax);
+  uint32_t *cnt = box_cnt[threadIdx.x / kWave];
   if (box.shared) {
     // the lanes count their tiles in the wave's LDS row, then lane j adds
     // box tile j's count with one atomic instruction for the whole box.
@@ -290,26 +387,32 @@ __global__ __launch_bounds__(kNT) void k_preprocess(Ws ws) {
     // the tile index takes that view's geometry from a lane that does.
     const int btx = __builtin_amdgcn_readlane(tiles_x, box.src);
     const int btb = __builtin_amdgcn_readlane(tile_base, box.src);
-    const int mt = box_tile_of_lane(box, btx, btb);
-    const uint32_t mine = box_counts(box, has, x0, y0, x1, y1, box_cnt[threadIdx.x / kWave]);
+    const int mt = box_tile(box, lane_id(), btx, btb);
+    box_counts(box, has, x0, y0, x1, y1, cnt);
+    const uint32_t mine = lane_id() < box.area ? cnt[lane_id()] : 0u;
     // the atomic's old value is the group's first position in box tile j:
     // kept for the key fill, which then claims nothing for this group
     if (mine) ws.wave_off[(r & ~(kWave - 1)) + lane_id()] = atomicAdd(ws.tile_count + mt, mine);
   } else {
     // the other groups' pairs take the positions after them, claimed by
     // the key fill
-    const bool wide = has && (x1 - x0 + 1) * (y1 - y0 + 1) > kLaneTiles;
-    if (has && !wide) {
-      uint32_t *cnt = ws.tile_count_ns + tile_base;
-      for (int ty = y0; ty <= y1; ty++)
-        for (int tx = x0; tx <= x1; tx++) atomicAdd(cnt + ty * tiles_x + tx, 1u);
+    const bool wide = is_wide(has, x0, y0, x1, y1), small = has && !wide;
+    const WaveBox mid = wave_box(small, view, x0, y0, x1, y1, kMidBox);
+    if (mid.shared) {
+      const int btx = __builtin_amdgcn_readlane(tiles_x, mid.src);
+      const int btb = __builtin_amdgcn_readlane(tile_base, mid.src);
+      box_counts(mid, small, x0, y0, x1, y1, cnt);
+      for (int j = lane_id(); j < mid.area; j += kWave)
+        if (cnt[j]) atomicAdd(ws.tile_count_ns + box_tile(mid, j, btx, btb), cnt[j]);
+    } else {
+      const int last = small ? y1 : -1;
+      for (TileWalk w = {x0, y0}; ballot64(w.ty <= last); w.next(x0, x1)) {
+        const int t = tile_base + w.ty * tiles_x + w.tx;
+        const SameTile s = same_tile(w.ty <= last, t);
+        if (w.ty <= last && s.rank == 0u) atomicAdd(ws.tile_count_ns + t, s.n);
+      }
     }
-    for (unsigned long long m = ballot64(wide); m; m &= m - 1ull) {
-      const int src = (int)__builtin_ctzll(m);
-      wave_tiles<1>(lane_value(x0, src), lane_value(y0, src), lane_value(x1, src),
-                    lane_value(y1, src), lane_value(tiles_x, src), lane_value(tile_base, src),
-                    [&](const int (&t)[1], int) { atomicAdd(ws.tile_count_ns + t[0], 1u); });
-    }
+    add_wide(ws, wide, r, zbits, x0, y0, x1, y1, tiles_x, tile_base);
   }
 }
 
@@ -356,7 +459,11 @@ __global__ __launch_bounds__(kScanNT) void k_scan_tiles(Ws ws, int n_groups) {
   __shared__ unsigned long long carry_s;
   __shared__ uint32_t nlong_s, nhuge_s;
   __shared__ uint32_t bk[kOrderBuckets];
-  if (threadIdx.x == 0) { carry_s = 0; nlong_s = 0; nhuge_s = 0; }
+  __shared__ uint32_t wide_s;
+  if (threadIdx.x == 0) { carry_s = 0; nlong_s = 0; nhuge_s = 0; wide_s = 0; }
+  // wide records: their rows' ends in tile_fill become counts per tile
+  const uint32_t n_wide = ws.n_wide[0];
+  const unsigned long long cap = (int64_t)n_wide <= wide_cap(ws) ? ws.cap : 0;
   if (threadIdx.x < kOrderBuckets) bk[threadIdx.x] = 0u;
   __syncthreads();
   for (int base = 0; base < ws.n_tiles; base += kScanNT * kScanPer) {
@@ -368,14 +475,28 @@ __global__ __launch_bounds__(kScanNT) void k_scan_tiles(Ws ws, int n_groups) {
       sum += v[k];
     }
     uint32_t tot;
+    if (n_wide) {
+      uint32_t d[kScanPer], ds = 0;
+      for (int k = 0; k < kScanPer; k++) {
+        d[k] = (i0 + k < ws.n_tiles) ? ws.tile_fill[i0 + k] : 0u;
+        ds += d[k];
+      }
+      uint32_t w = wide_s;
+      w += block_exclusive_scan<kScanNT>(ds, lw, &tot);
+      for (int k = 0; k < kScanPer; k++) {
+        w += d[k];
+        if (i0 + k < ws.n_tiles) { v[k] += w; sum += w; }
+      }
+      if (threadIdx.x == 0) wide_s += tot;
+    }
     const uint32_t ex = block_exclusive_scan<kScanNT>(sum, lw, &tot);
     const unsigned long long c = carry_s;
     unsigned long long pos = c + ex;
     for (int k = 0; k < kScanPer; k++) {
       const int i = i0 + k;
       if (i < ws.n_tiles) {
-        const unsigned long long s = pos < (unsigned long long)ws.cap ? pos : ws.cap;
-        const unsigned long long e = pos + v[k] < (unsigned long long)ws.cap ? pos + v[k] : ws.cap;
+        const unsigned long long s = pos < cap ? pos : cap;
+        const unsigned long long e = pos + v[k] < cap ? pos + v[k] : cap;
         ws.ranges[i] = make_uint2((uint32_t)s, (uint32_t)e);
         if (e - s > (unsigned long long)kMidSort)
           ws.long_tiles[(uint32_t)ws.n_tiles - 1u - atomicAdd(&nhuge_s, 1u)] = i;
@@ -397,6 +518,8 @@ __global__ __launch_bounds__(kScanNT) void k_scan_tiles(Ws ws, int n_groups) {
     if (carry_s > (unsigned long long)ws.cap) atomicOr(ws.flags, kFlagCapacity);
     ws.n_long[0] = nlong_s;
     ws.n_long[1] = nhuge_s;
+    ws.n_wide[0] = 0u;
+    ws.n_wide[1] = n_wide;
   }
   if (ws.tile_order) {
     // longest lists first: tiles bucketed by list length (two buckets per
@@ -426,14 +549,19 @@ __global__ __launch_bounds__(kScanNT) void k_scan_tiles(Ws ws, int n_groups) {
 // all of those with atomics here.  Either way a tile's keys land in no fixed
 // order; the sort that follows fixes it.
 template <int RPT>
-__global__ __launch_bounds__(kNT) void k_fill_keys(Ws ws) {
+__global__ __launch_bounds__(kNT) void k_fill_keys(Ws ws, int rec_blocks) {
+  if ((int)blockIdx.x >= rec_blocks) {
+    constexpr int kWaves = kNT / kWave;
+    fill_wide<4>(ws, (blockIdx.x - rec_blocks) * kWaves + threadIdx.x / kWave,
+                 (gridDim.x - rec_blocks) * kWaves);
+    return;
+  }
   // the views' first records, tiles per row and first tiles, read by the
   // block at once beside its records' loads and then searched in LDS
   // (plans with more views search the descriptors in global memory, plans
   // with one read its descriptor without a search)
   __shared__ int3 vtab[kViewLds];
-  __shared__ uint32_t fill_cnt[kNT / kWave][kBoxMax], fill_base[kNT / kWave][kBoxMax],
-      fill_lim[kNT / kWave][kBoxMax];
+  __shared__ uint32_t fill_pos[kNT / kWave][kMidBox], fill_lim[kNT / kWave][kMidBox];
   const bool view_lds = ws.n_views > 1 && ws.n_views <= kViewLds;
   bool has[RPT];
   int x0[RPT], y0[RPT], x1[RPT], y1[RPT], tiles_x[RPT], tile_base[RPT], view[RPT];
@@ -479,11 +607,11 @@ __global__ __launch_bounds__(kNT) void k_fill_keys(Ws ws) {
   // lane j of a group with a shared box: box tile j's first position and
   // end
   WaveBox box[RPT];
-  uint32_t base[RPT], lim[RPT];
+  uint32_t base[RPT], end[RPT];
 #pragma unroll
   for (int k = 0; k < RPT; k++) {
-    box[k] = wave_box(has[k], view[k], x0[k], y0[k], x1[k], y1[k]);
-    base[k] = 0u; lim[k] = 0u;
+    box[k] = wave_box(has[k], view[k], x0[k], y0[k], x1[k], y1[k], kBoxMax);
+    base[k] = 0u; end[k] = 0u;
     if (!box[k].shared) continue;
     const int btx = __builtin_amdgcn_readlane(tiles_x[k], box[k].src);
     const int btb = __builtin_amdgcn_readlane(tile_base[k], box[k].src);
@@ -491,65 +619,64 @@ __global__ __launch_bounds__(kNT) void k_fill_keys(Ws ws) {
       // the group's first position in box tile j, claimed by the
       // preprocess (unused, and never written, where no rectangle of the
       // group covers the tile)
-      const uint2 rg = ws.ranges[box_tile_of_lane(box[k], btx, btb)];
+      const uint2 rg = ws.ranges[box_tile(box[k], lane_id(), btx, btb)];
       const int g0 = (blockIdx.x * RPT + k) * kNT + (threadIdx.x & ~(kWave - 1));
       base[k] = rg.x + ws.wave_off[g0 + lane_id()];
-      lim[k] = rg.y;
+      end[k] = rg.y;
     }
   }
-  // stores: lane j parks box tile j's first position and end in the wave's
-  // LDS row; every lane then takes a rank in each box tile its rectangle
-  // covers from that tile's LDS counter (in whatever order the lanes come:
-  // the sort fixes it).  Groups without a shared box claim and store pair
-  // by pair.
-  uint32_t *cnt = fill_cnt[threadIdx.x / kWave], *bs = fill_base[threadIdx.x / kWave],
-           *ls = fill_lim[threadIdx.x / kWave];
+  // stores: the next position and the end of each box tile's list lie in the
+  // wave's LDS row; every lane then takes a position in each box tile its
+  // rectangle covers (in whatever order the lanes come: the sort fixes it).
+  // Groups without a shared box claim their tiles' positions first, and those
+  // of no box store pair by pair.
+  uint32_t *pos = fill_pos[threadIdx.x / kWave], *lim = fill_lim[threadIdx.x / kWave];
 #pragma unroll
   for (int k = 0; k < RPT; k++) {
+    auto put = [&](const WaveBox &b) {
+      for (int ty = y0[k]; ty <= y1[k]; ty++)
+        for (int tx = x0[k]; tx <= x1[k]; tx++) {
+          const int j = (ty - b.by0) * b.nx + (tx - b.bx0);
+          const uint32_t at = atomicAdd(&pos[j], 1u);
+          if (at < lim[j]) ws.keys[at] = key[k];
+        }
+    };
     if (box[k].shared) {
-      const int j = lane_id();
-      if (j < kBoxMax) { cnt[j] = 0u; bs[j] = base[k]; ls[j] = lim[k]; }
+      pos[lane_id()] = base[k];
+      lim[lane_id()] = end[k];
       lds_order();
-      if (has[k]) {
-        for (int ty = y0[k]; ty <= y1[k]; ty++)
-          for (int tx = x0[k]; tx <= x1[k]; tx++) {
-            const int jj = (ty - box[k].by0) * box[k].nx + (tx - box[k].bx0);
-            const uint32_t pos = bs[jj] + atomicAdd(&cnt[jj], 1u);
-            if (pos < ls[jj]) ws.keys[pos] = key[k];
-          }
+      if (has[k]) put(box[k]);
+      lds_order();
+      continue;
+    }
+    const bool small = has[k] && !is_wide(has[k], x0[k], y0[k], x1[k], y1[k]);
+    const WaveBox mid = wave_box(small, view[k], x0[k], y0[k], x1[k], y1[k], kMidBox);
+    if (mid.shared) {
+      const int btx = __builtin_amdgcn_readlane(tiles_x[k], mid.src);
+      const int btb = __builtin_amdgcn_readlane(tile_base[k], mid.src);
+      box_counts(mid, small, x0[k], y0[k], x1[k], y1[k], pos);
+      // (the claims of four tiles per lane in flight)
+#pragma unroll 4
+      for (int j = lane_id(); j < mid.area; j += kWave) {
+        const uint32_t n = pos[j];
+        const int t = box_tile(mid, j, btx, btb);
+        const uint2 rg = ws.ranges[t];
+        if (n) pos[j] = rg.x + atomicAdd(ws.tile_fill + t, n);
+        lim[j] = rg.y;
       }
+      lds_order();
+      if (small) put(mid);
       lds_order();
     } else {
-      auto put = [&](int t, unsigned long long kv) {
-        const uint2 rg = ws.ranges[t];
-        const uint32_t pos = rg.x + atomicAdd(ws.tile_fill + t, 1u);
-        if (pos < rg.y) ws.keys[pos] = kv;
-      };
-      const bool wide = has[k] && (x1[k] - x0[k] + 1) * (y1[k] - y0[k] + 1) > kLaneTiles;
-      if (has[k] && !wide) {
-        for (int ty = y0[k]; ty <= y1[k]; ty++)
-          for (int tx = x0[k]; tx <= x1[k]; tx++) put(tile_base[k] + ty * tiles_x[k] + tx, key[k]);
-      }
-      for (unsigned long long m = ballot64(wide); m; m &= m - 1ull) {
-        const int src = (int)__builtin_ctzll(m);
-        const unsigned long long kv =
-            ((unsigned long long)(uint32_t)lane_value((int)(uint32_t)(key[k] >> 32), src) << 32) |
-            (uint32_t)lane_value((int)(uint32_t)key[k], src);
-        wave_tiles<4>(lane_value(x0[k], src), lane_value(y0[k], src), lane_value(x1[k], src),
-                      lane_value(y1[k], src), lane_value(tiles_x[k], src), lane_value(tile_base[k], src),
-                      [&](const int (&t)[4], int n) {
-                        uint2 rg[4];
-                        uint32_t at[4];
-#pragma unroll
-                        for (int u = 0; u < 4; u++)
-                          if (u < n) {
-                            rg[u] = ws.ranges[t[u]];
-                            at[u] = atomicAdd(ws.tile_fill + t[u], 1u);
-                          }
-#pragma unroll
-                        for (int u = 0; u < 4; u++)
-                          if (u < n && rg[u].x + at[u] < rg[u].y) ws.keys[rg[u].x + at[u]] = kv;
-                      });
+      const int last = small ? y1[k] : -1;
+      for (TileWalk w = {x0[k], y0[k]}; ballot64(w.ty <= last); w.next(x0[k], x1[k])) {
+        const bool on = w.ty <= last;
+        const int t = on ? tile_base[k] + w.ty * tiles_x[k] + w.tx : 0;
+        const SameTile s = same_tile(on, t);
+        uint32_t at = 0u;
+        if (on && s.rank == 0u) at = ws.ranges[t].x + atomicAdd(ws.tile_fill + t, s.n);
+        at = (uint32_t)__shfl((int)at, s.first) + s.rank;
+        if (on && at < ws.ranges[t].y) ws.keys[at] = key[k];
       }
     }
   }
@@ -756,6 +883,9 @@ __launch_bounds__(NT) void k_sort_tiles(Ws ws, int lo_n, int hi_n, int queue) {
   constexpr int CAP = NT * E;
   __shared__ SortLds<NT, E> S;
   const int count = queue ? (int)ws.n_long[queue - 1] : ws.n_tiles;
+  // the fill is done with its counters: cleared for the next pass's wide
+  // records
+  if (queue == 0 && threadIdx.x == 0 && blockIdx.x < ws.n_tiles) ws.tile_fill[blockIdx.x] = 0u;
   for (int q = blockIdx.x; q < count; q += gridDim.x) {
     const int tile = queue == 0 ? q : (int)ws.long_tiles[queue == 1 ? q : ws.n_tiles - 1 - q];
     // ranges are clamped to the capacity, and every position of a clamped
@@ -881,11 +1011,14 @@ hipError_t launch_scan_tiles(const Ws &ws, hipStream_t st) {
 hipError_t launch_fill_keys(const Ws &ws, hipStream_t st) {
   if (ws.n_rec == 0) return hipSuccess;
   // four records per thread once the grid holds several waves per SIMD
-  // at that rate (1,024 SIMDs)
+  // at that rate (1,024 SIMDs); then a wave per tile for the wide records
+  const unsigned wide = std::min(blocks_for(ws.n_tiles, kNT / kWave), 2048u);
   if (ws.n_rec >= (1 << 20)) {
-    hipLaunchKernelGGL(k_fill_keys<4>, dim3(blocks_for(ws.n_rec, 4 * kNT)), dim3(kNT), 0, st, ws);
+    const unsigned nb = blocks_for(ws.n_rec, 4 * kNT);
+    hipLaunchKernelGGL(k_fill_keys<4>, dim3(nb + wide), dim3(kNT), 0, st, ws, (int)nb);
   } else {
-    hipLaunchKernelGGL(k_fill_keys<1>, dim3(blocks_for(ws.n_rec, kNT)), dim3(kNT), 0, st, ws);
+    const unsigned nb = blocks_for(ws.n_rec, kNT);
+    hipLaunchKernelGGL(k_fill_keys<1>, dim3(nb + wide), dim3(kNT), 0, st, ws, (int)nb);
   }
   return hipGetLastError();
 }

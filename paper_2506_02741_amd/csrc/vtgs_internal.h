@@ -72,6 +72,7 @@ struct Ws {
   unsigned long long *n_pairs;
   uint32_t *iter;              // tracking iteration counter (bumped by preprocess)
   uint32_t *n_long;            // [2] tiles with lists for the mid and the huge-list sort
+  uint32_t *n_wide;            // [2] wide records of this pass, so far and (by the scan) in all
   uint32_t *long_tiles;        // [n_tiles] the queues, huge lists from the end (by the scan)
   uint32_t *tile_order;        // [n_tiles] compositing order, longest lists first (NULL: tile order)
   // descriptors
@@ -95,8 +96,9 @@ struct Ws {
   uint32_t *scan_part;         // [record groups + 1] tiles of each group's records
   // per tile
   uint32_t *tile_count;        // [n_tiles] pairs of record groups with a shared tile box
-  uint32_t *tile_count_ns;     // [n_tiles] pairs of the other groups
-  uint32_t *tile_fill;         // [n_tiles] next free list position of the other groups
+  uint32_t *tile_count_ns;     // [n_tiles] pairs of the other groups, but wide records
+  uint32_t *tile_fill;         // [n_tiles] next free list position of the other groups;
+                               // before the scan: ends of the wide records' rows
   uint32_t *wave_off;          // [n_rec rounded up to 64] per 64-record group, lane j: the
                                // group's first position in its box tile j (relative)
   uint2 *ranges;               // [n_tiles] (start, end)
