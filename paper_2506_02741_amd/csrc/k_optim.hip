@@ -174,22 +174,18 @@ __global__ __launch_bounds__(kUpdNT) void k_track_update(Ws ws, vtgs_track_cfg c
 
 // ---- Eq. 2 ----------------------------------------------------------------
 
-__global__ __launch_bounds__(kNT) void k_map_l1(Ws ws, vtgs_map_cfg cfg) {
-  __shared__ float lds[kNT / kWave];
-  const int v = blockIdx.y;
+// Eq. 2's L1 terms of 256 pixels of view v: their sums and the depth's
+// gradient.  The colours' gradient joins that of the SSIM (k_ssim_b).
+__device__ __forceinline__ void map_l1(const Ws &ws, const vtgs_map_cfg &cfg, int v, int block, float *lds) {
   const DevView &vw = ws.views[v];
   const int64_t Pv = (int64_t)vw.width * vw.height;
-  const int64_t lp = (int64_t)blockIdx.x * kNT + threadIdx.x;
+  const int64_t lp = (int64_t)block * kNT + threadIdx.x;
   const int64_t P = ws.P;
   float l1 = 0.f, ld = 0.f;
   if (lp < Pv) {
     const int64_t p = vw.pix_off + lp;
-    const float inv3 = 1.0f / (3.0f * (float)Pv), inv1 = 1.0f / (float)Pv;
-    for (int c = 0; c < 3; c++) {
-      const float r = vw.obs_rgb[c * Pv + lp] - ws.img[c * P + p];
-      l1 += fabsf(r);
-      ws.gimg[c * P + p] = -cfg.rho * sgnf(r) * inv3;
-    }
+    const float inv1 = 1.0f / (float)Pv;
+    for (int c = 0; c < 3; c++) l1 += fabsf(vw.obs_rgb[c * Pv + lp] - ws.img[c * P + p]);
     const float od = vw.obs_depth[lp];
     const float rd = od - ws.img[3 * P + p];
     const bool U = od > 0.f;
@@ -199,13 +195,26 @@ __global__ __launch_bounds__(kNT) void k_map_l1(Ws ws, vtgs_map_cfg cfg) {
   const float s1 = block_sum(l1, lds);
   const float s2 = block_sum(ld, lds);
   if (threadIdx.x == 0) {
-    float *o = ws.loss_part + 4 * ((int64_t)v * ws.loss_blocks + blockIdx.x);
+    float *o = ws.loss_part + 4 * ((int64_t)v * ws.loss_blocks + block);
     o[0] = s1;
     o[1] = s2;
   }
 }
 
-constexpr int kS = 16, kR = 5, kH = kS + 2 * kR;  // SSIM output tile, window radius
+// SSIM: 11-tap windows of radius kR.  The moments' kernel takes squares of kS
+// outputs; FP64 arithmetic bounds it (75% of its time on the vector units, 86
+// us for 5 views of 640x480), and blocks of 32 x 16 with four outputs a thread
+// kept too few waves in flight (128 us).
+constexpr int kS = 16, kR = 5, kH = kS + 2 * kR;
+// The gradient's kernel, bound by its reads of the FP64 maps and of LDS, takes
+// kSW x kSH outputs (and their rim, kTW x kTH): a thread sums four neighbouring
+// outputs of a row, then two of a column, so that each value is read once for
+// the outputs that share it, and the rows' sums take the LDS of the values
+// they came from (79 -> 68 us).  Every output still adds its taps in order.
+constexpr int kSW = 32, kSH = 16, kTW = kSW + 2 * kR, kTH = kSH + 2 * kR;
+constexpr int kGW = 4, kGH = 2;                       // a thread's outputs in a row, a column
+constexpr int kRowItems = kTH * (kSW / kGW);
+static_assert(kRowItems <= kNT && kSW * kSH == kNT * kGH, "one turn of the block per pass");
 
 __device__ __forceinline__ double gwin(int k) {
   // normalised 11-tap Gaussian, sigma 1.5: exp(-i^2 / 4.5) / sum, i = -5..5
@@ -222,10 +231,19 @@ __device__ __forceinline__ double gwin(int k) {
 // variances are differences of second moments and squared means of similar
 // size, which FP32 would leave with ~1e-5 relative error, and the gradient
 // combines the filtered partials with cancellation.
-__global__ __launch_bounds__(kNT) void k_ssim_a(Ws ws, int gx, int gy) {
+// Columns of the grid past the squares' take the L1 terms, 256 pixels each: 14
+// us here against 17 in a launch of their own for 5 views of 640x480, 1 against
+// 5 for one of 320x240.
+__global__ __launch_bounds__(kNT) void k_ssim_a(Ws ws, vtgs_map_cfg cfg, int gx, int gy) {
   __shared__ float xs[kH][kH], ys[kH][kH];
   __shared__ double hs[5][kH][kS];
   __shared__ float lds[kNT / kWave];
+  if ((int)blockIdx.x >= gx) {
+    const int64_t b = ((int64_t)blockIdx.z * gy + blockIdx.y) * (gridDim.x - gx) + (blockIdx.x - gx);
+    if (b < (int64_t)ws.loss_blocks * ws.n_views)
+      map_l1(ws, cfg, (int)(b / ws.loss_blocks), (int)(b % ws.loss_blocks), lds);
+    return;
+  }
   const int v = blockIdx.z / 3, c = blockIdx.z % 3;
   const DevView &vw = ws.views[v];
   const int W = vw.width, H = vw.height;
@@ -284,61 +302,103 @@ __global__ __launch_bounds__(kNT) void k_ssim_a(Ws ws, int gx, int gy) {
   if (threadIdx.x == 0) ws.ssim_part[((int64_t)blockIdx.z * gy + blockIdx.y) * gx + blockIdx.x] = s;
 }
 
-// dSSIM_mean/dx(p) = (1/P) [ (w*A)(p) + 2 x(p) (w*B)(p) + y(p) (w*Cov)(p) ]
+// dSSIM_mean/dx(p) = (1/P) [ (w*A)(p) + 2 x(p) (w*B)(p) + y(p) (w*Cov)(p) ],
+// and the L1 term's gradient
 __global__ __launch_bounds__(kNT) void k_ssim_b(Ws ws, vtgs_map_cfg cfg) {
-  __shared__ double ms[3][kH][kH];
-  __shared__ double hs[3][kH][kS];
+  union Lds {
+    double m[3][kTH][kTW];
+    double h[3][kTH][kSW];
+  };
+  __shared__ __attribute__((aligned(16))) Lds L;
   const int v = blockIdx.z / 3, c = blockIdx.z % 3;
   const DevView &vw = ws.views[v];
   const int W = vw.width, H = vw.height;
-  const int x0 = blockIdx.x * kS, y0 = blockIdx.y * kS;
+  const int x0 = blockIdx.x * kSW, y0 = blockIdx.y * kSH;
   if (x0 >= W || y0 >= H) return;
   const int64_t P = ws.P, Pv = (int64_t)W * H;
-  for (int i = threadIdx.x; i < kH * kH; i += kNT) {
-    const int yy = y0 - kR + i / kH, xx = x0 - kR + i % kH;
+  for (int i = threadIdx.x; i < kTH * kTW; i += kNT) {
+    const int r = i / kTW, t = i % kTW;
+    const int yy = y0 - kR + r, xx = x0 - kR + t;
     const bool in = xx >= 0 && xx < W && yy >= 0 && yy < H;
     const int64_t p = (int64_t)c * P + vw.pix_off + (int64_t)yy * W + xx;
-    for (int q = 0; q < 3; q++) ms[q][i / kH][i % kH] = in ? ws.ssim_map[q * 3 * P + p] : 0.0;
+#pragma unroll
+    for (int q = 0; q < 3; q++) L.m[q][r][t] = in ? ws.ssim_map[q * 3 * P + p] : 0.0;
   }
   __syncthreads();
-  for (int i = threadIdx.x; i < kH * kS; i += kNT) {
-    const int r = i / kS, cc = i % kS;
-    double a[3] = {0.0, 0.0, 0.0};
-    for (int k = 0; k < 2 * kR + 1; k++) {
-      const double w = gwin(k);
-      for (int q = 0; q < 3; q++) a[q] = fma(w, ms[q][r][cc + k], a[q]);
+  double a[3][kGW];
+  const int hr = threadIdx.x / (kSW / kGW), hc = threadIdx.x % (kSW / kGW) * kGW;
+  if (threadIdx.x < kRowItems) {
+#pragma unroll
+    for (int q = 0; q < 3; q++) {
+#pragma unroll
+      for (int j = 0; j < kGW; j++) a[q][j] = 0.0;
+#pragma unroll
+      for (int i = 0; i < kGW + 2 * kR; i++) {
+        const double m = L.m[q][hr][hc + i];
+#pragma unroll
+        for (int j = 0; j < kGW; j++) {
+          const int k = i - j;
+          if (k >= 0 && k <= 2 * kR) a[q][j] = fma(gwin(k), m, a[q][j]);
+        }
+      }
     }
-    for (int q = 0; q < 3; q++) hs[q][r][cc] = a[q];
   }
   __syncthreads();
-  const int lx = threadIdx.x % kS, ly = threadIdx.x / kS;
-  const int xx = x0 + lx, yy = y0 + ly;
-  if (xx >= W || yy >= H) return;
-  double f[3] = {0.0, 0.0, 0.0};
-  for (int k = 0; k < 2 * kR + 1; k++) {
-    const double w = gwin(k);
-    for (int q = 0; q < 3; q++) f[q] = fma(w, hs[q][ly + k][lx], f[q]);
+  if (threadIdx.x < kRowItems) {
+#pragma unroll
+    for (int q = 0; q < 3; q++)
+#pragma unroll
+      for (int j = 0; j < kGW; j++) L.h[q][hr][hc + j] = a[q][j];
   }
-  const int64_t lp = (int64_t)yy * W + xx;
-  const int64_t p = vw.pix_off + lp;
-  const double x = ws.img[c * P + p], y = vw.obs_rgb[c * Pv + lp];
-  const double g = (f[0] + 2.0 * x * f[1] + y * f[2]) / (double)Pv;
-  ws.gimg[c * P + p] = (float)((double)ws.gimg[c * P + p] - (double)cfg.tau * g / 3.0);
+  __syncthreads();
+  const int lx = threadIdx.x % kSW, ly = threadIdx.x / kSW * kGH;
+  double ff[kGH][3];
+#pragma unroll
+  for (int q = 0; q < 3; q++) {
+#pragma unroll
+    for (int j = 0; j < kGH; j++) ff[j][q] = 0.0;
+#pragma unroll
+    for (int i = 0; i < kGH + 2 * kR; i++) {
+      const double h = L.h[q][ly + i][lx];
+#pragma unroll
+      for (int j = 0; j < kGH; j++) {
+        const int k = i - j;
+        if (k >= 0 && k <= 2 * kR) ff[j][q] = fma(gwin(k), h, ff[j][q]);
+      }
+    }
+  }
+  const int xx = x0 + lx;
+  const float inv3 = 1.0f / (3.0f * (float)Pv);
+#pragma unroll
+  for (int j = 0; j < kGH; j++) {
+    const int yy = y0 + ly + j;
+    if (xx >= W || yy >= H) continue;
+    const double *f = ff[j];
+    const int64_t lp = (int64_t)yy * W + xx;
+    const int64_t p = vw.pix_off + lp;
+    const float xf = ws.img[c * P + p], yf = vw.obs_rgb[c * Pv + lp];
+    const float l1 = -cfg.rho * sgnf(yf - xf) * inv3;
+    const double x = xf, y = yf;
+    const double g = (f[0] + 2.0 * x * f[1] + y * f[2]) / (double)Pv;
+    ws.gimg[c * P + p] = (float)((double)l1 - (double)cfg.tau * g / 3.0);
+  }
 }
 
 __global__ __launch_bounds__(kNT) void k_map_loss_reduce(Ws ws, vtgs_map_cfg cfg, int gx, int gy,
-                                                         float *loss) {
+                                                         float *loss, int32_t *step) {
   __shared__ float lds[kNT / kWave];
   const int v = blockIdx.x;
   const DevView &vw = ws.views[v];
   const int64_t Pv = (int64_t)vw.width * vw.height;
   const int nb = (int)((Pv + kNT - 1) / kNT);
   float a = 0.f, b = 0.f, s = 0.f;
+#pragma unroll 4
   for (int i = threadIdx.x; i < nb; i += kNT) {
     const float *o = ws.loss_part + 4 * ((int64_t)v * ws.loss_blocks + i);
     a += o[0];
     b += o[1];
   }
+#pragma unroll 4
   for (int i = threadIdx.x; i < 3 * gx * gy; i += kNT) s += ws.ssim_part[(int64_t)v * 3 * gx * gy + i];
   a = block_sum(a, lds);
   b = block_sum(b, lds);
@@ -348,6 +408,8 @@ __global__ __launch_bounds__(kNT) void k_map_loss_reduce(Ws ws, vtgs_map_cfg cfg
                     cfg.sigma * b / (float)Pv;
     if (!__builtin_isfinite(L)) atomicOr(ws.flags, kFlagNonfinite);
     if (loss) loss[v] = L;
+    // one more step; the Adam kernel that follows reads it
+    if (v == 0) *step += 1;
   }
 }
 
@@ -558,8 +620,6 @@ __global__ __launch_bounds__(kNT) void k_kpose_update(Ws ws, vtgs_map_cfg cfg) {
   for (int c = 0; c < 12; c++) K.pose[c] = N[c];
 }
 
-__global__ void k_step_inc(int32_t *step) { *step += 1; }
-
 }  // namespace
 
 
@@ -574,17 +634,13 @@ hipError_t launch_track_update(const Ws &ws, const vtgs_track_cfg &cfg, float *l
   return hipGetLastError();
 }
 
-void ssim_grid(const Ws &ws, int *gx, int *gy) {
-  *gx = ws.ssim_gx;
-  *gy = ws.ssim_gy;
-}
-
 hipError_t launch_map_loss(const Ws &ws, const vtgs_map_cfg &cfg, hipStream_t st) {
-  int gx, gy;
-  ssim_grid(ws, &gx, &gy);
-  hipLaunchKernelGGL(k_map_l1, dim3(ws.loss_blocks, ws.n_views), dim3(kNT), 0, st, ws, cfg);
-  hipLaunchKernelGGL(k_ssim_a, dim3(gx, gy, 3 * ws.n_views), dim3(kNT), 0, st, ws, gx, gy);
-  hipLaunchKernelGGL(k_ssim_b, dim3(gx, gy, 3 * ws.n_views), dim3(kNT), 0, st, ws, cfg);
+  const int gx = ws.ssim_gx, gy = ws.ssim_gy;
+  const int l1_cols = (ws.loss_blocks + 3 * gy - 1) / (3 * gy);
+  hipLaunchKernelGGL(k_ssim_a, dim3(gx + l1_cols, gy, 3 * ws.n_views), dim3(kNT), 0, st, ws, cfg, gx,
+                     gy);
+  hipLaunchKernelGGL(k_ssim_b, dim3((gx * kS + kSW - 1) / kSW, (gy * kS + kSH - 1) / kSH, 3 * ws.n_views),
+                     dim3(kNT), 0, st, ws, cfg);
   return hipGetLastError();
 }
 
@@ -599,10 +655,8 @@ hipError_t launch_gather(const Ws &ws, int max_n, hipStream_t st) {
 
 hipError_t launch_map_update(const Ws &ws, const vtgs_map_cfg &cfg, int32_t *step, float *loss,
                                int max_n, hipStream_t st) {
-  int gx, gy;
-  ssim_grid(ws, &gx, &gy);
-  hipLaunchKernelGGL(k_map_loss_reduce, dim3(ws.n_views), dim3(kNT), 0, st, ws, cfg, gx, gy, loss);
-  hipLaunchKernelGGL(k_step_inc, dim3(1), dim3(1), 0, st, step);
+  hipLaunchKernelGGL(k_map_loss_reduce, dim3(ws.n_views), dim3(kNT), 0, st, ws, cfg, ws.ssim_gx,
+                     ws.ssim_gy, loss, step);
   if (max_n > 0 && ws.n_kf > 0) {
     hipLaunchKernelGGL(k_map_adam, dim3((max_n + kNT - 1) / kNT, ws.n_kf), dim3(kNT), 0, st, ws,
                        cfg, (const int32_t *)step);
