@@ -244,7 +244,7 @@ void make_ws(vtgs_plan *p) {
   w.P = p->P;
   w.cap = p->cap;
   w.recA = at<float4>(b, p->r_recA);
-  w.recB = at<float4>(b, p->r_recB);
+  w.recB = at<float2>(b, p->r_recB);
   w.rect = at<uint2>(b, p->r_rect);
   w.rec_cnt = at<uint32_t>(b, p->r_rec_cnt);
   w.zbits = at<uint32_t>(b, p->r_zbits);

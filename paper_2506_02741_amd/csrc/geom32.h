@@ -8,9 +8,8 @@
 
 namespace vtgs {
 
-// M = Tv * Tk^-1 = [Rv Rk^T | tv - (Rv Rk^T) tk], fixed summation order.
 // Relative pose M = T_v T_k^-1 (3x4, world->camera poses with orthonormal
-// rotations, so T_k^-1 = [R_k^T | -R_k^T t_k]) in a fixed FP32 order.
+// rotations) = [Rv Rk^T | tv - (Rv Rk^T) tk] in a fixed FP32 order.
 __device__ __forceinline__ void relative_pose(const float *Tv, const float *Tk, float *M) {
   float tv[12], tk[12];
 #pragma unroll
@@ -25,6 +24,14 @@ __device__ __forceinline__ void relative_pose(const float *Tv, const float *Tk, 
   for (int i = 0; i < 3; i++)
     M[4 * i + 3] = tv[4 * i + 3] -
                    ((M[4 * i + 0] * tk[3] + M[4 * i + 1] * tk[7]) + M[4 * i + 2] * tk[11]);
+}
+
+// Row i of it alone (tv: row i of T_v), by the same operations.
+__device__ __forceinline__ void relative_pose_row(const float *tv, const float *tk, float *m) {
+#pragma unroll
+  for (int j = 0; j < 3; j++)
+    m[j] = (tv[0] * tk[4 * j + 0] + tv[1] * tk[4 * j + 1]) + tv[2] * tk[4 * j + 2];
+  m[3] = tv[3] - ((m[0] * tk[3] + m[1] * tk[7]) + m[2] * tk[11]);
 }
 
 // A keyframe pixel (u, v) with z-depth d, back-projected through the

@@ -82,19 +82,40 @@ struct WaveBox {
   bool shared;
 };
 
+// Lane-wise minimum or maximum of two 16-bit fields over the wave, as a
+// uniform value: row_ror 8, 4, 2, 1 within rows, then row_bcast:15 and :31.
+typedef unsigned short u16x2 __attribute__((ext_vector_type(2)));
+template <bool kMax>
+__device__ __forceinline__ uint32_t wave_pair(uint32_t x) {
+  auto step = [&](uint32_t y) {
+    const u16x2 a = __builtin_bit_cast(u16x2, x), b = __builtin_bit_cast(u16x2, y);
+    x = __builtin_bit_cast(uint32_t, kMax ? __builtin_elementwise_max(a, b) : __builtin_elementwise_min(a, b));
+  };
+  step((uint32_t)__builtin_amdgcn_update_dpp((int)x, (int)x, 0x128, 0xf, 0xf, false));
+  step((uint32_t)__builtin_amdgcn_update_dpp((int)x, (int)x, 0x124, 0xf, 0xf, false));
+  step((uint32_t)__builtin_amdgcn_update_dpp((int)x, (int)x, 0x122, 0xf, 0xf, false));
+  step((uint32_t)__builtin_amdgcn_update_dpp((int)x, (int)x, 0x121, 0xf, 0xf, false));
+  step((uint32_t)__builtin_amdgcn_update_dpp((int)x, (int)x, 0x142, 0xa, 0xf, false));
+  step((uint32_t)__builtin_amdgcn_update_dpp((int)x, (int)x, 0x143, 0xc, 0xf, false));
+  return (uint32_t)__builtin_amdgcn_readlane((int)x, kWave - 1);
+}
+
+// (views do not decrease from lane to lane; a lane past the last record gives
+// that record's)
 __device__ __forceinline__ WaveBox wave_box(bool has, int view, int x0, int y0, int x1, int y1,
                                             int most) {
   WaveBox b;
-  const int vmin = wave_min_i(has ? view : 0x7fffffff);
-  const int vmax = wave_max_i(has ? view : -1);
-  b.bx0 = wave_min_i(has ? x0 : 0x7fffffff);
-  b.by0 = wave_min_i(has ? y0 : 0x7fffffff);
-  const int bx1 = wave_max_i(has ? x1 : -1), by1 = wave_max_i(has ? y1 : -1);
-  b.nx = bx1 - b.bx0 + 1;
-  const long area = vmax < 0 ? 0 : (long)b.nx * (long)(by1 - b.by0 + 1);
-  b.shared = vmax >= 0 && vmin == vmax && area <= most;
+  const unsigned long long any = ballot64(has);
+  const bool one_view = __builtin_amdgcn_readlane(view, 0) == __builtin_amdgcn_readlane(view, kWave - 1);
+  const uint2 rc = pack_rect(x0, y0, x1, y1);
+  const uint32_t lo = wave_pair<false>(has ? rc.x : 0xffffffffu), hi = wave_pair<true>(has ? rc.y : 0u);
+  b.bx0 = (int)(lo & 0xffffu);
+  b.by0 = (int)(lo >> 16);
+  b.nx = (int)(hi & 0xffffu) - b.bx0 + 1;
+  const long area = any ? (long)b.nx * (long)((int)(hi >> 16) - b.by0 + 1) : 0;
+  b.shared = any && one_view && area <= most;
   b.area = b.shared ? (int)area : 0;
-  b.src = (int)__builtin_ctzll(ballot64(has) | (1ull << 63));
+  b.src = (int)__builtin_ctzll(any | (1ull << 63));
   return b;
 }
 
@@ -256,121 +277,178 @@ __device__ __forceinline__ T gload(const T *p, int64_t i) {
   return ((const __attribute__((address_space(1))) T *)p)[i];
 }
 
-constexpr int kSegLds = 1024;  // segment starts the preprocess keeps in LDS
+// The same through the scalar cache, where the address is the wave's: for
+// what no kernel writes while this one runs (descriptors' constants, poses).
+template <class T>
+__device__ __forceinline__ T uload(const T *p) {
+  return *(const __attribute__((address_space(4))) T *)p;
+}
+
 constexpr int kViewLds = 256;  // view descriptors the key fill keeps in LDS
 
-__global__ __launch_bounds__(kNT) void k_preprocess(Ws ws) {
+// A record's view and tiles.
+struct Projected {
+  int view, x0, y0, x1, y1, tiles_x, tile_base;
+  uint32_t zbits;
+  bool has;
+};
+
+// Column and row of pixel index pix in an image of width w: the quotient from
+// a reciprocal, off by one at most (pix < 2^24, w >= 8: its error is below
+// 0.4), then put right.
+__device__ __forceinline__ void pixel_of(uint32_t pix, uint32_t w, int &u, int &v) {
+  uint32_t q, r;
+  if (w < 8u || ballot64(pix >= 1u << 24)) {
+    q = pix / w;
+    r = pix % w;
+  } else {
+    q = (uint32_t)((float)pix * __builtin_amdgcn_rcpf((float)w));
+    r = pix - q * w;
+    if ((int)r < 0) { r += w; q--; }
+    if (r >= w) { r -= w; q++; }
+  }
+  u = (int)r;
+  v = (int)q;
+}
+
+// Record r of segment seg.  kOneSeg: the segment is the block's (and the lanes
+// past the last record run along): its descriptors and pointers stay in scalar
+// registers, and three lanes form a row each of the relative pose.  Otherwise
+// every lane reads its own.
+template <bool kOneSeg>
+__device__ __forceinline__ Projected project_record(const Ws &ws, int seg, int r, bool active) {
+  Projected o = {0, 1, 0, 0, 0, 1, 0, 0u, false};
+  const DevSeg &sg = ws.segs[seg];
+  const int kfi = kOneSeg ? uload(&sg.kf) : sg.kf, rec_start = kOneSeg ? uload(&sg.rec_start) : sg.rec_start;
+  o.view = kOneSeg ? uload(&sg.view) : sg.view;
+  const DevKF &kf = ws.kfs[kfi];
+  const DevView &vw = ws.views[o.view];
+  // the descriptor fields used below, read up front (not inside branches)
+  auto get = [](const auto &x) { return kOneSeg ? uload(&x) : x; };
+  const float kfx = get(kf.fx), kfy = get(kf.fy), kcx = get(kf.cx), kcy = get(kf.cy);
+  const float vfx = get(vw.fx), vfy = get(vw.fy), vcx = get(vw.cx), vcy = get(vw.cy);
+  const int kwidth = get(kf.width), kn = get(kf.n), klearn = get(kf.learnable);
+  const uint32_t *kpix = get(kf.pix);
+  const float *kdepth = get(kf.depth), *kradius = get(kf.radius), *kopa = get(kf.opacity),
+              *kcolor = get(kf.color);
+  const float *vpose = get(vw.pose), *kpose = get(kf.pose);
+  const int tiles_y = get(vw.tiles_y);
+  o.tiles_x = get(vw.tiles_x);
+  o.tile_base = get(vw.tile_base);
+  // (a lane past the last record reads the segment's last one)
+  const int i = min(r - rec_start, kn - 1);
+  // the two poses and every per-Gaussian load issued together, before the
+  // arithmetic (and before any store, which the compiler could not move
+  // them past)
+  const uint32_t pix = gload(kpix, i);
+  const float d = gload(kdepth, i);
+  const float rad = gload(kradius, i);
+  const float opa = gload(kopa, i);
+  const float c0 = gload(kcolor, i), c1 = gload(kcolor, (int64_t)kn + i), c2 = gload(kcolor, 2 * (int64_t)kn + i);
+  float M[12];
+  if (kOneSeg) {
+    float tv[4], tk[12];
+    const int row = min(lane_id() & 3, 2);
+#pragma unroll
+    for (int c = 0; c < 4; c++) tv[c] = gload(vpose, 4 * row + c);
+#pragma unroll
+    for (int c = 0; c < 12; c++) tk[c] = uload(kpose + c);
+    float m[4];
+    relative_pose_row(tv, tk, m);
+#pragma unroll
+    for (int c = 0; c < 12; c++)
+      M[c] = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(m[c % 4]), c / 4));
+  } else {
+    float tv[12], tk[12];
+#pragma unroll
+    for (int c = 0; c < 12; c++) { tv[c] = gload(vpose, c); tk[c] = gload(kpose, c); }
+    relative_pose(tv, tk, M);
+  }
+  int u, v;
+  pixel_of(pix, (uint32_t)kwidth, u, v);
+  // back-projection of the tied depth pixel (keyframe camera), into the view
+  float px, py, pz;
+  backproject_move(M, kfx, kfy, kcx, kcy, u, v, d, px, py, pz);
+  float mx = 0.f, my = 0.f, qa = 0.f, qb = 0.f, qc = 0.f, R = 0.f;
+  if (active && pz > ws.znear) {
+    mx = vfx * (px / pz) + vcx;
+    my = vfy * (py / pz) + vcy;
+    const float a = vfx / pz, b = vfy / pz;
+    const float zz = pz * pz;
+    const float jx = -(vfx * px) / zz, jy = -(vfy * py) / zz;
+    const float r2 = rad * rad;
+    const float s11 = r2 * (a * a + jx * jx) + ws.lowpass;
+    const float s12 = r2 * (jx * jy);
+    const float s22 = r2 * (b * b + jy * jy) + ws.lowpass;
+    const float det = s11 * s22 - s12 * s12;
+    if (det > 0.f) {
+      const float mid = 0.5f * (s11 + s22);
+      const float lmax = mid + sqrtf(fmaxf(0.f, mid * mid - det));
+      R = ceilf(sqrtf(ws.qcut * lmax));
+      if (__builtin_isfinite(mx) && __builtin_isfinite(my) && __builtin_isfinite(R)) {
+        qa = s22 / det; qb = -s12 / det; qc = s11 / det;
+        const float invB = 1.0f / (float)ws.tile;
+        const float fx0 = fmaxf(floorf((mx - R) * invB), 0.f);
+        const float fy0 = fmaxf(floorf((my - R) * invB), 0.f);
+        const float fx1 = fminf(floorf((mx + R) * invB), (float)(o.tiles_x - 1));
+        const float fy1 = fminf(floorf((my + R) * invB), (float)(tiles_y - 1));
+        if (!(fx0 > fx1 || fy0 > fy1)) {
+          o.x0 = (int)fx0; o.y0 = (int)fy0; o.x1 = (int)fx1; o.y1 = (int)fy1;
+          o.has = true;
+        }
+      }
+    }
+  }
+  if (!active) return o;
+  o.zbits = __float_as_uint(pz);
+  float4 *A = ws.recA + 3 * (int64_t)r;
+  A[0] = make_float4(mx, my, qa, qb);
+  // (R >= 0: its sign bit is free)
+  A[1] = make_float4(qc, opa, pz, __builtin_copysignf(R, klearn ? 1.f : -1.f));
+  A[2] = make_float4(c0, c1, c2, rad);
+  if (o.has) ws.recB[r] = make_float2(px, py);
+  ws.rect[r] = pack_rect(o.x0, o.y0, o.x1, o.y1);
+  // the depth again on its own, so that the key fill reads 4 B per record
+  ws.zbits[r] = o.zbits;
+  // the segment's relative pose, kept for the gradient gathers
+  if (r == rec_start) {
+#pragma unroll
+    for (int c = 0; c < 12; c++) ws.segs[seg].M[c] = M[c];
+  }
+  return o;
+}
+
+// Bound by its stores, some 75 bytes a record (1.2 GB with the loads for 5
+// views over 8 keyframes of 640x480, 12.3 M records: 290 us, a copy's 260).
+// Nearly every block lies within one segment: then the descriptors are scalar
+// loads and operands instead of 24 pose loads and 64-bit addresses per lane
+// (410 us, the arithmetic alone 226; 2 M records: 82 -> 63).
+__global__ __attribute__((amdgpu_waves_per_eu(8))) __launch_bounds__(kNT) void k_preprocess(Ws ws) {
   const int r = blockIdx.x * kNT + threadIdx.x;
-  // the segments' first records, read by the block at once, then searched
-  // in LDS (plans with more segments search them in global memory, plans
-  // with one take it without a search)
-  __shared__ int seg_start[kSegLds];
   __shared__ uint32_t box_cnt[kNT / kWave][kMidBox];
   __shared__ uint32_t slot_cnt[kNT / kWave];
-  const bool seg_lds = ws.n_segs > 1 && ws.n_segs <= kSegLds;
-  if (seg_lds) {
-    for (int k = threadIdx.x; k < ws.n_segs; k += kNT) seg_start[k] = ws.segs[k].rec_start;
-    __syncthreads();
+  const bool active = r < ws.n_rec;
+  Projected o = {0, 1, 0, 0, 0, 1, 0, 0u, false};
+  if (ws.n_rec > 0) {
+    // the segment of the block's first record, found with scalar loads, and
+    // the first record of the next one
+    int lo = 0, hi = ws.n_segs - 1;
+    const int b0 = blockIdx.x * kNT;
+    while (lo < hi) {
+      const int mid = (lo + hi + 1) >> 1;
+      if (uload(&ws.segs[mid].rec_start) <= b0) lo = mid; else hi = mid - 1;
+    }
+    if (lo == ws.n_segs - 1 || uload(&ws.segs[lo + 1].rec_start) >= min(b0 + kNT, ws.n_rec))
+      o = project_record<true>(ws, lo, r, active);
+    else
+      o = project_record<false>(ws, find_seg(ws, min(r, ws.n_rec - 1)), r, active);
   }
   // one more pass of the pipeline: the tracking update writes its loss at
   // this index, so a captured iteration needs no per-iteration argument
   if (r == 0) *ws.iter += 1u;
-  const bool active = r < ws.n_rec;
-  bool has = false;
-  int view = 0, x0 = 1, y0 = 0, x1 = 0, y1 = 0, tiles_x = 1, tiles_y = 1, tile_base = 0;
-  uint32_t zbits = 0u;
-  if (active) {
-    int seg = 0;
-    if (seg_lds) {
-      int lo = 0, hi = ws.n_segs - 1;
-      while (lo < hi) {
-        const int mid = (lo + hi + 1) >> 1;
-        if (seg_start[mid] <= r) lo = mid; else hi = mid - 1;
-      }
-      seg = lo;
-    } else {
-      seg = find_seg(ws, r);
-    }
-    const DevSeg &sg = ws.segs[seg];
-    const DevKF &kf = ws.kfs[sg.kf];
-    const DevView &vw = ws.views[sg.view];
-    // the descriptor fields used below, read up front (not inside branches)
-    const float kfx = kf.fx, kfy = kf.fy, kcx = kf.cx, kcy = kf.cy;
-    const float vfx = vw.fx, vfy = vw.fy, vcx = vw.cx, vcy = vw.cy;
-    const int kwidth = kf.width, kn = kf.n, klearn = kf.learnable;
-    const uint32_t *kpix = kf.pix;
-    const float *kdepth = kf.depth, *kradius = kf.radius, *kopa = kf.opacity, *kcolor = kf.color;
-    const float *vpose = vw.pose, *kpose = kf.pose;
-    view = sg.view;
-    tiles_x = vw.tiles_x;
-    tiles_y = vw.tiles_y;
-    tile_base = vw.tile_base;
-    const int i = r - sg.rec_start;
-    // the two poses and every per-Gaussian load issued together, before the
-    // arithmetic (and before any store, which the compiler could not move
-    // them past)
-    const uint32_t pix = gload(kpix, i);
-    const float d = gload(kdepth, i);
-    const float rad = gload(kradius, i);
-    const float o = gload(kopa, i);
-    const float c0 = gload(kcolor, i), c1 = gload(kcolor, (int64_t)kn + i),
-                c2 = gload(kcolor, 2 * (int64_t)kn + i);
-    float tv[12], tk[12];
-#pragma unroll
-    for (int c = 0; c < 12; c++) { tv[c] = gload(vpose, c); tk[c] = gload(kpose, c); }
-    float M[12];
-    relative_pose(tv, tk, M);
-    const float learn = klearn ? 1.f : 0.f;
-    const int u = (int)(pix % (uint32_t)kwidth), v = (int)(pix / (uint32_t)kwidth);
-    // back-projection of the tied depth pixel (keyframe camera), into the view
-    float px, py, pz;
-    backproject_move(M, kfx, kfy, kcx, kcy, u, v, d, px, py, pz);
-    float mx = 0.f, my = 0.f, qa = 0.f, qb = 0.f, qc = 0.f, R = 0.f;
-    if (pz > ws.znear) {
-      mx = vfx * (px / pz) + vcx;
-      my = vfy * (py / pz) + vcy;
-      const float a = vfx / pz, b = vfy / pz;
-      const float zz = pz * pz;
-      const float jx = -(vfx * px) / zz, jy = -(vfy * py) / zz;
-      const float r2 = rad * rad;
-      const float s11 = r2 * (a * a + jx * jx) + ws.lowpass;
-      const float s12 = r2 * (jx * jy);
-      const float s22 = r2 * (b * b + jy * jy) + ws.lowpass;
-      const float det = s11 * s22 - s12 * s12;
-      if (det > 0.f) {
-        const float mid = 0.5f * (s11 + s22);
-        const float lmax = mid + sqrtf(fmaxf(0.f, mid * mid - det));
-        R = ceilf(sqrtf(ws.qcut * lmax));
-        if (__builtin_isfinite(mx) && __builtin_isfinite(my) && __builtin_isfinite(R)) {
-          qa = s22 / det; qb = -s12 / det; qc = s11 / det;
-          const float invB = 1.0f / (float)ws.tile;
-          const float fx0 = fmaxf(floorf((mx - R) * invB), 0.f);
-          const float fy0 = fmaxf(floorf((my - R) * invB), 0.f);
-          const float fx1 = fminf(floorf((mx + R) * invB), (float)(tiles_x - 1));
-          const float fy1 = fminf(floorf((my + R) * invB), (float)(tiles_y - 1));
-          if (!(fx0 > fx1 || fy0 > fy1)) {
-            x0 = (int)fx0; y0 = (int)fy0; x1 = (int)fx1; y1 = (int)fy1;
-            has = true;
-          }
-        }
-      }
-    }
-    float4 *A = ws.recA + 3 * (int64_t)r;
-    A[0] = make_float4(mx, my, qa, qb);
-    A[1] = make_float4(qc, o, pz, R);
-    A[2] = make_float4(c0, c1, c2, rad);
-    ws.recB[r] = make_float4(px, py, learn, 0.f);
-    if (!has) { x0 = 1; y0 = 0; x1 = 0; y1 = 0; }
-    ws.rect[r] = pack_rect(x0, y0, x1, y1);
-    // the depth again on its own, so that the key fill reads 4 B per record
-    zbits = __float_as_uint(pz);
-    ws.zbits[r] = zbits;
-    // the segment's relative pose, kept for the gradient gathers
-    if (i == 0) {
-#pragma unroll
-      for (int c = 0; c < 12; c++) ws.segs[seg].M[c] = M[c];
-    }
-  }
+  const bool has = o.has;
+  const int view = o.view, x0 = o.x0, y0 = o.y0, x1 = o.x1, y1 = o.y1, tiles_x = o.tiles_x,
+            tile_base = o.tile_base;
   if (ws.slots) {
     // plans with gradients per Gaussian: the records' tiles, summed up to
     // and with this one over the block, for the slot offsets
@@ -412,7 +490,7 @@ __global__ __launch_bounds__(kNT) void k_preprocess(Ws ws) {
         if (w.ty <= last && s.rank == 0u) atomicAdd(ws.tile_count_ns + t, s.n);
       }
     }
-    add_wide(ws, wide, r, zbits, x0, y0, x1, y1, tiles_x, tile_base);
+    add_wide(ws, wide, r, o.zbits, x0, y0, x1, y1, tiles_x, tile_base);
   }
 }
 
@@ -583,6 +661,7 @@ __global__ __launch_bounds__(kNT) void k_fill_keys(Ws ws, int rec_blocks) {
 #pragma unroll
   for (int k = 0; k < RPT; k++) {
     const int r = (blockIdx.x * RPT + k) * kNT + threadIdx.x;
+    const int rr = min(r, ws.n_rec - 1);
     const bool active = r < ws.n_rec;
     unpack_rect(rc[k], x0[k], y0[k], x1[k], y1[k]);
     has[k] = active && x0[k] <= x1[k];
@@ -592,13 +671,13 @@ __global__ __launch_bounds__(kNT) void k_fill_keys(Ws ws, int rec_blocks) {
       int lo = 0, hi = ws.n_views - 1;
       while (lo < hi) {
         const int mid = (lo + hi + 1) >> 1;
-        if (vtab[mid].x <= r) lo = mid; else hi = mid - 1;
+        if (vtab[mid].x <= rr) lo = mid; else hi = mid - 1;
       }
-      view[k] = active ? lo : 0;
+      view[k] = lo;
       const int3 e = vtab[view[k]];
       rec_base = e.x; tiles_x[k] = e.y; tile_base[k] = e.z;
     } else {
-      view[k] = active ? find_view_by_record(ws, r) : 0;
+      view[k] = find_view_by_record(ws, rr);
       const DevView &vw = ws.views[view[k]];
       rec_base = vw.rec_base; tiles_x[k] = vw.tiles_x; tile_base[k] = vw.tile_base;
     }
@@ -967,7 +1046,7 @@ __global__ void k_debug_copy(Ws ws, float *records, int32_t *rect) {
                  c = ws.recA[3 * (int64_t)r + 2];
     float *o = records + 12 * (int64_t)r;
     o[0] = a.x; o[1] = a.y; o[2] = a.z; o[3] = a.w;
-    o[4] = b.x; o[5] = b.y; o[6] = b.z; o[7] = b.w;
+    o[4] = b.x; o[5] = b.y; o[6] = b.z; o[7] = fabsf(b.w);
     o[8] = c.x; o[9] = c.y; o[10] = c.z; o[11] = c.w;
   }
   if (rect) {
@@ -1010,12 +1089,13 @@ hipError_t launch_scan_tiles(const Ws &ws, hipStream_t st) {
 
 hipError_t launch_fill_keys(const Ws &ws, hipStream_t st) {
   if (ws.n_rec == 0) return hipSuccess;
-  // four records per thread once the grid holds several waves per SIMD
-  // at that rate (1,024 SIMDs); then a wave per tile for the wide records
+  // two records per thread once the grid holds several waves per SIMD at
+  // that rate (1,024 SIMDs; 12.3 M records: 112 us with four, 102 with two, 103
+  // with one, 2 M: 40, 41, 44); then a wave per tile for the wide records
   const unsigned wide = std::min(blocks_for(ws.n_tiles, kNT / kWave), 2048u);
   if (ws.n_rec >= (1 << 20)) {
-    const unsigned nb = blocks_for(ws.n_rec, 4 * kNT);
-    hipLaunchKernelGGL(k_fill_keys<4>, dim3(nb + wide), dim3(kNT), 0, st, ws, (int)nb);
+    const unsigned nb = blocks_for(ws.n_rec, 2 * kNT);
+    hipLaunchKernelGGL(k_fill_keys<2>, dim3(nb + wide), dim3(kNT), 0, st, ws, (int)nb);
   } else {
     const unsigned nb = blocks_for(ws.n_rec, kNT);
     hipLaunchKernelGGL(k_fill_keys<1>, dim3(nb + wide), dim3(kNT), 0, st, ws, (int)nb);

@@ -500,7 +500,8 @@ __global__ __attribute__((amdgpu_waves_per_eu(TILE == 16 ? 4 : 2))) __launch_bou
 // the camera-frame centre and learnable flag, the record's tile rectangle and
 // first slot.  Gathered without branches, as in the forward.
 struct BwdEntry {
-  float4 e0, e1, e2, eb;
+  float4 e0, e1, e2;
+  float2 eb;
   uint2 rc;
   uint32_t off;
   bool ok;
@@ -674,7 +675,8 @@ __global__ __attribute__((amdgpu_waves_per_eu(TILE == 16 ? 4 : 2))) __launch_bou
 
   // the pass below is gathered while the current one is replayed, its ids one
   // pass ahead (positions clamped to the list, extra loads unused)
-  float4 r0[PER], r1[PER], r2[PER], rb[PER];
+  float4 r0[PER], r1[PER], r2[PER];
+  float2 rb[PER];
   uint32_t pid[PER];
   const int n_rec = vw.n_rec, rec_base = vw.rec_base;
   auto fetch_ids = [&](int top) {
@@ -936,14 +938,14 @@ __global__ __launch_bounds__(Shape<TILE>::NT, (MODE & 4) ? 2 : 3) void k_bwd(Ws 
       e0s[j] = make_float4(E.e0.x, E.e0.y, E.e0.z, 2.0f * E.e0.w);
       const uint32_t sl = entry_slot(ws, E, tx, ty);
       // no slot (only after a capacity overflow): the entry learns nothing
-      const float learn = sl != 0xffffffffu ? E.eb.z : 0.f;
+      const float learn = sl != 0xffffffffu ? __builtin_copysignf(1.f, E.e1.w) : -1.f;
       e1s[j] = make_float4(E.e1.x, E.e1.y, E.e1.z, E.e0.w);
       // (a set sign bit of r: not learnable; r itself is positive)
-      e2s[j] = make_float4(E.e2.x, E.e2.y, E.e2.z, __builtin_copysignf(E.e2.w, learn != 0.f ? 1.f : -1.f));
+      e2s[j] = make_float4(E.e2.x, E.e2.y, E.e2.z, __builtin_copysignf(E.e2.w, learn));
       const float iz = 1.0f / E.e1.z;
       ejs[j] = make_float4(vfx * iz, vfy * iz, -vfx * E.eb.x * iz * iz, -vfy * E.eb.y * iz * iz);
       if (kDp) eps_[j] = make_float4(E.eb.x, E.eb.y, 2.0f * E.e2.w * E.e2.w * iz, 0.f);
-      slot[k] = learn != 0.f ? sl : 0xffffffffu;
+      slot[k] = learn > 0.f ? sl : 0xffffffffu;
 #pragma unroll
       for (int ww = 0; ww < NW; ww++) {
         accA[ww][j] = f32x4{0.f, 0.f, 0.f, 0.f};

@@ -86,8 +86,9 @@ struct Ws {
   int64_t P;                   // total pixels
   int64_t cap;                 // pair capacity
   // per record
-  float4 *recA;                // [n_rec][3]: (mx,my,qa,qb) (qc,o,z,R) (c0,c1,c2,r)
-  float4 *recB;                // [n_rec]: (px, py, learnable, 0)
+  float4 *recA;                // [n_rec][3]: (mx,my,qa,qb) (qc,o,z,R; sign set: not learnable)
+                               // (c0,c1,c2,r)
+  float2 *recB;                // [n_rec]: (px, py), records with tiles only
   uint2 *rect;                 // [n_rec]: tx0|ty0<<16, tx1|ty1<<16 (tx0 > tx1: culled)
   uint32_t *rec_cnt;           // [n_rec] tiles of the records up to and with this one, from
                                // its preprocess block's first (plans with slots)
