@@ -189,7 +189,7 @@ void layout(vtgs_plan *p) {
   take(p->r_zbits, nr * 4);
   take(p->r_rec_off, (nr + 1) * 4);
   take(p->r_scan, (rec_scan_blocks(nr) + 1) * 4);
-  take(p->r_tcount, nt * 4);
+  take(p->r_tcount, nt * 4);  // (these three counter_pitch() apart)
   take(p->r_tcount_ns, nt * 4);
   take(p->r_tfill, nt * 4);
   take(p->r_woff, (nr + 63) / 64 * 64 * 4);
@@ -227,9 +227,14 @@ void make_ws(vtgs_plan *p) {
   w.n_pairs = reinterpret_cast<unsigned long long *>(b + p->r_hdr.off + 8);
   w.iter = reinterpret_cast<uint32_t *>(b + p->r_hdr.off + 16);
   w.n_long = reinterpret_cast<uint32_t *>(b + p->r_hdr.off + 24);
-  w.n_wide = reinterpret_cast<uint32_t *>(b + p->r_hdr.off + 32);
+  w.n_wide = w.n_long + kWideWord;
   w.long_tiles = at<uint32_t>(b, p->r_long);
   w.tile_order = p->tile_order ? at<uint32_t>(b, p->r_order) : nullptr;
+  // (the order's buffer is free without one)
+  w.tile_claim = !p->tile_order && p->n_tiles <= kFillTiles &&
+                         !long_lists(p->n_rec, p->n_tiles, p->prm.tile)
+                     ? at<uint32_t>(b, p->r_order)
+                     : nullptr;
   char *d = b + p->r_desc.off;
   w.kfs = reinterpret_cast<const DevKF *>(d + p->desc_kf);
   w.views = reinterpret_cast<const DevView *>(d + p->desc_view);

@@ -234,12 +234,11 @@ __device__ __forceinline__ void add_wide(const Ws &ws, bool wide, int r, uint32_
 // The wide records' keys, at the ends of the lists of the tiles that they
 // cover: a wave takes a tile, its lanes the list's records, 64 at a time, U
 // of these chunks in flight.
-template <int U>
-__device__ __forceinline__ void fill_wide(const Ws &ws, int wave, int n_waves) {
-  const uint32_t n = ws.n_wide[1];
-  if (n == 0u || (int64_t)n > wide_cap(ws)) return;
+template <int U, typename Range>
+__device__ __forceinline__ void fill_wide(const Ws &ws, uint32_t n, int wave, int n_waves, Range range) {
+  if ((int64_t)n > wide_cap(ws)) return;
   for (int t = wave; t < ws.n_tiles; t += n_waves) {
-    const uint2 rg = ws.ranges[t];
+    const uint2 rg = range(t);
     int lo = 0, hi = ws.n_views - 1;
     while (lo < hi) {
       const int mid = (lo + hi + 1) >> 1;
@@ -443,6 +442,9 @@ __global__ __attribute__((amdgpu_waves_per_eu(8))) __launch_bounds__(kNT) void k
     else
       o = project_record<false>(ws, find_seg(ws, min(r, ws.n_rec - 1)), r, active);
   }
+  // positions for this pass's key fill
+  if (ws.tile_claim)
+    for (int t = r; t < ws.n_tiles; t += (int)gridDim.x * kNT) ws.tile_claim[t] = 0u;
   // one more pass of the pipeline: the tracking update writes its loss at
   // this index, so a captured iteration needs no per-iteration argument
   if (r == 0) *ws.iter += 1u;
@@ -500,8 +502,7 @@ constexpr int kSmallSort = 1024, kMidSort = 4096;
 
 // One block: tile counts -> ranges (clamped to the pair capacity), total
 // pairs, capacity flag; lists longer than kSmallSort are queued for the
-// long-list sorts, those over kMidSort from the queue array's end; clears the
-// counters for the next pass.
+// long-list sorts, those over kMidSort from the queue array's end.
 constexpr int kScanNT = 1024, kScanPer = 8;
 constexpr int kOrderBuckets = 64;
 // Bucket of a list of n entries in the longest-first order: 0 for the
@@ -523,14 +524,71 @@ __device__ __forceinline__ uint32_t block_tiles(const Ws &ws, int64_t b) {
   return b < ws.n_rec ? ws.rec_cnt[min(b + kNT, (int64_t)ws.n_rec) - 1] : 0u;
 }
 
+// Sums of the record groups, one lane per preprocess block (the words lie 1 KB
+// apart); block: the caller's index among the blocks doing this.
+template <int NT>
+__device__ __forceinline__ void group_sums(const Ws &ws, int block, int n_groups) {
+  const int b = block * NT + threadIdx.x;
+  uint32_t s = block_tiles(ws, (int64_t)b * kNT);
+#pragma unroll
+  for (int o = 1; o < kRecBlocks; o <<= 1) s += (uint32_t)__shfl_xor((int)s, o);
+  if (b % kRecBlocks == 0 && b / kRecBlocks < n_groups) ws.scan_part[b / kRecBlocks] = s;
+}
+
+// The range of a list of n entries from pos, cut off at the capacity.
+__device__ __forceinline__ uint2 list_range(unsigned long long pos, uint32_t n, unsigned long long cap) {
+  return make_uint2((uint32_t)min(pos, cap), (uint32_t)min(pos + n, cap));
+}
+
+// The tile scan inside each block of the key fill (plans with a tile_claim:
+// one view, at most kFillTiles tiles): every block sums up all counts for
+// itself, the first one stores the results.  With 75 blocks and 80 tiles
+// (160x120) the fill takes 4.8 us with or without it and the scan's launch
+// (4.7 us) is saved; with 1,200 and 1,200 (640x480) it took 14.6 us instead of
+// 4.8 + 5.9.
+constexpr int kFillPer = kFillTiles / kNT;
+__device__ __forceinline__ void scan_in_fill(const Ws &ws, uint32_t n_wide, bool store, uint2 *range,
+                                             uint32_t *lw) {
+  const unsigned long long cap = (int64_t)n_wide <= wide_cap(ws) ? ws.cap : 0;
+  const int i0 = threadIdx.x * kFillPer;
+  uint32_t v[kFillPer], sum = 0u, tot;
+#pragma unroll
+  for (int k = 0; k < kFillPer; k++) {
+    v[k] = i0 + k < ws.n_tiles ? ws.tile_count[i0 + k] + ws.tile_count_ns[i0 + k] : 0u;
+    sum += v[k];
+  }
+  if (n_wide) {
+    uint32_t d[kFillPer], w = 0u;
+#pragma unroll
+    for (int k = 0; k < kFillPer; k++) {
+      d[k] = i0 + k < ws.n_tiles ? ws.tile_fill[i0 + k] : 0u;
+      w += d[k];
+    }
+    w = block_exclusive_scan<kNT>(w, lw, nullptr);
+#pragma unroll
+    for (int k = 0; k < kFillPer; k++) {
+      w += d[k];
+      if (i0 + k < ws.n_tiles) { v[k] += w; sum += w; }
+    }
+  }
+  unsigned long long pos = block_exclusive_scan<kNT>(sum, lw, &tot);
+#pragma unroll
+  for (int k = 0; k < kFillPer; k++) {
+    const uint2 rg = list_range(pos, v[k], cap);
+    range[i0 + k] = rg;
+    if (store && i0 + k < ws.n_tiles) ws.ranges[i0 + k] = rg;
+    pos += v[k];
+  }
+  if (store && threadIdx.x == 0) {
+    *ws.n_pairs = tot;
+    if (tot > (unsigned long long)ws.cap) atomicOr(ws.flags, kFlagCapacity);
+  }
+  __syncthreads();
+}
+
 __global__ __launch_bounds__(kScanNT) void k_scan_tiles(Ws ws, int n_groups) {
   if (blockIdx.x > 0) {
-    // one lane per preprocess block: the words lie 1 KB apart
-    const int b = (blockIdx.x - 1) * kScanNT + threadIdx.x;
-    uint32_t s = block_tiles(ws, (int64_t)b * kNT);
-#pragma unroll
-    for (int o = 1; o < kRecBlocks; o <<= 1) s += (uint32_t)__shfl_xor((int)s, o);
-    if (b % kRecBlocks == 0 && b / kRecBlocks < n_groups) ws.scan_part[b / kRecBlocks] = s;
+    group_sums<kScanNT>(ws, blockIdx.x - 1, n_groups);
     return;
   }
   __shared__ uint32_t lw[kScanNT / kWave];
@@ -573,17 +631,15 @@ __global__ __launch_bounds__(kScanNT) void k_scan_tiles(Ws ws, int n_groups) {
     for (int k = 0; k < kScanPer; k++) {
       const int i = i0 + k;
       if (i < ws.n_tiles) {
-        const unsigned long long s = pos < cap ? pos : cap;
-        const unsigned long long e = pos + v[k] < cap ? pos + v[k] : cap;
-        ws.ranges[i] = make_uint2((uint32_t)s, (uint32_t)e);
-        if (e - s > (unsigned long long)kMidSort)
+        const uint2 rg = list_range(pos, v[k], cap);
+        const uint32_t len = rg.y - rg.x;
+        ws.ranges[i] = rg;
+        if (len > (uint32_t)kMidSort)
           ws.long_tiles[(uint32_t)ws.n_tiles - 1u - atomicAdd(&nhuge_s, 1u)] = i;
-        else if (e - s > (unsigned long long)kSmallSort)
+        else if (len > (uint32_t)kSmallSort)
           ws.long_tiles[atomicAdd(&nlong_s, 1u)] = i;
-        ws.tile_count[i] = 0;
-        ws.tile_count_ns[i] = 0;
         ws.tile_fill[i] = vs[k];
-        if (ws.tile_order) atomicAdd(&bk[order_bucket((uint32_t)(e - s))], 1u);
+        if (ws.tile_order) atomicAdd(&bk[order_bucket(len)], 1u);
       }
       pos += v[k];
     }
@@ -596,7 +652,6 @@ __global__ __launch_bounds__(kScanNT) void k_scan_tiles(Ws ws, int n_groups) {
     if (carry_s > (unsigned long long)ws.cap) atomicOr(ws.flags, kFlagCapacity);
     ws.n_long[0] = nlong_s;
     ws.n_long[1] = nhuge_s;
-    ws.n_wide[0] = 0u;
     ws.n_wide[1] = n_wide;
   }
   if (ws.tile_order) {
@@ -626,12 +681,29 @@ __global__ __launch_bounds__(kScanNT) void k_scan_tiles(Ws ws, int n_groups) {
 // positions its atomics returned; the other groups claim positions after
 // all of those with atomics here.  Either way a tile's keys land in no fixed
 // order; the sort that follows fixes it.
-template <int RPT>
-__global__ __launch_bounds__(kNT) void k_fill_keys(Ws ws, int rec_blocks) {
+//
+// The grid: rec_blocks blocks of records, wide_blocks for the wide records
+// and, with kScan (the tile scan is done here), blocks of record groups.
+template <int RPT, bool kScan>
+__global__ __launch_bounds__(kNT) void k_fill_keys(Ws ws, int rec_blocks, int wide_blocks, int n_groups) {
+  __shared__ uint2 range_s[kScan ? kFillTiles : 1];
+  __shared__ uint32_t lw[kNT / kWave];
+  const uint32_t n_wide = kScan ? ws.n_wide[0] : ws.n_wide[1];
+  if ((int)blockIdx.x >= rec_blocks + wide_blocks) {
+    if (kScan) group_sums<kNT>(ws, blockIdx.x - rec_blocks - wide_blocks, n_groups);
+    return;
+  }
+  auto range = [&](int t) { return kScan ? range_s[t] : ws.ranges[t]; };
+  // n positions of tile t's list, after those of the shared boxes
+  auto claim = [&](int t, uint32_t n) {
+    return kScan ? ws.tile_count[t] + atomicAdd(ws.tile_claim + t, n) : atomicAdd(ws.tile_fill + t, n);
+  };
   if ((int)blockIdx.x >= rec_blocks) {
     constexpr int kWaves = kNT / kWave;
-    fill_wide<4>(ws, (blockIdx.x - rec_blocks) * kWaves + threadIdx.x / kWave,
-                 (gridDim.x - rec_blocks) * kWaves);
+    if (!n_wide) return;
+    if (kScan) scan_in_fill(ws, n_wide, false, range_s, lw);
+    fill_wide<4>(ws, n_wide, (blockIdx.x - rec_blocks) * kWaves + threadIdx.x / kWave,
+                 wide_blocks * kWaves, range);
     return;
   }
   // the views' first records, tiles per row and first tiles, read by the
@@ -649,9 +721,13 @@ __global__ __launch_bounds__(kNT) void k_fill_keys(Ws ws, int rec_blocks) {
 #pragma unroll
   for (int k = 0; k < RPT; k++) {
     const int r = (blockIdx.x * RPT + k) * kNT + threadIdx.x;
-    const int rr = min(r, ws.n_rec - 1);
+    const int rr = max(min(r, ws.n_rec - 1), 0);
     rc[k] = ws.rect[rr];
     zb[k] = ws.zbits[rr];
+  }
+  if (kScan) {
+    scan_in_fill(ws, n_wide, blockIdx.x == 0, range_s, lw);
+    if (ws.n_rec == 0) return;
   }
   if (view_lds) {
     for (int v = threadIdx.x; v < ws.n_views; v += kNT)
@@ -698,7 +774,7 @@ __global__ __launch_bounds__(kNT) void k_fill_keys(Ws ws, int rec_blocks) {
       // the group's first position in box tile j, claimed by the
       // preprocess (unused, and never written, where no rectangle of the
       // group covers the tile)
-      const uint2 rg = ws.ranges[box_tile(box[k], lane_id(), btx, btb)];
+      const uint2 rg = range(box_tile(box[k], lane_id(), btx, btb));
       const int g0 = (blockIdx.x * RPT + k) * kNT + (threadIdx.x & ~(kWave - 1));
       base[k] = rg.x + ws.wave_off[g0 + lane_id()];
       end[k] = rg.y;
@@ -739,8 +815,8 @@ __global__ __launch_bounds__(kNT) void k_fill_keys(Ws ws, int rec_blocks) {
       for (int j = lane_id(); j < mid.area; j += kWave) {
         const uint32_t n = pos[j];
         const int t = box_tile(mid, j, btx, btb);
-        const uint2 rg = ws.ranges[t];
-        if (n) pos[j] = rg.x + atomicAdd(ws.tile_fill + t, n);
+        const uint2 rg = range(t);
+        if (n) pos[j] = rg.x + claim(t, n);
         lim[j] = rg.y;
       }
       lds_order();
@@ -753,9 +829,9 @@ __global__ __launch_bounds__(kNT) void k_fill_keys(Ws ws, int rec_blocks) {
         const int t = on ? tile_base[k] + w.ty * tiles_x[k] + w.tx : 0;
         const SameTile s = same_tile(on, t);
         uint32_t at = 0u;
-        if (on && s.rank == 0u) at = ws.ranges[t].x + atomicAdd(ws.tile_fill + t, s.n);
+        if (on && s.rank == 0u) at = range(t).x + claim(t, s.n);
         at = (uint32_t)__shfl((int)at, s.first) + s.rank;
-        if (on && at < ws.ranges[t].y) ws.keys[at] = key[k];
+        if (on && at < range(t).y) ws.keys[at] = key[k];
       }
     }
   }
@@ -962,10 +1038,18 @@ __launch_bounds__(NT) void k_sort_tiles(Ws ws, int lo_n, int hi_n, int queue) {
   constexpr int CAP = NT * E;
   __shared__ SortLds<NT, E> S;
   const int count = queue ? (int)ws.n_long[queue - 1] : ws.n_tiles;
-  // the fill is done with its counters: cleared for the next pass's wide
-  // records
-  if (queue == 0 && threadIdx.x == 0 && blockIdx.x < ws.n_tiles) ws.tile_fill[blockIdx.x] = 0u;
-  for (int q = blockIdx.x; q < count; q += gridDim.x) {
+  // the fill is done with the tile counters and the number of wide records:
+  // cleared for the next pass, by blocks of their own
+  if (NT == 256 && (int)blockIdx.x >= ws.n_tiles) {
+    const int i = ((int)blockIdx.x - ws.n_tiles) * NT + threadIdx.x;
+    const int64_t pitch = counter_pitch(ws.n_tiles);
+    for (int a = 0; a < 3; a++)
+      if (i < ws.n_tiles) ws.tile_count[a * pitch + i] = 0u;
+    if (i == 0) ws.n_long[kWideWord] = 0u;
+    return;
+  }
+  const int blocks = NT == 256 ? ws.n_tiles : (int)gridDim.x;
+  for (int q = blockIdx.x; q < count; q += blocks) {
     const int tile = queue == 0 ? q : (int)ws.long_tiles[queue == 1 ? q : ws.n_tiles - 1 - q];
     // ranges are clamped to the capacity, and every position of a clamped
     // range was written by the fill, so sorting stays in bounds on overflow
@@ -1082,40 +1166,54 @@ hipError_t launch_preprocess(const Ws &ws, hipStream_t st) {
 
 
 hipError_t launch_scan_tiles(const Ws &ws, hipStream_t st) {
+  if (ws.tile_claim) return hipSuccess;  // part of the key fill
   const int ng = ws.slots ? (int)rec_scan_blocks(ws.n_rec) : 0;
   hipLaunchKernelGGL(k_scan_tiles, dim3(1 + blocks_for((int64_t)ng * kRecBlocks, kScanNT)), dim3(kScanNT), 0, st, ws, ng);
   return hipGetLastError();
 }
 
 hipError_t launch_fill_keys(const Ws &ws, hipStream_t st) {
+  // a wave per tile for the wide records
+  const int wide = (int)std::min(blocks_for(ws.n_tiles, kNT / kWave), 2048u);
+  if (ws.tile_claim) {
+    const int nb = std::max((int)blocks_for(ws.n_rec, kNT), 1);
+    const int ng = ws.slots ? (int)rec_scan_blocks(ws.n_rec) : 0;
+    hipLaunchKernelGGL((k_fill_keys<1, true>), dim3(nb + wide + blocks_for((int64_t)ng * kRecBlocks, kNT)),
+                       dim3(kNT), 0, st, ws, nb, wide, ng);
+    return hipGetLastError();
+  }
   if (ws.n_rec == 0) return hipSuccess;
   // two records per thread once the grid holds several waves per SIMD at
   // that rate (1,024 SIMDs; 12.3 M records: 112 us with four, 102 with two, 103
-  // with one, 2 M: 40, 41, 44); then a wave per tile for the wide records
-  const unsigned wide = std::min(blocks_for(ws.n_tiles, kNT / kWave), 2048u);
+  // with one, 2 M: 40, 41, 44)
   if (ws.n_rec >= (1 << 20)) {
-    const unsigned nb = blocks_for(ws.n_rec, 2 * kNT);
-    hipLaunchKernelGGL(k_fill_keys<2>, dim3(nb + wide), dim3(kNT), 0, st, ws, (int)nb);
+    const int nb = (int)blocks_for(ws.n_rec, 2 * kNT);
+    hipLaunchKernelGGL((k_fill_keys<2, false>), dim3(nb + wide), dim3(kNT), 0, st, ws, nb, wide, 0);
   } else {
-    const unsigned nb = blocks_for(ws.n_rec, kNT);
-    hipLaunchKernelGGL(k_fill_keys<1>, dim3(nb + wide), dim3(kNT), 0, st, ws, (int)nb);
+    const int nb = (int)blocks_for(ws.n_rec, kNT);
+    hipLaunchKernelGGL((k_fill_keys<1, false>), dim3(nb + wide), dim3(kNT), 0, st, ws, nb, wide, 0);
   }
   return hipGetLastError();
 }
 
+// Whether the records' expected pairs per tile (a Gaussian of extent ~4-5 px
+// covers about (1 + 10 / B)^2 tiles of side B) make long lists the rule.
+bool long_lists(double n_rec, double n_tiles, int tile) {
+  const double per = (1.0 + 10.0 / tile) * (1.0 + 10.0 / tile);
+  return per * n_rec > 1024.0 * n_tiles;
+}
+
 hipError_t launch_sort_tiles(const Ws &ws, hipStream_t st) {
-  // Where the records' expected pairs per tile (a Gaussian of extent ~4-5 px
-  // covers about (1 + 10 / B)^2 tiles of side B) make long lists the rule,
-  // lists of up to 1024 go to 256-thread blocks, those of up to 4096, queued
-  // by the scan, to 512-thread blocks (three per CU) and longer ones to
-  // 1024-thread blocks (one per CU; 8192 keys in LDS, longer lists merged from
-  // runs), each grid a few rounds of the device's blocks.  Otherwise the
-  // 256-thread blocks sort every list, a long one (the odd one) as runs of
-  // 1024 merged in rounds, and no other kernel is launched (an empty launch
-  // costs a tracking iteration ~5 us).
-  const double per = (1.0 + 10.0 / ws.tile) * (1.0 + 10.0 / ws.tile);
-  const bool many = per * (double)ws.n_rec > 1024.0 * (double)ws.n_tiles;
-  hipLaunchKernelGGL((k_sort_tiles<256, kSmallSort / 256>), dim3(ws.n_tiles), dim3(256), 0, st, ws, 0,
+  // Where long lists are the rule, lists of up to 1024 go to 256-thread blocks,
+  // those of up to 4096, queued by the scan, to 512-thread blocks (three per
+  // CU) and longer ones to 1024-thread blocks (one per CU; 8192 keys in LDS,
+  // longer lists merged from runs), each grid a few rounds of the device's
+  // blocks.  Otherwise the 256-thread blocks sort every list, a long one (the
+  // odd one) as runs of 1024 merged in rounds, and no other kernel is launched
+  // (an empty launch costs a tracking iteration ~5 us).
+  const bool many = long_lists(ws.n_rec, ws.n_tiles, ws.tile);
+  hipLaunchKernelGGL((k_sort_tiles<256, kSmallSort / 256>), dim3(ws.n_tiles + blocks_for(ws.n_tiles, 256)),
+                     dim3(256), 0, st, ws, 0,
                      many ? kSmallSort : 0x7fffffff, 0);
   if (many) {
     hipLaunchKernelGGL((k_sort_tiles<512, kMidSort / 512>), dim3(std::min(ws.n_tiles, 3072)), dim3(512),

@@ -63,6 +63,13 @@ struct DevKFUse {
   int32_t seg;        // the (view, keyframe) segment
 };
 
+// Most tiles of a plan whose key fill sums up the tile counts in each block.
+constexpr int kFillTiles = 512;
+// Words from one of tile_count, tile_count_ns and tile_fill to the next, and
+// from n_long to n_wide.
+__host__ __device__ inline int64_t counter_pitch(int64_t n_tiles) { return (n_tiles + 63) / 64 * 64; }
+constexpr int kWideWord = 2;
+
 enum : uint32_t { kFlagCapacity = 1u, kFlagNonfinite = 2u };
 
 // Everything a kernel needs, passed by value.
@@ -98,6 +105,8 @@ struct Ws {
   // per tile
   uint32_t *tile_count;        // [n_tiles] pairs of record groups with a shared tile box
   uint32_t *tile_count_ns;     // [n_tiles] pairs of the other groups, but wide records
+  uint32_t *tile_claim;        // [n_tiles] positions given to the other groups, plans whose key
+                               // fill sums up the tile counts itself (else NULL)
   uint32_t *tile_fill;         // [n_tiles] next free list position of the other groups;
                                // before the scan: ends of the wide records' rows
   uint32_t *wave_off;          // [n_rec rounded up to 64] per 64-record group, lane j: the
@@ -263,6 +272,7 @@ hipError_t launch_preprocess(const Ws &ws, hipStream_t st);
 hipError_t launch_scan_tiles(const Ws &ws, hipStream_t st);
 hipError_t launch_fill_keys(const Ws &ws, hipStream_t st);
 hipError_t launch_sort_tiles(const Ws &ws, hipStream_t st);
+bool long_lists(double n_rec, double n_tiles, int tile);
 hipError_t launch_scan_records(const Ws &ws, hipStream_t st);
 hipError_t launch_composite_fwd(const Ws &ws, float *rgb, float *depth, float *sil,
                                 hipStream_t st);
