@@ -101,14 +101,15 @@ class Keyframe:
         m = None if mask is None else torch.as_tensor(mask).to(dev).to(torch.uint8).contiguous()
         nbytes = L.vtgs_ingest_scratch_bytes(H, W, stride)
         scratch = torch.empty(max(nbytes, 4), dtype=torch.uint8, device=dev)
-        count = torch.zeros(1, dtype=torch.int32, device=dev)
+        # (the count, and the colours where there are any, are written in full)
+        count = torch.empty(1, dtype=torch.int32, device=dev)
         st = _stream(stream)
         check(L.vtgs_ingest_count(_ptr(d), _ptr(m), H, W, stride, _ptr(scratch), nbytes,
                                   _ptr(count), st))
         n = int(count.item())
         pix = torch.empty(n, dtype=torch.int32, device=dev)
         dep = torch.empty(n, dtype=torch.float32, device=dev)
-        col = torch.zeros(3, n, dtype=torch.float32, device=dev)
+        col = (torch.zeros if rgb is None else torch.empty)(3, n, dtype=torch.float32, device=dev)
         opa = torch.empty(n, dtype=torch.float32, device=dev)
         rad = torch.empty(n, dtype=torch.float32, device=dev)
         check(L.vtgs_ingest_fill(_ptr(d), _ptr(rgb), _ptr(m), H, W, stride, float(cam.fx),
