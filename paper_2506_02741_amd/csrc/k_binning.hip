@@ -1,13 +1,14 @@
 // Preprocessing and tile binning of view-tied Gaussians.
 //
-//  setup      M_vk = T_v T_k^-1 for every (view, keyframe) pair
-//  preprocess per (view, Gaussian): back-project the tied depth pixel with
-//             the keyframe pose (Sec. 3.2), move it to the view camera,
-//             project, Sigma_2D = r^2 J J^T + lowpass*I, conic, extent
-//             R = ceil(sqrt(q_cut * lambda_max)), tile rectangle; then count
-//             the Gaussian in each tile it covers (wave-aggregated atomics,
-//             whose old values are the wave's positions in those tiles)
+//  preprocess per (view, Gaussian): M_vk = T_v T_k^-1; back-project the tied
+//             depth pixel with the keyframe pose (Sec. 3.2), move it to the
+//             view camera, project, Sigma_2D = r^2 J J^T + lowpass*I, conic,
+//             extent R = ceil(sqrt(q_cut * lambda_max)), tile rectangle; then
+//             count the Gaussian in each tile it covers (wave-aggregated
+//             atomics, whose old values are the wave's positions in those
+//             tiles; rectangles of many tiles go into a list)
 //  scan_tiles exclusive scan of the tile counts -> per-tile [start, end)
+//             (small plans: in the fill)
 //  fill_keys  write (depth bits << 32 | view-local id) into the tile slots
 //  sort_tiles sort each tile's keys (ascending depth, ties by id) in LDS and
 //             emit the id list the compositing kernels walk

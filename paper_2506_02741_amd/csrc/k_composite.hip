@@ -9,7 +9,7 @@
 // six coefficients per entry against six monomials per pixel, and the signs
 // of the MFMA's results are every lane's bit mask of the entries that may
 // reach its pixel.  The lanes then composite their own entries of a group of
-// chunks (up to 256 entries) as one stream each, with the exact test, so a
+// chunks (up to 512 entries) as one stream each, with the exact test, so a
 // wave takes as many steps as its busiest lane has entries in the group.
 //
 // Forward, per pixel, front to back [splat of Sec. 3.3]:
@@ -45,8 +45,9 @@
 // (rho += dL/dp, phi += p x dL/dp) in registers, summed per tile.
 // Mode "slots": each lane adds its (dL/dc, dL/do, dL/dr) -- and with
 // geometry its dL/dp -- for an entry into its wave's own LDS accumulators
-// (LDS atomics, in the wave's program order); after a batch the four waves'
-// sums go to the pair's (record, tile) slot, and a gather pass sums a
+// (read and written back by the lane that claims the entry, LDS atomics for
+// the lanes that lose, in the wave's program order); after a batch the four
+// waves' sums go to the pair's (record, tile) slot, and a gather pass sums a
 // record's slots.  Neither mode uses global
 // atomics and no two waves share an accumulator, so both are deterministic.
 #include <type_traits>

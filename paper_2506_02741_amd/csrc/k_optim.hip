@@ -7,7 +7,8 @@
 //  track_update twist reduce + Adam on the twist (lr_trans on rho, lr_rot on
 //               phi; App. A) + pose <- exp(step^) pose
 //  map_l1       Eq. 2 (Sec. 3.4) L1 terms: rho mean|V - V'|,
-//               sigma mean(U |D - D'|) with U = (D > 0); gradients
+//               sigma mean(U |D - D'|) with U = (D > 0); the depth's gradient
+//               (part of ssim_a's grid; ssim_b adds the colours')
 //  ssim_a/b     tau (1 - SSIM(V, V')): 11x11 Gaussian window (sigma 1.5),
 //               zero padding, C1 = 0.01^2, C2 = 0.03^2; separable passes
 //               through LDS; the backward filters the per-pixel partials
