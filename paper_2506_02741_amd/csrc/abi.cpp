@@ -629,10 +629,14 @@ int vtgs_plan_create(const vtgs_keyframe *kfs, int32_t n_kf, const vtgs_view *vi
     p->n_tiles = (int32_t)n_tiles;
     p->P = Ptot;
     // longest tile lists first where views of different sizes and list
-    // lengths share a grid (a multi-view plan); VTGS_TILE_ORDER=0 / 1 forces it
+    // lengths share a grid (a multi-view plan), and where the tiles are more
+    // than the device composites at once (four blocks per CU, three in the
+    // backward to slots; 64-thread blocks of 8-pixel tiles: four times that), so
+    // that its last blocks are short ones; VTGS_TILE_ORDER=0 / 1 forces it
+    const int64_t at_once = (p->any_learnable ? 768 : 1024) * (P.tile == 8 ? 4 : 1);
     {
       const char *e = std::getenv("VTGS_TILE_ORDER");
-      p->tile_order = e ? std::atoi(e) != 0 : n_views > 1;
+      p->tile_order = e ? std::atoi(e) != 0 : n_views > 1 || n_tiles > at_once;
     }
     p->loss_blocks = std::max(loss_blocks, 1);
     p->ssim_gx = (maxw + 15) / 16;

@@ -507,12 +507,13 @@ constexpr int kSmallSort = 1024, kMidSort = 4096;
 constexpr int kScanNT = 1024, kScanPer = 8;
 constexpr int kOrderBuckets = 64;
 // Bucket of a list of n entries in the longest-first order: 0 for the
-// longest, two per octave (bit length and the next bit), 63 for empty.
+// longest, eight per octave from 64 entries on, then one for shorter lists and
+// one for empty ones.  (With two per octave the lists of a tracking frame, 590
+// entries on average and 750 at most, shared one bucket.)
 __device__ __forceinline__ int order_bucket(uint32_t n) {
-  if (n == 0u) return kOrderBuckets - 1;
-  const int bl = 32 - __clz((int)n);                              // 1 .. 32
-  const int sb = bl >= 2 ? (int)((n >> (bl - 2)) & 1u) : 0;
-  return kOrderBuckets - 2 - min(2 * bl + sb - 2, kOrderBuckets - 2);
+  if (n < 64u) return kOrderBuckets - (n ? 2 : 1);
+  const int bl = 32 - __clz((int)n);  // 7 ..
+  return max(kOrderBuckets - 3 - (8 * (bl - 7) + (int)((n >> (bl - 4)) & 7u)), 0);
 }
 
 // Groups of records for the slot offsets: kRecBlocks blocks of the
