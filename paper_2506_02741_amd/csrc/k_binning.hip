@@ -604,6 +604,10 @@ __global__ __launch_bounds__(kScanNT) void k_scan_tiles(Ws ws, int n_groups) {
   const unsigned long long cap = (int64_t)n_wide <= wide_cap(ws) ? ws.cap : 0;
   if (threadIdx.x < kOrderBuckets) bk[threadIdx.x] = 0u;
   __syncthreads();
+  // a plan of one round keeps its tiles' buckets and their ranks there
+  const bool one_round = ws.n_tiles <= kScanNT * kScanPer;
+  int bucket[kScanPer];
+  uint32_t rank[kScanPer];
   for (int base = 0; base < ws.n_tiles; base += kScanNT * kScanPer) {
     const int i0 = base + threadIdx.x * kScanPer;
     uint32_t v[kScanPer], vs[kScanPer], sum = 0;
@@ -641,7 +645,10 @@ __global__ __launch_bounds__(kScanNT) void k_scan_tiles(Ws ws, int n_groups) {
         else if (len > (uint32_t)kSmallSort)
           ws.long_tiles[atomicAdd(&nlong_s, 1u)] = i;
         ws.tile_fill[i] = vs[k];
-        if (ws.tile_order) atomicAdd(&bk[order_bucket(len)], 1u);
+        if (ws.tile_order) {
+          bucket[k] = order_bucket(len);
+          rank[k] = atomicAdd(&bk[bucket[k]], 1u);
+        }
       }
       pos += v[k];
     }
@@ -657,7 +664,7 @@ __global__ __launch_bounds__(kScanNT) void k_scan_tiles(Ws ws, int n_groups) {
     ws.n_wide[1] = n_wide;
   }
   if (ws.tile_order) {
-    // longest lists first: tiles bucketed by list length (two buckets per
+    // longest lists first: tiles bucketed by list length (eight buckets per
     // octave, longest first, empty lists last), so that the compositing
     // grid, dispatched in block order, starts its heaviest tiles first and
     // ends on light ones; the order within a bucket is whatever the atomics
@@ -668,6 +675,13 @@ __global__ __launch_bounds__(kScanNT) void k_scan_tiles(Ws ws, int n_groups) {
       bk[threadIdx.x] = wave_incl_scan_u32(c) - c;
     }
     __syncthreads();
+    if (one_round) {
+      for (int k = 0; k < kScanPer; k++) {
+        const int i = threadIdx.x * kScanPer + k;
+        if (i < ws.n_tiles) ws.tile_order[bk[bucket[k]] + rank[k]] = (uint32_t)i;
+      }
+      return;
+    }
     for (int i = threadIdx.x; i < ws.n_tiles; i += kScanNT)
       ws.tile_order[atomicAdd(&bk[order_bucket(ws.ranges[i].y - ws.ranges[i].x)], 1u)] = (uint32_t)i;
   }
