@@ -1,6 +1,6 @@
 """Binning of Gaussians whose tile rectangles are too wide for a shared box:
-small ones walked by their own lane, those of more than 64 tiles by the whole
-wave.  Lists against the oracle, bit for bit."""
+small ones counted in the wave's own counters, those of more than 64 tiles from a
+list.  Lists against the oracle, bit for bit."""
 import numpy as np
 import pytest
 
