@@ -939,14 +939,15 @@ __global__ __launch_bounds__(Shape<TILE>::NT, (MODE & 4) ? 2 : 3) void k_bwd(Ws 
       e0s[j] = make_float4(E.e0.x, E.e0.y, E.e0.z, 2.0f * E.e0.w);
       const uint32_t sl = entry_slot(ws, E, tx, ty);
       // no slot (only after a capacity overflow): the entry learns nothing
-      const float learn = sl != 0xffffffffu ? __builtin_copysignf(1.f, E.e1.w) : -1.f;
+      const bool learn = sl != 0xffffffffu && __float_as_int(E.e1.w) >= 0;
       e1s[j] = make_float4(E.e1.x, E.e1.y, E.e1.z, E.e0.w);
-      // (a set sign bit of r: not learnable; r itself is positive)
-      e2s[j] = make_float4(E.e2.x, E.e2.y, E.e2.z, __builtin_copysignf(E.e2.w, learn));
+      // (r is NaN where the entry does not learn; a record with tiles has a
+      // finite one, of either sign)
+      e2s[j] = make_float4(E.e2.x, E.e2.y, E.e2.z, learn ? E.e2.w : __builtin_nanf(""));
       const float iz = 1.0f / E.e1.z;
       ejs[j] = make_float4(vfx * iz, vfy * iz, -vfx * E.eb.x * iz * iz, -vfy * E.eb.y * iz * iz);
       if (kDp) eps_[j] = make_float4(E.eb.x, E.eb.y, 2.0f * E.e2.w * E.e2.w * iz, 0.f);
-      slot[k] = learn > 0.f ? sl : 0xffffffffu;
+      slot[k] = learn ? sl : 0xffffffffu;
 #pragma unroll
       for (int ww = 0; ww < NW; ww++) {
         accA[ww][j] = f32x4{0.f, 0.f, 0.f, 0.f};
@@ -1114,7 +1115,7 @@ __global__ __launch_bounds__(Shape<TILE>::NT, (MODE & 4) ? 2 : 3) void k_bwd(Ws 
           // the settle waits for the previous claim's reads: after the step's
           // arithmetic (which this empty statement consumes)
           asm volatile("" ::"v"(C.va[0]), "v"(C.va[1]), "v"(C.va[2]), "v"(C.va[3]), "v"(v4) : "memory");
-          return ok && __float_as_int(A.e2.w) >= 0;
+          return ok && !__builtin_isnan(A.e2.w);
         };
         // the claim O settled in the lanes `open`: the lane whose number
         // stayed in the tag writes its sum back; then the lanes that lost add
