@@ -407,6 +407,7 @@ __device__ __forceinline__ Projected project_record(const Ws &ws, int seg, int r
   A[1] = make_float4(qc, opa, pz, __builtin_copysignf(R, klearn ? 1.f : -1.f));
   A[2] = make_float4(c0, c1, c2, rad);
   if (o.has) ws.recB[r] = make_float2(px, py);
+  if (o.has && !all_finite(c0, c1, c2, pz)) *odd_records(ws) = 1u;
   ws.rect[r] = pack_rect(o.x0, o.y0, o.x1, o.y1);
   // the depth again on its own, so that the key fill reads 4 B per record
   ws.zbits[r] = o.zbits;
@@ -1055,13 +1056,18 @@ __launch_bounds__(NT) void k_sort_tiles(Ws ws, int lo_n, int hi_n, int queue) {
   __shared__ SortLds<NT, E> S;
   const int count = queue ? (int)ws.n_long[queue - 1] : ws.n_tiles;
   // the fill is done with the tile counters and the number of wide records:
-  // cleared for the next pass, by blocks of their own
+  // cleared for the next pass, by blocks of their own (the mark of records
+  // that are not finite goes to the compositors first)
   if (NT == 256 && (int)blockIdx.x >= ws.n_tiles) {
     const int i = ((int)blockIdx.x - ws.n_tiles) * NT + threadIdx.x;
     const int64_t pitch = counter_pitch(ws.n_tiles);
     for (int a = 0; a < 3; a++)
       if (i < ws.n_tiles) ws.tile_count[a * pitch + i] = 0u;
-    if (i == 0) ws.n_long[kWideWord] = 0u;
+    if (i == 0) {
+      ws.n_long[kWideWord] = 0u;
+      odd_records(ws)[1] = odd_records(ws)[0];
+      odd_records(ws)[0] = 0u;
+    }
     return;
   }
   const int blocks = NT == 256 ? ws.n_tiles : (int)gridDim.x;

@@ -386,6 +386,32 @@ __global__ __attribute__((amdgpu_waves_per_eu(TILE == 16 ? 4 : 2))) __launch_bou
           dst[k * kWave + lane_id()] = ((unsigned long long)hi << 32) | lo;
         }
       }
+      if (odd_records(ws)[1] && !wave_done()) {
+        // Plans with colours or depths that are not finite: a step that the
+        // exact test refuses weighs 0, which would still put such a value into
+        // the pixel's sums, so these entries take the exact test here.
+        for (int c = g0; c < cend; c++) {
+          const int n = min(nb - c * kWave, kWave);
+          const uint32_t id = ws.ids[b + c * kWave + min(lane_id(), n - 1)];
+          const float4 *A = ws.recA + 3 * ((int64_t)rec_base + (id < (uint32_t)n_rec ? id : 0u));
+          const bool finite = all_finite(A[2].x, A[2].y, A[2].z, A[1].z);
+          for (unsigned long long m = lanes(!finite && lane_id() < n); m; m &= m - 1ull) {
+            const int e = __builtin_ctzll(m);
+            const uint32_t i = (uint32_t)__builtin_amdgcn_readlane((int)id, e);
+            const float4 *E = ws.recA + 3 * ((int64_t)rec_base + (i < (uint32_t)n_rec ? i : 0u));
+            const float4 e0 = make_float4(E[0].x, E[0].y, E[0].z, 2.0f * E[0].w);
+            const int h = 2 * (c - g0) + (e >> 5);
+#pragma unroll
+            for (int k = 0; k < PPT; k++) {
+              uint32_t &word = words[h][w * PPT + k][lane_id()];
+              if (!(quad2(e0, E[1].x, px[k], py[k]) <= qcut)) word &= ~(1u << (e & 31));
+              if (word == 0u) nz[k] &= ~(1u << h);
+              uint32_t *dst = (uint32_t *)(ws.lane_bits + chunk_word(start, b - start, c, t, w, NW, PPT));
+              dst[2 * (k * kWave + lane_id()) + (e >> 5)] = word;
+            }
+          }
+        }
+      }
       if (kShare) {
         __syncthreads();
         stage_entries();

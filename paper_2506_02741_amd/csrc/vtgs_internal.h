@@ -224,6 +224,16 @@ __device__ __forceinline__ uint32_t block_exclusive_scan(uint32_t v, uint32_t *l
   return base + x - v;
 }
 
+// [2] after n_wide: whether a record with tiles has a colour or a depth that is
+// not finite, in this pass so far (by the preprocess) and in the last one
+// binned (by the tile sort).
+__device__ __forceinline__ uint32_t *odd_records(const Ws &ws) { return ws.n_wide + kWideWord; }
+
+__device__ __forceinline__ bool all_finite(float a, float b, float c, float d) {
+  // (0 x is 0 for finite x only)
+  return fmaf(0.f, a, fmaf(0.f, b, fmaf(0.f, c, 0.f * d))) == 0.f;
+}
+
 __device__ __forceinline__ int find_view_by_record(const Ws &ws, int r) {
   int lo = 0, hi = ws.n_views - 1;
   while (lo < hi) {
