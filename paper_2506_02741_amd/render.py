@@ -104,8 +104,16 @@ class Keyframe:
         # (the count, and the colours where there are any, are written in full)
         count = torch.empty(1, dtype=torch.int32, device=dev)
         st = _stream(stream)
+        # on a stream of the caller's: after what the current one holds (the
+        # inputs' copies, earlier uses of the memory allocated here)
+        cur = None if stream is None else torch.cuda.current_stream(dev)
+        own = stream if cur is not None and stream != cur else None
+        if own is not None:
+            own.wait_stream(cur)
         check(L.vtgs_ingest_count(_ptr(d), _ptr(m), H, W, stride, _ptr(scratch), nbytes,
                                   _ptr(count), st))
+        if own is not None:
+            own.synchronize()
         n = int(count.item())
         pix = torch.empty(n, dtype=torch.int32, device=dev)
         dep = torch.empty(n, dtype=torch.float32, device=dev)
@@ -115,6 +123,11 @@ class Keyframe:
         check(L.vtgs_ingest_fill(_ptr(d), _ptr(rgb), _ptr(m), H, W, stride, float(cam.fx),
                                  float(o_init), _ptr(scratch), nbytes, n, _ptr(pix), _ptr(dep),
                                  _ptr(col), _ptr(opa), _ptr(rad), st))
+        if own is not None:
+            for t in (d, rgb, m, scratch, pix, dep, col, opa, rad):
+                if t is not None:
+                    t.record_stream(own)
+            cur.wait_stream(own)  # (the constructor may copy them)
         k = cls(cam, pose, pix, dep, col, opa, rad, learnable, dev)
         k.depth_map = d.reshape(-1)  # the frame's depth map (visibility tests)
         return k
