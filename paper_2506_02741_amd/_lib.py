@@ -7,6 +7,8 @@ no fallback.
 from __future__ import annotations
 
 import ctypes as C
+import functools
+import hashlib
 import os
 
 PKG = os.path.dirname(os.path.abspath(__file__))
@@ -128,6 +130,16 @@ def load():
                               % (L.vtgs_abi_version(), VTGS_ABI_VERSION))
         _lib = L
     return _lib
+
+
+@functools.lru_cache(maxsize=None)
+def revision() -> str:
+    """A digest of the library file: another one after any change of a kernel."""
+    try:
+        with open(LIB_PATH, "rb") as f:
+            return hashlib.blake2b(f.read(), digest_size=8).hexdigest()
+    except OSError:
+        return "none"
 
 
 def last_error() -> str:

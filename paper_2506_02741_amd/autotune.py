@@ -3,11 +3,13 @@
 For a workload (keyframes, views, mode) the tuner sweeps tile size
 {8, 16, 32} x LDS batch {128, 256, 512}, times the forward + backward of
 each configuration with the library's per-stage HIP events, and keeps the
-fastest.  Results are cached per shape bucket in a JSON file keyed by the
-GPU architecture:
+fastest.  Results are cached per shape bucket in a JSON file:
 
-    bucket = (arch, mode, number of views, sorted distinct resolutions,
-              Gaussians per view rounded to a power of two)
+    bucket = (arch, library, mode, number of views, sorted distinct
+              resolutions, Gaussians per view rounded to a power of two)
+
+(library: a digest of its file, so that a shape found with other kernels,
+whose tile and batch may have meant other launches, is not taken over).
 
 Every configuration renders the same image bit for bit (each pixel walks
 its Gaussians in the same depth order whatever the tile), so the choice
@@ -22,6 +24,7 @@ import threading
 
 import torch
 
+from . import _lib
 from . import render as R
 
 TILES = (8, 16, 32)
@@ -46,8 +49,8 @@ def bucket(keyframes, views, mode):
     per_view = [sum(k.n for k in keyframes[v.kf_first:v.kf_first + v.kf_count]) for v in views]
     g = max(per_view) if per_view else 0
     gb = 0 if g == 0 else 1 << int(math.ceil(math.log2(g)))
-    return "%s|%s|v%d|%s|g%d" % (_arch(), mode, len(views),
-                                  ",".join("%dx%d" % r for r in res), gb)
+    return "%s|%s|%s|v%d|%s|g%d" % (_arch(), _lib.revision(), mode, len(views),
+                                    ",".join("%dx%d" % r for r in res), gb)
 
 
 def _load():
