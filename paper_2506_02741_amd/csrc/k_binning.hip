@@ -896,43 +896,59 @@ struct SortLds {
   unsigned long long buf[CAP];
   uint32_t bins[CAP + 4];
   uint32_t coarse[256], cbase[256];
-  uint32_t wsum[NT / kWave], zlo[NT / kWave], zhi[NT / kWave];
+  uint32_t wsum[NT / kWave], zlo[NT / kWave], zhi[NT / kWave], ilo[NT / kWave], ihi[NT / kWave];
 };
 
 constexpr uint32_t kMaxBucket = 48;  // keys of a bucket ranked by comparison
+// A list whose depths differ by less than this many steps of a float is
+// bucketed by depth and id together: on a plane seen face on, from its
+// keyframe's own pose, whole tiles have one depth or a few neighbouring ones.
+// (16 bits: with 16 of the id they fill a word; more steps than that already
+// divide finer than the buckets.)  Sorts of flat frames, with it, without
+// (every list bitonic) and by radix passes before there were buckets: one
+// 640x480 keyframe 10, 35 and 15 us, six of them 72, 165 and 206, a 64x48 one 9,
+// 24 and 10; frames of other depths take as long as without.
+constexpr uint32_t kNearDepths = 1u << 16;
 
 // Sort of one tile's n <= NT * E keys (depth bits << 32 | id, unique), written
 // to dst in ascending key order as D (u32: the ids, u64: the keys), by two
 // levels of buckets.  256 coarse buckets divide the list's own depth range
 // evenly; a coarse bucket of c keys is divided evenly into c fine ones, so
 // that surfaces that fill a small part of the range still get buckets of
-// their own.  Both maps are monotone in the depth, so a key's place is its
+// their own.  Both maps are monotone in the key, so a key's place is its
 // fine bucket's start plus its rank among that bucket's few keys, counted by
 // comparing whole keys.  Every pass is LDS atomics or independent reads, ~20
 // VALU instructions per key in all, against five dependent radix passes of
 // 23 or more before; a list of up to 1024 keys is spread over four waves, where one
 // wave had sorted it alone: tracking frame 15.8 -> 6.8 us, 5 views over 8
 // keyframes (lists of ~1,400) 560 -> 138.  Returns false, with dst untouched,
-// when a fine bucket holds more than kMaxBucket keys (many equal depths): a
-// bitonic sort, which needs no registers to speak of, takes those lists.
+// when a fine bucket holds more than kMaxBucket keys (many equal depths at a
+// few values far apart, of a sensor's steps): a bitonic sort, which needs no
+// registers to speak of, takes those lists (a room at 1 mm steps, lists of
+// 620, 1,240 and 3,730 keys: 25, 92 and 215 us against 26, 933 and 608 of the
+// radix passes).
 template <int NT, int E, typename D>
 __device__ __forceinline__ bool bucket_sort(const unsigned long long (&k)[E], D *dst, int n,
                                             SortLds<NT, E> &S) {
   constexpr int NW = NT / kWave;
   static_assert(E % 4 == 0, "fine buckets are scanned four at a time");
   const int t = threadIdx.x, l = lane_id(), w = t / kWave;
-  // (the sign bit flipped: signed comparisons in the keys' unsigned order)
-  int zlo = 0x7fffffff, zhi = (int)0x80000000;
+  // a word's range over the keys, wave by wave (the sign bit flipped: signed
+  // comparisons in the keys' unsigned order)
+  auto range = [&](int shift, uint32_t *lows, uint32_t *highs) {
+    int lo = 0x7fffffff, hi = (int)0x80000000;
 #pragma unroll
-  for (int e = 0; e < E; e++) {
-    const bool in = t + NT * e < n;
-    const int z = (int)((uint32_t)(k[e] >> 32) ^ 0x80000000u);
-    zlo = in ? min(zlo, z) : zlo;
-    zhi = in ? max(zhi, z) : zhi;
-  }
-  zlo = wave_min_i(zlo);
-  zhi = wave_max_i(zhi);
-  if (l == 0) { S.zlo[w] = (uint32_t)zlo ^ 0x80000000u; S.zhi[w] = (uint32_t)zhi ^ 0x80000000u; }
+    for (int e = 0; e < E; e++) {
+      const bool in = t + NT * e < n;
+      const int z = (int)((uint32_t)(k[e] >> shift) ^ 0x80000000u);
+      lo = in ? min(lo, z) : lo;
+      hi = in ? max(hi, z) : hi;
+    }
+    lo = wave_min_i(lo);
+    hi = wave_max_i(hi);
+    if (l == 0) { lows[w] = (uint32_t)lo ^ 0x80000000u; highs[w] = (uint32_t)hi ^ 0x80000000u; }
+  };
+  range(32, S.zlo, S.zhi);
   if (t < 256) S.coarse[t] = 0u;
   uint4 *bins4 = (uint4 *)S.bins;
 #pragma unroll
@@ -941,12 +957,32 @@ __device__ __forceinline__ bool bucket_sort(const unsigned long long (&k)[E], D 
   uint32_t lo = S.zlo[0], hi = S.zhi[0];
 #pragma unroll
   for (int i = 1; i < NW; i++) { lo = min(lo, S.zlo[i]); hi = max(hi, S.zhi[i]); }
-  const int shift = max(0, 24 - __clz((int)(hi - lo)));  // (hi - lo) >> shift < 256
-  // fine position within a coarse bucket: at most 16 bits of the depth
+  // a key's place in the list's range: its depth, and where the depths are near
+  // each other its id behind it (ib bits of the id's own range)
+  uint32_t ilo = 0u, most_place = hi - lo;
+  int ib = 0, is = 31;
+  if (hi - lo < kNearDepths) {
+    range(0, S.ilo, S.ihi);
+    __syncthreads();
+    uint32_t ihi = S.ihi[0];
+    ilo = S.ilo[0];
+#pragma unroll
+    for (int i = 1; i < NW; i++) { ilo = min(ilo, S.ilo[i]); ihi = max(ihi, S.ihi[i]); }
+    const int bits = 32 - __clz((int)(ihi - ilo));
+    ib = min(bits, 16);
+    is = bits - ib;
+    most_place = ((hi - lo) << ib) + ((ihi - ilo) >> is);
+  }
+  // (elsewhere no bit of the id is left: it is below 2^31)
+  auto place = [&](unsigned long long key) {
+    return (((uint32_t)(key >> 32) - lo) << ib) + (((uint32_t)key - ilo) >> is);
+  };
+  const int shift = max(0, 24 - __clz((int)most_place));  // most_place >> shift < 256
+  // fine position within a coarse bucket: at most 16 bits of the place
   const int fb = min(shift, 16), fs = shift - fb;
 #pragma unroll
   for (int e = 0; e < E; e++)
-    if (t + NT * e < n) atomicAdd(&S.coarse[((uint32_t)(k[e] >> 32) - lo) >> shift], 1u);
+    if (t + NT * e < n) atomicAdd(&S.coarse[place(k[e]) >> shift], 1u);
   __syncthreads();
   if (w == 0) {  // exclusive scan of the 256 coarse counts
     const uint4 c = ((const uint4 *)S.coarse)[l];
@@ -959,7 +995,7 @@ __device__ __forceinline__ bool bucket_sort(const unsigned long long (&k)[E], D 
 #pragma unroll
   for (int e = 0; e < E; e++) {
     if (t + NT * e >= n) continue;
-    const uint32_t z = (uint32_t)(k[e] >> 32) - lo, c = z >> shift;
+    const uint32_t z = place(k[e]), c = z >> shift;
     const uint32_t part = (z & ((1u << shift) - 1u)) >> fs;
     f[e] = S.cbase[c] + ((part * S.coarse[c]) >> fb);
     slot[e] = atomicAdd(&S.bins[f[e]], 1u);
