@@ -192,6 +192,7 @@ void layout(vtgs_plan *p) {
   take(p->r_tcount, nt * 4);  // (these three counter_pitch() apart)
   take(p->r_tcount_ns, nt * 4);
   take(p->r_tfill, nt * 4);
+  take(p->r_twist, nt * 32);
   take(p->r_woff, (nr + 63) / 64 * 64 * 4);
   take(p->r_ranges, nt * 8);
   take(p->r_long, nt * 4);
@@ -208,7 +209,6 @@ void layout(vtgs_plan *p) {
   take(p->r_last, P * 4);
   take(p->r_img, 5 * P * 4);
   take(p->r_gimg, 5 * P * 4);
-  take(p->r_twist, nt * 32);
   take(p->r_loss, nv * (int64_t)p->loss_blocks * 16);
   take(p->r_ssim_map, 9 * P * 8);
   take(p->r_ssim_part, nv * 3 * (int64_t)p->ssim_gx * p->ssim_gy * 4);
@@ -412,8 +412,8 @@ int track_iteration(vtgs_plan *p, const vtgs_track_cfg &cfg, float *loss, hipStr
 }
 
 // Point the plan at workspace `ws`: upload the descriptor tables from the
-// host copy `h` (pinned, or the plan's own), clear the header and the tile
-// counters, and drop graphs captured against the previous binding.
+// host copy `h` (pinned, or the plan's own), clear the header, the tile
+// counters and the views' (in the rows of the twist sums), and drop graphs captured against the previous binding.
 int bind_to(vtgs_plan *p, char *ws, const char *h, hipStream_t st) {
   if (!p->upload_done) HIP_OK(hipEventCreateWithFlags(&p->upload_done, hipEventDisableTiming));
   p->ws = ws;
@@ -425,9 +425,8 @@ int bind_to(vtgs_plan *p, char *ws, const char *h, hipStream_t st) {
   HIP_OK(hipMemcpyAsync(p->ws + p->r_desc.off, h, p->desc_bytes, hipMemcpyHostToDevice, st));
   HIP_OK(hipEventRecord(p->upload_done, st));
   HIP_OK(launch_fill_u32((uint32_t *)(p->ws + p->r_hdr.off), 0u, 64, st));
-  HIP_OK(launch_fill_u32(p->w.tile_count, 0u, p->n_tiles, st));
-  HIP_OK(launch_fill_u32(p->w.tile_fill, 0u, p->n_tiles, st));
-  HIP_OK(launch_fill_u32(p->w.tile_count_ns, 0u, p->n_tiles, st));
+  HIP_OK(launch_fill_u32(p->w.tile_count, 0u, 3 * counter_pitch(p->n_tiles), st));
+  HIP_OK(launch_fill_u32(reinterpret_cast<uint32_t *>(p->w.twist_part), 0u, 8 * (int64_t)p->n_tiles, st));
   p->bound = true;
   p->fwd_done = false;
   p->slots_done = false;

@@ -157,9 +157,9 @@ __device__ __forceinline__ void box_counts(const WaveBox &b, bool has, int x0, i
 // all: preprocess and fill take 0.19 + 0.30 ms with the wave walking such a
 // rectangle together, an atomic per pair (1.89 + 4.60 ms with its lane
 // alone), 0.08 + 0.04 ms with the list and the counters of kMidBox.  The line:
-// a listed record costs a test per tile of the plan (1.2 ns in all for 3,225
-// tiles), its pairs in a lane's walk 30 ps each; at 64 the list is still no
-// slower with eight views in the plan.
+// a listed record costs a test per tile of its view (1.2 ns in all for 3,225
+// tiles, less where most have none), its pairs in a lane's walk 30 ps each; at
+// 64 (81 tiles a record) the list is faster in plans of one to forty views.
 constexpr int kLaneTiles = 64;
 
 // The lanes standing at the same tile as this one: the first of them, their
@@ -199,28 +199,48 @@ __device__ __forceinline__ bool is_wide(bool has, int x0, int y0, int x1, int y1
 }
 
 // The list: (record, depth bits, rectangle) in the buffer of the tile sort's
-// runs, which is free until then.
+// runs, which is free until then.  Half of it is divided among the views by
+// their records, so that a tile's wave reads its own view's alone (with one
+// list for all views the fill grew by their square: 300 views of 300 tiles with
+// 200 such records each took 2.11 ms, against 0.20; without any of them 0.10);
+// the other half takes what a view's part does not (views of few records with
+// many wide ones, in plans of little capacity).
 __device__ __forceinline__ uint4 *wide_list(const Ws &ws) {
   return reinterpret_cast<uint4 *>(ws.keys_tmp);
 }
-__device__ __forceinline__ int64_t wide_cap(const Ws &ws) { return ws.cap / 2; }
+struct WidePart {
+  int64_t first;
+  uint32_t n;
+};
+__device__ __forceinline__ WidePart wide_part(const Ws &ws, int64_t rec_base, int64_t n_rec) {
+  const int64_t half = ws.cap / 4, first = half * rec_base / ws.n_rec;
+  return {first, (uint32_t)(half * (rec_base + n_rec) / ws.n_rec - first)};
+}
+__device__ __forceinline__ WidePart wide_rest(const Ws &ws) {
+  return {ws.cap / 4, (uint32_t)(ws.cap / 2 - ws.cap / 4)};
+}
+// Records past the rest's end are left out: each has more than kLaneTiles
+// pairs, so the pass is over the pair capacity anyway; it counts its pairs and
+// leaves all lists empty.
+__device__ __forceinline__ bool wide_fit(const Ws &ws) { return ws.n_wide[kWideRest] <= wide_rest(ws).n; }
 
-// The wave's wide records into the list (records past its capacity are left
-// out: each has more than kLaneTiles pairs, so the pass is over the pair
-// capacity anyway; it counts its pairs and leaves all lists empty) and their rows into
-// the difference array, one interval for all rows of a rectangle as wide as
-// the view.
-__device__ __forceinline__ void add_wide(const Ws &ws, bool wide, int r, uint32_t zbits, int x0, int y0,
-                                         int x1, int y1, int tiles_x, int t0) {
-  const unsigned long long m = ballot64(wide);
-  if (!m) return;
-  uint32_t first = 0u;
-  if (lane_id() == 0) first = atomicAdd(ws.n_wide, (uint32_t)__popcll(m));
-  first = (uint32_t)__builtin_amdgcn_readlane((int)first, 0);
+// The wave's wide records into the list and their rows into the difference
+// array, one interval for all rows of a rectangle as wide as the view.
+__device__ __forceinline__ void add_wide(const Ws &ws, bool wide, int view, int r, uint32_t zbits, int x0,
+                                         int y0, int x1, int y1, int tiles_x, int t0) {
   if (!wide) return;
-  const int64_t i = (int64_t)first + __popcll(m & lanemask_lt());
+  ws.n_wide[0] = 1u;
+  const SameTile sv = same_tile(true, view);
+  uint32_t i = 0u;
+  if (sv.rank == 0u) i = atomicAdd(view_wide(ws, t0), sv.n);
+  i = (uint32_t)__shfl((int)i, sv.first) + sv.rank;
+  WidePart part = wide_part(ws, ws.views[view].rec_base, ws.views[view].n_rec);
+  if (i >= part.n) {
+    part = wide_rest(ws);
+    i = atomicAdd(ws.n_wide + kWideRest, 1u);
+  }
   const uint2 rc = pack_rect(x0, y0, x1, y1);
-  if (i < wide_cap(ws)) wide_list(ws)[i] = make_uint4((uint32_t)r, zbits, rc.x, rc.y);
+  if (i < part.n) wide_list(ws)[part.first + i] = make_uint4((uint32_t)r, zbits, rc.x, rc.y);
   const bool full = x0 == 0 && x1 == tiles_x - 1;
   const int rows = full ? 1 : y1 - y0 + 1, len = full ? (y1 - y0 + 1) * tiles_x : x1 - x0 + 1;
   for (int q = 0; q < rows; q++) {
@@ -234,41 +254,53 @@ __device__ __forceinline__ void add_wide(const Ws &ws, bool wide, int r, uint32_
 
 // The wide records' keys, at the ends of the lists of the tiles that they
 // cover: a wave takes a tile, its lanes the list's records, 64 at a time, U
-// of these chunks in flight.
+// of these chunks in flight, until the tile has as many as were counted.
 template <int U, typename Range>
-__device__ __forceinline__ void fill_wide(const Ws &ws, uint32_t n, int wave, int n_waves, Range range) {
-  if ((int64_t)n > wide_cap(ws)) return;
+__device__ __forceinline__ void fill_wide(const Ws &ws, uint32_t n_rest, uint32_t n_first, int wave, int n_waves,
+                                          Range range) {
+  if (n_rest > wide_rest(ws).n) return;
   for (int t = wave; t < ws.n_tiles; t += n_waves) {
     const uint2 rg = range(t);
+    // (of a list cut off at the capacity: the positions past the others)
+    const uint32_t others = ws.tile_count[t] + ws.tile_count_ns[t];
+    uint32_t left = rg.y - rg.x - min(rg.y - rg.x, others);
+    if (!left) continue;
+    uint32_t end = rg.y;
     int lo = 0, hi = ws.n_views - 1;
     while (lo < hi) {
       const int mid = (lo + hi + 1) >> 1;
       if (ws.views[mid].tile_base <= t) lo = mid; else hi = mid - 1;
     }
-    const uint32_t r0 = ws.views[lo].rec_base, r1 = lo + 1 < ws.n_views ? ws.views[lo + 1].rec_base : ws.n_rec;
-    const int tiles_x = ws.views[lo].tiles_x, at = t - ws.views[lo].tile_base;
+    const DevView &vw = ws.views[lo];
+    const uint32_t r0 = vw.rec_base, r1 = r0 + vw.n_rec;
+    const int tiles_x = vw.tiles_x, at = t - vw.tile_base;
     const int ty = at / tiles_x, tx = at - ty * tiles_x;
-    uint32_t left = rg.y - rg.x;
-    for (uint32_t c = 0; c < n && left; c += U * kWave) {
-      uint4 e[U];
+    auto walk = [&](const uint4 *list, uint32_t n) {
+      for (uint32_t c = 0; c < n && left; c += U * kWave) {
+        uint4 e[U];
 #pragma unroll
-      for (int u = 0; u < U; u++) e[u] = wide_list(ws)[min(c + u * kWave + lane_id(), n - 1)];
+        for (int u = 0; u < U; u++) e[u] = list[min(c + u * kWave + lane_id(), n - 1)];
 #pragma unroll
-      for (int u = 0; u < U; u++) {
-        int x0, y0, x1, y1;
-        unpack_rect(make_uint2(e[u].z, e[u].w), x0, y0, x1, y1);
-        const bool in = c + u * kWave + lane_id() < n && e[u].x >= r0 && e[u].x < r1 && x0 <= tx &&
-                        tx <= x1 && y0 <= ty && ty <= y1;
-        const unsigned long long m = ballot64(in);
-        const uint32_t rank = (uint32_t)__popcll(m & lanemask_lt());
-        if (in && rank < left)
-          ws.keys[rg.x + (left - 1u - rank)] = ((unsigned long long)e[u].y << 32) | (e[u].x - r0);
-        left -= min(left, (uint32_t)__popcll(m));
+        for (int u = 0; u < U; u++) {
+          int x0, y0, x1, y1;
+          unpack_rect(make_uint2(e[u].z, e[u].w), x0, y0, x1, y1);
+          const bool in = c + u * kWave + lane_id() < n && e[u].x >= r0 && e[u].x < r1 && x0 <= tx &&
+                          tx <= x1 && y0 <= ty && ty <= y1;
+          const unsigned long long m = ballot64(in);
+          const uint32_t rank = (uint32_t)__popcll(m & lanemask_lt());
+          if (in && rank < left)
+            ws.keys[end - 1u - rank] = ((unsigned long long)e[u].y << 32) | (e[u].x - r0);
+          const uint32_t n_in = min(left, (uint32_t)__popcll(m));
+          left -= n_in;
+          end -= n_in;
+        }
       }
-    }
+    };
+    const WidePart part = wide_part(ws, r0, vw.n_rec);
+    walk(wide_list(ws) + part.first, min(lo ? *view_wide(ws, vw.tile_base) : n_first, part.n));
+    walk(wide_list(ws) + wide_rest(ws).first, n_rest);
   }
 }
-
 
 // A load through a descriptor's pointer, which addresses global memory:
 // read as such (the compiler cannot tell, and would issue a flat load).
@@ -494,7 +526,7 @@ __global__ __attribute__((amdgpu_waves_per_eu(8))) __launch_bounds__(kNT) void k
         if (w.ty <= last && s.rank == 0u) atomicAdd(ws.tile_count_ns + t, s.n);
       }
     }
-    add_wide(ws, wide, r, o.zbits, x0, y0, x1, y1, tiles_x, tile_base);
+    add_wide(ws, wide, view, r, o.zbits, x0, y0, x1, y1, tiles_x, tile_base);
   }
 }
 
@@ -552,7 +584,7 @@ __device__ __forceinline__ uint2 list_range(unsigned long long pos, uint32_t n, 
 constexpr int kFillPer = kFillTiles / kNT;
 __device__ __forceinline__ void scan_in_fill(const Ws &ws, uint32_t n_wide, bool store, uint2 *range,
                                              uint32_t *lw) {
-  const unsigned long long cap = (int64_t)n_wide <= wide_cap(ws) ? ws.cap : 0;
+  const unsigned long long cap = !n_wide || wide_fit(ws) ? ws.cap : 0;
   const int i0 = threadIdx.x * kFillPer;
   uint32_t v[kFillPer], sum = 0u, tot;
 #pragma unroll
@@ -602,7 +634,7 @@ __global__ __launch_bounds__(kScanNT) void k_scan_tiles(Ws ws, int n_groups) {
   if (threadIdx.x == 0) { carry_s = 0; nlong_s = 0; nhuge_s = 0; wide_s = 0; }
   // wide records: their rows' ends in tile_fill become counts per tile
   const uint32_t n_wide = ws.n_wide[0];
-  const unsigned long long cap = (int64_t)n_wide <= wide_cap(ws) ? ws.cap : 0;
+  const unsigned long long cap = !n_wide || wide_fit(ws) ? ws.cap : 0;
   if (threadIdx.x < kOrderBuckets) bk[threadIdx.x] = 0u;
   __syncthreads();
   // a plan of one round keeps its tiles' buckets and their ranks there
@@ -717,9 +749,10 @@ __global__ __launch_bounds__(kNT) void k_fill_keys(Ws ws, int rec_blocks, int wi
   };
   if ((int)blockIdx.x >= rec_blocks) {
     constexpr int kWaves = kNT / kWave;
+    const uint32_t n_rest = ws.n_wide[kWideRest], n_first = *view_wide(ws, 0);
     if (!n_wide) return;
     if (kScan) scan_in_fill(ws, n_wide, false, range_s, lw);
-    fill_wide<4>(ws, n_wide, (blockIdx.x - rec_blocks) * kWaves + threadIdx.x / kWave,
+    fill_wide<4>(ws, n_rest, n_first, (blockIdx.x - rec_blocks) * kWaves + threadIdx.x / kWave,
                  wide_blocks * kWaves, range);
     return;
   }
@@ -1099,8 +1132,10 @@ __launch_bounds__(NT) void k_sort_tiles(Ws ws, int lo_n, int hi_n, int queue) {
     const int64_t pitch = counter_pitch(ws.n_tiles);
     for (int a = 0; a < 3; a++)
       if (i < ws.n_tiles) ws.tile_count[a * pitch + i] = 0u;
+    if (i < ws.n_views) *view_wide(ws, ws.views[i].tile_base) = 0u;
     if (i == 0) {
-      ws.n_long[kWideWord] = 0u;
+      ws.n_wide[0] = 0u;
+      ws.n_wide[kWideRest] = 0u;
       odd_records(ws)[1] = odd_records(ws)[0];
       odd_records(ws)[0] = 0u;
     }

@@ -69,6 +69,8 @@ constexpr int kFillTiles = 512;
 // from n_long to n_wide.
 __host__ __device__ inline int64_t counter_pitch(int64_t n_tiles) { return (n_tiles + 63) / 64 * 64; }
 constexpr int kWideWord = 2;
+// Word of n_wide that counts the wide records past their view's part of the list.
+constexpr int kWideRest = 4;
 
 enum : uint32_t { kFlagCapacity = 1u, kFlagNonfinite = 2u };
 
@@ -79,7 +81,8 @@ struct Ws {
   unsigned long long *n_pairs;
   uint32_t *iter;              // tracking iteration counter (bumped by preprocess)
   uint32_t *n_long;            // [2] tiles with lists for the mid and the huge-list sort
-  uint32_t *n_wide;            // [2] wide records of this pass, so far and (by the scan) in all
+  uint32_t *n_wide;            // [2] whether this pass has wide records, so far and (by the
+                               // scan) at all; odd_records; [kWideRest]
   uint32_t *long_tiles;        // [n_tiles] the queues, huge lists from the end (by the scan)
   uint32_t *tile_order;        // [n_tiles] compositing order, longest lists first (NULL: tile order)
   // descriptors
@@ -126,7 +129,8 @@ struct Ws {
   uint32_t *last;              // [P] contributors end (relative to tile start)
   float *img;                  // [5][P] internal rgb(3), depth, sil
   float *gimg;                 // [5][P] internal upstream gradients
-  float *twist_part;           // [n_tiles][8]: six twist sums, the Eq. 1 loss, one unused
+  float *twist_part;           // [n_tiles][8]: six twist sums, the Eq. 1 loss, and
+                               // in the row of a view's first tile its wide records
   float *loss_part;            // [n_views][loss_blocks][4]
   double *ssim_map;            // [3 kinds][3 ch][P], FP64
   float *ssim_part;            // [n_views][3][loss_blocks]
@@ -228,6 +232,11 @@ __device__ __forceinline__ uint32_t block_exclusive_scan(uint32_t v, uint32_t *l
 // not finite, in this pass so far (by the preprocess) and in the last one
 // binned (by the tile sort).
 __device__ __forceinline__ uint32_t *odd_records(const Ws &ws) { return ws.n_wide + kWideWord; }
+
+// The wide records so far of the view whose first tile is tile_base.
+__device__ __forceinline__ uint32_t *view_wide(const Ws &ws, int64_t tile_base) {
+  return reinterpret_cast<uint32_t *>(ws.twist_part) + 8 * tile_base + 7;
+}
 
 __device__ __forceinline__ bool all_finite(float a, float b, float c, float d) {
   // (0 x is 0 for finite x only)
