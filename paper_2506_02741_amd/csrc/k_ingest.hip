@@ -18,17 +18,23 @@ constexpr int kCells = kNT * kPer;      // grid cells per block
 // took 23 us for the fill and 4.4 for the counts, this takes 9.6 and 3.9 (the
 // fill moves 36 MB, 7.6 us).
 struct Cells {
-  uint32_t gx, gy;
+  uint32_t gx, gy, rows, cols;  // (rows, cols: 64 cells on, in a grid of nx columns)
   int64_t c;
   __device__ __forceinline__ Cells(int64_t first, int nx) : c(first + lane_id()) {
     // (an image has fewer than 2^31 pixels)
     gy = (uint32_t)c / (uint32_t)nx;
     gx = (uint32_t)c - gy * (uint32_t)nx;
+    rows = (uint32_t)kWave / (uint32_t)nx;
+    cols = (uint32_t)kWave - rows * (uint32_t)nx;
   }
+  // (row by row, an image of one column took 15.3 us for the fill, this 5.3)
   __device__ __forceinline__ void next(int nx) {
     c += kWave;
-    gx += kWave;
-    while (gx >= (uint32_t)nx) { gx -= (uint32_t)nx; gy++; }
+    gx += cols;
+    gy += rows;
+    const bool over = gx >= (uint32_t)nx;
+    gx -= over ? (uint32_t)nx : 0u;
+    gy += over ? 1u : 0u;
   }
   __device__ __forceinline__ int64_t pixel(int W, int s) const {
     return (int64_t)((int)gy * s) * W + (int)gx * s;
