@@ -22,19 +22,22 @@ namespace vtgs {
 
 namespace {
 
-constexpr int kVisNT = 1024;
+// A mask alone needs no counts, and small blocks fill the device better: 640x480
+// against three targets 7.6 us in blocks of 1024, 6.9 in blocks of 256.
+constexpr int kVisNT = 1024, kVisMaskNT = 256;
 
-__global__ __launch_bounds__(kVisNT) void k_visibility(const float *src_depth, VisCam sc,
+template <int NT>
+__global__ __launch_bounds__(NT) void k_visibility(const float *src_depth, VisCam sc,
                                                        const float *src_pose, VisTargets tg,
                                                        float tol, float znear, uint8_t *mask,
                                                        int32_t *counts, int first) {
   __shared__ float Ms[kVisMaxTargets][12];
-  __shared__ int32_t wave_cnt[kVisNT / kWave][kVisMaxTargets];
+  __shared__ int32_t wave_cnt[NT / kWave][kVisMaxTargets];
   static_assert(kVisMaxTargets <= kWave, "lane t of a wave keeps target t's count");
   if (threadIdx.x < (unsigned)tg.n) relative_pose(tg.pose[threadIdx.x], src_pose, Ms[threadIdx.x]);
   __syncthreads();
   const int64_t P = (int64_t)sc.width * sc.height;
-  const int64_t p = (int64_t)blockIdx.x * kVisNT + threadIdx.x;
+  const int64_t p = (int64_t)blockIdx.x * NT + threadIdx.x;
   const bool in = p < P;
   const float d = in ? src_depth[p] : 0.f;
   const int u = in ? (int)(p % sc.width) : 0, v = in ? (int)(p / sc.width) : 0;
@@ -77,7 +80,7 @@ __global__ __launch_bounds__(kVisNT) void k_visibility(const float *src_depth, V
     __syncthreads();
     if (threadIdx.x < (unsigned)tg.n) {
       int32_t c = 0;
-      for (int w = 0; w < kVisNT / kWave; w++) c += wave_cnt[w][threadIdx.x];
+      for (int w = 0; w < NT / kWave; w++) c += wave_cnt[w][threadIdx.x];
       if (c) atomicAdd(&counts[threadIdx.x], c);
     }
   }
@@ -91,8 +94,12 @@ hipError_t launch_visibility(const float *src_depth, const VisCam &sc, const flo
                              int32_t *counts, int first, hipStream_t st) {
   const int64_t P = (int64_t)sc.width * sc.height;
   if (P <= 0) return hipSuccess;
-  hipLaunchKernelGGL(k_visibility, dim3((unsigned)((P + kVisNT - 1) / kVisNT)), dim3(kVisNT), 0, st,
-                     src_depth, sc, src_pose, tg, tol, znear, mask, counts, first);
+  auto launch = [&](auto kernel, int nt) {
+    hipLaunchKernelGGL(kernel, dim3((unsigned)((P + nt - 1) / nt)), dim3(nt), 0, st, src_depth, sc,
+                       src_pose, tg, tol, znear, mask, counts, first);
+  };
+  if (counts) launch(k_visibility<kVisNT>, kVisNT);
+  else launch(k_visibility<kVisMaskNT>, kVisMaskNT);
   return hipGetLastError();
 }
 
