@@ -183,7 +183,7 @@ void layout(vtgs_plan *p) {
   take(p->r_desc, p->desc_bytes);
   const int64_t nr = p->n_rec, nt = p->n_tiles, cap = p->cap, P = p->P;
   take(p->r_recA, nr * 48);
-  take(p->r_recB, nr * 16);
+  take(p->r_recB, nr * 8);
   take(p->r_rect, nr * 8);
   take(p->r_rec_cnt, nr * 4);
   take(p->r_zbits, nr * 4);
