@@ -922,10 +922,13 @@ __device__ void merge_round(const unsigned long long *in, D *out, int n, int wid
   }
 }
 
-// The LDS of a tile sort: the keys, the buckets and small tables.
+// The LDS of a tile sort: the keys, the buckets and small tables (bins, coarse
+// and cbase are also read four words at a time: 16 bytes, and sizes that keep
+// the arrays before them at multiples of 16).
 template <int NT, int E>
-struct SortLds {
+struct alignas(16) SortLds {
   static constexpr int CAP = NT * E;
+  static_assert(CAP % 4 == 0, "bins, coarse and cbase begin at multiples of 16 bytes");
   unsigned long long buf[CAP];
   uint32_t bins[CAP + 4];
   uint32_t coarse[256], cbase[256];
