@@ -126,7 +126,10 @@ typedef struct {
   float lowpass;             /* added to Sigma_2D diagonal (default 0.3 px^2)  */
   float bg[3];               /* background colour (default 0)                  */
   int32_t tile;              /* 8, 16 or 32 (default 16)                       */
-  int32_t batch;             /* LDS batch of Gaussians: 128, 256, 512 (default 256) */
+  int32_t batch;             /* list entries per pass: 128, 256, 512 (default 256).
+                                A measure of speed only: with 16-pixel tiles 256 is
+                                512 in the forward and 384 in the backward to the
+                                twist, whose passes keep less per entry            */
 } vtgs_params;
 
 /* Eq. 1 weights and pose learning rates (App. A); sil_thr is the coverage

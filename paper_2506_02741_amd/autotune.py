@@ -1,7 +1,7 @@
 """Autotuner of the compositing launch shape.
 
 For a workload (keyframes, views, mode) the tuner sweeps tile size
-{8, 16, 32} x LDS batch {128, 256, 512}, times the forward + backward of
+{8, 16, 32} x batch {128, 256, 512}, times the forward + backward of
 each configuration with the library's per-stage HIP events, and keeps the
 fastest.  Results are cached per shape bucket in a JSON file:
 

@@ -631,11 +631,14 @@ int vtgs_plan_create(const vtgs_keyframe *kfs, int32_t n_kf, const vtgs_view *vi
     // lengths share a grid (a multi-view plan), and where the tiles are more
     // than the device composites at once (four blocks per CU, three in the
     // backward to slots; 64-thread blocks of 8-pixel tiles: four times that), so
-    // that its last blocks are short ones (three frames of 1,200 tiles, 20
-    // tracking iterations: 2497, 2466, 2620 us in the image's order, 2475,
-    // 2425, 2477 sorted; four views of 3,225, forward alone: 334, 104, 130, 325
-    // and 289, 105, 134, 281; below, every block starts at once and the
-    // order only costs the scan ~1 us); VTGS_TILE_ORDER=0 / 1 forces it
+    // that its last blocks are short ones.  The counts are those of the default
+    // batch; other shapes hold fewer blocks, and the line is the same for them.
+    // In the image's order and sorted: 10 tracking iterations of 1,200 tiles 1552
+    // and 1492 us, of 4,800 8-pixel tiles 1616 and 1601; two views' gradients, 939 and
+    // 824 (8 pixels: 867 and 816, 32: 2558 and 2532); but one view of 3,225 tiles,
+    // forward alone, 273 and 279, of 12,750 8-pixel ones 730 and 740.  Below, every
+    // block starts at once and the order only costs the scan (817 tiles of 32
+    // pixels, forward: 304 and 328).  VTGS_TILE_ORDER=0 / 1 forces it
     const int64_t at_once = (p->any_learnable ? 768 : 1024) * (P.tile == 8 ? 4 : 1);
     {
       const char *e = std::getenv("VTGS_TILE_ORDER");

@@ -580,7 +580,8 @@ __device__ __forceinline__ uint2 list_range(unsigned long long pos, uint32_t n, 
 // itself, the first one stores the results.  With 75 blocks and 80 tiles
 // (160x120) the fill takes 4.8 us with or without it and the scan's launch
 // (4.7 us) is saved; with 1,200 and 1,200 (640x480) it took 14.6 us instead of
-// 4.8 + 5.9.
+// 4.8 + 5.9.  At the line, with about 510 blocks: a render of 512 tiles takes 44.0
+// us, one of 520 with the scan 47.0 (stride 2, 125 blocks: 30.1 and 33.9).
 constexpr int kFillPer = kFillTiles / kNT;
 __device__ __forceinline__ void scan_in_fill(const Ws &ws, uint32_t n_wide, bool store, uint2 *range,
                                              uint32_t *lw) {
@@ -956,8 +957,8 @@ constexpr uint32_t kNearDepths = 1u << 16;
 // comparing whole keys.  Every pass is LDS atomics or independent reads, ~20
 // VALU instructions per key in all, against five dependent radix passes of
 // 23 or more before; a list of up to 1024 keys is spread over four waves, where one
-// wave had sorted it alone: tracking frame 15.8 -> 6.8 us, 5 views over 8
-// keyframes (lists of ~1,400) 560 -> 138.  Returns false, with dst untouched,
+// wave had sorted it alone: tracking frame 15.8 -> 6.8 us (9.3 with the clearing
+// of the counters, which this kernel does too), 5 views over 8 keyframes (lists of ~1,400) 560 -> 138.  Returns false, with dst untouched,
 // when a fine bucket holds more than kMaxBucket keys (many equal depths at a
 // few values far apart, of a sensor's steps): a bitonic sort, which needs no
 // registers to speak of, takes those lists (a room at 1 mm steps, lists of

@@ -1275,9 +1275,10 @@ hipError_t fwd_tile(const Ws &ws, float *rgb, float *depth, float *sil, hipStrea
     // twice as long takes fewer steps (a lane waits less for its wave's
     // busiest) and fewer barriers, and at four blocks per CU it still beats
     // 256 at five: 12 tiles 30 -> 22 us, 80 tiles 32 -> 23, 1,200 tiles 44 ->
-    // 41, 6,000 tiles of 1,400 entries 848 -> 758; only lists that fill
-    // neither lose (3,225 tiles of a stride-2 map 88 -> 105). 384 at five
-    // blocks lies between (42, 816 and 101 us).
+    // 41, 6,000 tiles of 1,400 entries 848 -> 758.  Only large grids of lists that
+    // fill no pass lose: 3,225 tiles of a stride-2 map 110 us in passes of 128,
+    // 125 in these (139 before the coverage was a matrix product); batch 128
+    // remains for them.
     case 256: return fwd_launch<TILE, TILE == 16 ? 512 : 256>(ws, rgb, depth, sil, st);
     case 512: return fwd_launch<TILE, 512>(ws, rgb, depth, sil, st);
   }
