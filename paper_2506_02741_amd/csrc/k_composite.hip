@@ -663,7 +663,7 @@ __device__ __forceinline__ void store_twist(const Ws &ws, int t, const float (&t
 // steps amplifies any other rounding of the twist.  Against that kernel's form
 // without slots, in 256-entry batches with five 16-byte reads a step: 640x480
 // tracking frame 55 -> 49 us, 160x120 42 -> 31, a batch of served tracks 1166
-// -> 1026; bound by VALU issue (~60 %) and the waits of four waves per SIMD.
+// -> 1026; bound by VALU issue (72 %) and the waits of four waves per SIMD.
 template <int TILE, int BATCH, bool kTrack>
 __global__ __attribute__((amdgpu_waves_per_eu(TILE == 16 ? 4 : 2))) __launch_bounds__(
     Shape<TILE>::NT) void k_bwd_twist(Ws ws, const float *g_rgb, const float *g_depth,
