@@ -108,7 +108,7 @@ struct vtgs_plan {
   bool any_geo = false;  // a learnable keyframe wants depth / pose gradients
   bool tile_order = false;  // composite the longest tile lists first
   // workspace layout
-  Region r_hdr, r_desc, r_recA, r_recB, r_rect, r_rec_cnt, r_zbits, r_rec_off, r_scan, r_tcount, r_tcount_ns, r_tfill, r_woff,
+  Region r_hdr, r_desc, r_recA, r_recB, r_rect, r_rec_cnt, r_zbits, r_rec_off, r_scan, r_tcount, r_tcount_ns, r_tfill, r_vwide, r_woff,
       r_ranges, r_long, r_order, r_keys, r_keys_tmp, r_ids, r_slots, r_kpose, r_bits, r_tfinal, r_last,
       r_img, r_gimg, r_twist, r_loss, r_ssim_map, r_ssim_part;
   int64_t desc_kf = 0, desc_view = 0, desc_seg = 0, desc_use_off = 0, desc_use = 0, desc_bytes = 0;
@@ -192,7 +192,7 @@ void layout(vtgs_plan *p) {
   take(p->r_tcount, nt * 4);  // (these three counter_pitch() apart)
   take(p->r_tcount_ns, nt * 4);
   take(p->r_tfill, nt * 4);
-  take(p->r_twist, nt * 32);
+  take(p->r_vwide, nv * kViewPitch * 4);  // (right behind them, cleared with them)
   take(p->r_woff, (nr + 63) / 64 * 64 * 4);
   take(p->r_ranges, nt * 8);
   take(p->r_long, nt * 4);
@@ -209,6 +209,7 @@ void layout(vtgs_plan *p) {
   take(p->r_last, P * 4);
   take(p->r_img, 5 * P * 4);
   take(p->r_gimg, 5 * P * 4);
+  take(p->r_twist, nt * 32);
   take(p->r_loss, nv * (int64_t)p->loss_blocks * 16);
   take(p->r_ssim_map, 9 * P * 8);
   take(p->r_ssim_part, nv * 3 * (int64_t)p->ssim_gx * p->ssim_gy * 4);
@@ -248,6 +249,7 @@ void make_ws(vtgs_plan *p) {
   w.n_tiles = p->n_tiles;
   w.P = p->P;
   w.cap = p->cap;
+  w.wide_part = (uint32_t)std::min<int64_t>(65536, ((p->cap / 4) << 16) / std::max(p->n_rec, 1));
   w.recA = at<float4>(b, p->r_recA);
   w.recB = at<float2>(b, p->r_recB);
   w.rect = at<uint2>(b, p->r_rect);
@@ -413,7 +415,7 @@ int track_iteration(vtgs_plan *p, const vtgs_track_cfg &cfg, float *loss, hipStr
 
 // Point the plan at workspace `ws`: upload the descriptor tables from the
 // host copy `h` (pinned, or the plan's own), clear the header, the tile
-// counters and the views' (in the rows of the twist sums), and drop graphs captured against the previous binding.
+// counters and the views', and drop graphs captured against the previous binding.
 int bind_to(vtgs_plan *p, char *ws, const char *h, hipStream_t st) {
   if (!p->upload_done) HIP_OK(hipEventCreateWithFlags(&p->upload_done, hipEventDisableTiming));
   p->ws = ws;
@@ -425,8 +427,8 @@ int bind_to(vtgs_plan *p, char *ws, const char *h, hipStream_t st) {
   HIP_OK(hipMemcpyAsync(p->ws + p->r_desc.off, h, p->desc_bytes, hipMemcpyHostToDevice, st));
   HIP_OK(hipEventRecord(p->upload_done, st));
   HIP_OK(launch_fill_u32((uint32_t *)(p->ws + p->r_hdr.off), 0u, 64, st));
-  HIP_OK(launch_fill_u32(p->w.tile_count, 0u, 3 * counter_pitch(p->n_tiles), st));
-  HIP_OK(launch_fill_u32(reinterpret_cast<uint32_t *>(p->w.twist_part), 0u, 8 * (int64_t)p->n_tiles, st));
+  HIP_OK(launch_fill_u32(p->w.tile_count, 0u,
+                         3 * counter_pitch(p->n_tiles) + kViewPitch * (int64_t)p->views.size(), st));
   p->bound = true;
   p->fwd_done = false;
   p->slots_done = false;

@@ -213,31 +213,35 @@ struct WidePart {
   uint32_t n;
 };
 __device__ __forceinline__ WidePart wide_part(const Ws &ws, int64_t rec_base, int64_t n_rec) {
-  const int64_t half = ws.cap / 4, first = half * rec_base / ws.n_rec;
-  return {first, (uint32_t)(half * (rec_base + n_rec) / ws.n_rec - first)};
+  const int64_t first = rec_base * ws.wide_part >> 16;
+  return {first, (uint32_t)(((rec_base + n_rec) * ws.wide_part >> 16) - first)};
 }
 __device__ __forceinline__ WidePart wide_rest(const Ws &ws) {
   return {ws.cap / 4, (uint32_t)(ws.cap / 2 - ws.cap / 4)};
 }
-// Records past the rest's end are left out: each has more than kLaneTiles
-// pairs, so the pass is over the pair capacity anyway; it counts its pairs and
-// leaves all lists empty.
-__device__ __forceinline__ bool wide_fit(const Ws &ws) { return ws.n_wide[kWideRest] <= wide_rest(ws).n; }
+// The first word of n_wide: whether the pass has such records, and whether there
+// were more than the rest holds.  Those past its end are left out: each has more
+// than kLaneTiles pairs, so the pass is over the pair capacity anyway; it counts
+// its pairs and leaves all lists empty.
+constexpr uint32_t kWideAny = 1u, kWideFull = 2u;
 
 // The wave's wide records into the list and their rows into the difference
 // array, one interval for all rows of a rectangle as wide as the view.
 __device__ __forceinline__ void add_wide(const Ws &ws, bool wide, int view, int r, uint32_t zbits, int x0,
                                          int y0, int x1, int y1, int tiles_x, int t0) {
   if (!wide) return;
-  ws.n_wide[0] = 1u;
   const SameTile sv = same_tile(true, view);
   uint32_t i = 0u;
-  if (sv.rank == 0u) i = atomicAdd(view_wide(ws, t0), sv.n);
+  if (sv.rank == 0u) {
+    i = atomicAdd(view_wide(ws, view), sv.n);
+    if (i == 0u) atomicOr(ws.n_wide, kWideAny);
+  }
   i = (uint32_t)__shfl((int)i, sv.first) + sv.rank;
   WidePart part = wide_part(ws, ws.views[view].rec_base, ws.views[view].n_rec);
   if (i >= part.n) {
     part = wide_rest(ws);
     i = atomicAdd(ws.n_wide + kWideRest, 1u);
+    if (i == part.n) atomicOr(ws.n_wide, kWideFull);
   }
   const uint2 rc = pack_rect(x0, y0, x1, y1);
   if (i < part.n) wide_list(ws)[part.first + i] = make_uint4((uint32_t)r, zbits, rc.x, rc.y);
@@ -258,7 +262,6 @@ __device__ __forceinline__ void add_wide(const Ws &ws, bool wide, int view, int 
 template <int U, typename Range>
 __device__ __forceinline__ void fill_wide(const Ws &ws, uint32_t n_rest, uint32_t n_first, int wave, int n_waves,
                                           Range range) {
-  if (n_rest > wide_rest(ws).n) return;
   for (int t = wave; t < ws.n_tiles; t += n_waves) {
     const uint2 rg = range(t);
     // (of a list cut off at the capacity: the positions past the others)
@@ -297,7 +300,7 @@ __device__ __forceinline__ void fill_wide(const Ws &ws, uint32_t n_rest, uint32_
       }
     };
     const WidePart part = wide_part(ws, r0, vw.n_rec);
-    walk(wide_list(ws) + part.first, min(lo ? *view_wide(ws, vw.tile_base) : n_first, part.n));
+    walk(wide_list(ws) + part.first, min(lo ? *view_wide(ws, lo) : n_first, part.n));
     walk(wide_list(ws) + wide_rest(ws).first, n_rest);
   }
 }
@@ -585,7 +588,7 @@ __device__ __forceinline__ uint2 list_range(unsigned long long pos, uint32_t n, 
 constexpr int kFillPer = kFillTiles / kNT;
 __device__ __forceinline__ void scan_in_fill(const Ws &ws, uint32_t n_wide, bool store, uint2 *range,
                                              uint32_t *lw) {
-  const unsigned long long cap = !n_wide || wide_fit(ws) ? ws.cap : 0;
+  const unsigned long long cap = n_wide & kWideFull ? 0 : ws.cap;
   const int i0 = threadIdx.x * kFillPer;
   uint32_t v[kFillPer], sum = 0u, tot;
 #pragma unroll
@@ -635,7 +638,7 @@ __global__ __launch_bounds__(kScanNT) void k_scan_tiles(Ws ws, int n_groups) {
   if (threadIdx.x == 0) { carry_s = 0; nlong_s = 0; nhuge_s = 0; wide_s = 0; }
   // wide records: their rows' ends in tile_fill become counts per tile
   const uint32_t n_wide = ws.n_wide[0];
-  const unsigned long long cap = !n_wide || wide_fit(ws) ? ws.cap : 0;
+  const unsigned long long cap = n_wide & kWideFull ? 0 : ws.cap;
   if (threadIdx.x < kOrderBuckets) bk[threadIdx.x] = 0u;
   __syncthreads();
   // a plan of one round keeps its tiles' buckets and their ranks there
@@ -751,7 +754,7 @@ __global__ __launch_bounds__(kNT) void k_fill_keys(Ws ws, int rec_blocks, int wi
   if ((int)blockIdx.x >= rec_blocks) {
     constexpr int kWaves = kNT / kWave;
     const uint32_t n_rest = ws.n_wide[kWideRest], n_first = *view_wide(ws, 0);
-    if (!n_wide) return;
+    if (!n_wide || n_wide & kWideFull) return;
     if (kScan) scan_in_fill(ws, n_wide, false, range_s, lw);
     fill_wide<4>(ws, n_rest, n_first, (blockIdx.x - rec_blocks) * kWaves + threadIdx.x / kWave,
                  wide_blocks * kWaves, range);
@@ -1136,7 +1139,7 @@ __launch_bounds__(NT) void k_sort_tiles(Ws ws, int lo_n, int hi_n, int queue) {
     const int64_t pitch = counter_pitch(ws.n_tiles);
     for (int a = 0; a < 3; a++)
       if (i < ws.n_tiles) ws.tile_count[a * pitch + i] = 0u;
-    if (i < ws.n_views) *view_wide(ws, ws.views[i].tile_base) = 0u;
+    if (i < ws.n_views) *view_wide(ws, i) = 0u;
     if (i == 0) {
       ws.n_wide[0] = 0u;
       ws.n_wide[kWideRest] = 0u;

@@ -71,6 +71,9 @@ __host__ __device__ inline int64_t counter_pitch(int64_t n_tiles) { return (n_ti
 constexpr int kWideWord = 2;
 // Word of n_wide that counts the wide records past their view's part of the list.
 constexpr int kWideRest = 4;
+// Words from one view's count of wide records to the next: atomics queue for a
+// line (40 views with 200 such records each, preprocess: 72 us side by side, 41 so).
+constexpr int kViewPitch = 8;
 
 enum : uint32_t { kFlagCapacity = 1u, kFlagNonfinite = 2u };
 
@@ -81,8 +84,9 @@ struct Ws {
   unsigned long long *n_pairs;
   uint32_t *iter;              // tracking iteration counter (bumped by preprocess)
   uint32_t *n_long;            // [2] tiles with lists for the mid and the huge-list sort
-  uint32_t *n_wide;            // [2] whether this pass has wide records, so far and (by the
-                               // scan) at all; odd_records; [kWideRest]
+  uint32_t *n_wide;            // [2] whether this pass has wide records and more than their
+                               // list holds, so far and (by the scan) in all; odd_records;
+                               // [kWideRest]
   uint32_t *long_tiles;        // [n_tiles] the queues, huge lists from the end (by the scan)
   uint32_t *tile_order;        // [n_tiles] compositing order, longest lists first (NULL: tile order)
   // descriptors
@@ -92,7 +96,9 @@ struct Ws {
   const int32_t *kf_use_off;   // [n_kf + 1]
   const DevKFUse *kf_use;      // per keyframe, the views rendering it
   int32_t n_kf, n_views, n_segs, n_rec, n_tiles, max_view_tiles;
-  int32_t max_view_px, pad0;
+  int32_t max_view_px;
+  uint32_t wide_part;          // places in the list of wide records per record, in 1/65536 (one at
+                               // most, a quarter of the capacity in all)
   int64_t P;                   // total pixels
   int64_t cap;                 // pair capacity
   // per record
@@ -129,8 +135,7 @@ struct Ws {
   uint32_t *last;              // [P] contributors end (relative to tile start)
   float *img;                  // [5][P] internal rgb(3), depth, sil
   float *gimg;                 // [5][P] internal upstream gradients
-  float *twist_part;           // [n_tiles][8]: six twist sums, the Eq. 1 loss, and
-                               // in the row of a view's first tile its wide records
+  float *twist_part;           // [n_tiles][8]: six twist sums, the Eq. 1 loss, one unused
   float *loss_part;            // [n_views][loss_blocks][4]
   double *ssim_map;            // [3 kinds][3 ch][P], FP64
   float *ssim_part;            // [n_views][3][loss_blocks]
@@ -233,9 +238,9 @@ __device__ __forceinline__ uint32_t block_exclusive_scan(uint32_t v, uint32_t *l
 // binned (by the tile sort).
 __device__ __forceinline__ uint32_t *odd_records(const Ws &ws) { return ws.n_wide + kWideWord; }
 
-// The wide records so far of the view whose first tile is tile_base.
-__device__ __forceinline__ uint32_t *view_wide(const Ws &ws, int64_t tile_base) {
-  return reinterpret_cast<uint32_t *>(ws.twist_part) + 8 * tile_base + 7;
+// The wide records so far of view v, counted behind the tile counters.
+__device__ __forceinline__ uint32_t *view_wide(const Ws &ws, int v) {
+  return ws.tile_count + 3 * counter_pitch(ws.n_tiles) + (int64_t)kViewPitch * v;
 }
 
 __device__ __forceinline__ bool all_finite(float a, float b, float c, float d) {

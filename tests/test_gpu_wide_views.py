@@ -50,3 +50,24 @@ def test_lists_of_a_few_wide_records_beside_many_small_ones(orc, order):
         # (the parts are a quarter of the capacity in all)
         v = order.index(0)
         assert wide[v] > need / 4 * ks[v].n / rec + 1 and need == first
+
+
+@pytest.mark.parametrize("n_views", [2, 49, 130])
+def test_wide_records_of_many_views(orc, n_views):
+    """Parts of some hundred places each, counted side by side."""
+    from paper_2506_02741_amd import render as R
+    k, okf = keyframe(orc, 150, (0.5, 2.0), 3)
+    poses = np.repeat(POSE[None], n_views, 0)
+    poses[:, 2, 3] = np.linspace(0.0, 2.0, n_views)  # from few tiles per record to many
+    plan, _ = R.plan_checked([k], [R.View(CAM, p, 0, 1) for p in poses], run=lambda p: p.render_fwd())
+    for _ in range(2):
+        plan.render_fwd()
+        st = plan.debug_state()
+        ids, ranges_all, first = np_(st["ids"]).astype(np.uint32), np_(st["ranges"]).astype(np.int64), 0
+        for v, p in enumerate(poses):
+            _, vals, ranges = orc.tile_lists(orc.ViewSpec(CAM, p), [okf], orc.params())
+            nt = ranges.shape[0]
+            assert same_ranges(ranges_all[v * nt:(v + 1) * nt] - first, ranges)
+            assert np.array_equal(ids[first:first + len(vals)], vals)
+            first += len(vals)
+        assert plan.status() == (0, first)
