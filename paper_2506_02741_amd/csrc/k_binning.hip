@@ -202,7 +202,7 @@ __device__ __forceinline__ bool is_wide(bool has, int x0, int y0, int x1, int y1
 // runs, which is free until then.  Half of it is divided among the views by
 // their records, so that a tile's wave reads its own view's alone (with one
 // list for all views the fill grew by their square: 300 views of 300 tiles with
-// 200 such records each took 2.11 ms, against 0.20; without any of them 0.10);
+// 200 such records each took 2.11 ms, against 0.19; without any of them 0.10);
 // the other half takes what a view's part does not (views of few records with
 // many wide ones, in plans of little capacity).
 __device__ __forceinline__ uint4 *wide_list(const Ws &ws) {
